@@ -237,9 +237,7 @@ hipError_t sample_weights_any(const qrfs_sampler* s, uint64_t index, int64_t n_s
                                        has_ap, D, d, f32, fx, fy, w, st);
 }
 
-// Largest grid of one launch: the work-items of a dispatch (blocks x
-// threads, at most 1024 threads per block here) must fit in 32 bits.
-constexpr int64_t kMaxLaunchBlocks = (int64_t)1 << 22;
+using qrfs::kMaxLaunchBlocks;
 
 // Runs launch_sum over all sets, splitting the grid so no launch exceeds
 // kMaxLaunchBlocks blocks.
@@ -805,13 +803,16 @@ qrfs_status qrfs_temporal_sf(qrfs_context* ctx, int64_t R, int64_t M, int32_t pr
     if (!ctx) return fail(QRFS_ERR_INVALID_ARG, "context is NULL");
     DeviceGuard g(ctx->device);
     if (!g.okay) return fail(QRFS_ERR_DEVICE, "cannot select device %d", ctx->device);
-    const int64_t nb = qrfs::temporal_blocks(R);
+    int rows = qrfs::TEMPORAL_ROWS;
+    if (ctx->ws_cap && align256((size_t)cdiv(R, rows) * M * 2 * sizeof(double)) > ctx->ws_cap)
+        rows = qrfs::TEMPORAL_ROWS_CAPPED;
+    const int64_t nb = cdiv(R, rows);
     qrfs_status st = ensure_workspace(ctx, align256((size_t)nb * M * 2 * sizeof(double)));
     if (st) return st;
     double* part = (double*)ctx->ws;
     hipStream_t stream_ = (hipStream_t)stream;
-    hipError_t e = qrfs::launch_temporal_rows(precision == QRFS_PREC_FP64, pistons, R, M, part,
-                                              stream_);
+    hipError_t e = qrfs::launch_temporal_rows(precision == QRFS_PREC_FP64, false, pistons, R, M,
+                                              rows, part, stream_);
     if (e != hipSuccess) return hip_fail(e, "temporal estimator launch");
     e = qrfs::launch_reduce_sf(part, nb, M, R, sf, sf_stderr, stream_);
     if (e != hipSuccess) return hip_fail(e, "reduction launch");
@@ -851,22 +852,34 @@ qrfs_status qrfs_temporal_piston_structure(qrfs_context* ctx, const qrfs_psd* ps
     const int64_t P = 2 * M;
     const bool fp64 = precision == QRFS_PREC_FP64;
     const size_t esize = fp64 ? sizeof(double) : sizeof(float);
+    // FP64 series of more than 64 samples use their equal spacing (tiles of
+    // 1024 samples: 268 cycles per frequency and tile against 148 per 64
+    // points, 32 samples of both telescopes, in the general kernel)
+    const bool series = fp64 && M > 64;
     // pieces of whole sets (at most ~1 GiB of frequencies and pistons) whose
-    // first realisation is a multiple of the estimator's row blocks, so the
-    // fixed-order reduction sees the same blocks however the sets are cut
-    const int64_t q = qrfs::TEMPORAL_ROWS_PER_BLOCK / std::gcd(R_block,
-                                                              (int64_t)qrfs::TEMPORAL_ROWS_PER_BLOCK);
+    // first realisation is a multiple of the estimator's row blocks (of
+    // either size), so the fixed-order reduction sees the same blocks however
+    // the sets are cut
+    const int64_t q =
+        qrfs::TEMPORAL_ROWS_CAPPED / std::gcd(R_block, (int64_t)qrfs::TEMPORAL_ROWS_CAPPED);
     const size_t per_set = (size_t)K * 4 * sizeof(double) + (size_t)R_block * P * esize;
     int64_t spb = (int64_t)(((size_t)1 << 30) / per_set);
     spb = spb / q * q;
     if (spb < q) spb = q;
     if (spb > n_sets) spb = n_sets;
-    const int64_t nb = qrfs::temporal_blocks(R);
-    const size_t part_bytes = align256((size_t)nb * M * 2 * sizeof(double));
     const size_t pt_bytes = align256((size_t)P * sizeof(double));
     const size_t arr = align256((size_t)spb * K * sizeof(double));
-    const size_t pist_bytes = align256((size_t)spb * R_block * P * esize);
-    if ((st = ensure_workspace(ctx, part_bytes + 2 * pt_bytes + 4 * arr + pist_bytes))) return st;
+    // such a series keeps the differential pistons only
+    const size_t pist_bytes = align256((size_t)spb * R_block * (series ? M : P) * esize);
+    const size_t fixed_bytes = 2 * pt_bytes + 4 * arr + pist_bytes;
+    int rows_block = qrfs::TEMPORAL_ROWS;
+    size_t part_bytes = align256((size_t)cdiv(R, rows_block) * M * 2 * sizeof(double));
+    if (ctx->ws_cap && part_bytes + fixed_bytes > ctx->ws_cap) {
+        rows_block = qrfs::TEMPORAL_ROWS_CAPPED;
+        part_bytes = align256((size_t)cdiv(R, rows_block) * M * 2 * sizeof(double));
+    }
+    const int64_t nb = cdiv(R, rows_block);
+    if ((st = ensure_workspace(ctx, part_bytes + fixed_bytes))) return st;
     char* base = (char*)ctx->ws;
     double* part = (double*)base;
     double* px = (double*)(base + part_bytes);
@@ -880,8 +893,11 @@ qrfs_status qrfs_temporal_piston_structure(qrfs_context* ctx, const qrfs_psd* ps
     hipStream_t stream_ = (hipStream_t)stream;
     const double c = qrfs::psd_constant(psd->c, psd->wavelength);
 
-    hipError_t e = qrfs::launch_taylor_points(c1, c2, v, dt, M, px, py, stream_);
-    if (e != hipSuccess) return hip_fail(e, "point launch");
+    hipError_t e = hipSuccess;
+    if (!series) {
+        e = qrfs::launch_taylor_points(c1, c2, v, dt, M, px, py, stream_);
+        if (e != hipSuccess) return hip_fail(e, "point launch");
+    }
     for (int64_t s0 = 0; s0 < n_sets; s0 += spb) {
         const int64_t s1 = s0 + spb < n_sets ? s0 + spb : n_sets;
         const int64_t ns = s1 - s0;
@@ -892,30 +908,55 @@ qrfs_status qrfs_temporal_piston_structure(qrfs_context* ctx, const qrfs_psd* ps
                                area, w, stream_);
         if (e != hipSuccess) return hip_fail(e, "sampler / weights launch");
         // the piece as a problem of its own: realisations r0 .. r0 + rows
-        qrfs::SumArgs a{};
-        a.K = K;
-        a.fx = fx;
-        a.fy = fy;
-        a.w = w;
-        a.P = P;
-        a.px = px;
-        a.py = py;
-        a.R = rows;
-        a.R_block = R_block;
-        a.seed = rng->seed;
-        a.counter = rng->counter + (uint64_t)r0;
-        a.mode = rng->mode;
-        a.coef = nullptr;
-        a.out = pist;
-        a.partial = nullptr;
-        a.ksplit = 1;
-        a.kspan = K;
-        a.phi_part = nullptr;
-        if ((st = run_sum(precision, qrfs::BASIS_PHASE, qrfs::EPI_STORE, a, ns, stream_)))
-            return st;
-        e = qrfs::launch_temporal_rows(fp64, pist, rows, M,
-                                       part + (r0 / qrfs::TEMPORAL_ROWS_PER_BLOCK) * M * 2,
-                                       stream_);
+        if (series) {
+            // the samples are equally spaced: rows of 32 of them share the
+            // sine and cosine of their first, and p1 - p2 is formed per frequency
+            qrfs::SepArgs a{};
+            a.K = K;
+            a.fx = fx;
+            a.fy = fy;
+            a.w = w;
+            a.R = rows;
+            a.R_block = R_block;
+            a.P = M;
+            a.seed = rng->seed;
+            a.counter = rng->counter + (uint64_t)r0;
+            a.mode = rng->mode;
+            a.V = 32;
+            a.ox = c1[0];
+            a.oy = c1[1];
+            a.sx = -v[0] * dt;
+            a.sy = -v[1] * dt;
+            a.dx = c2[0] - c1[0];
+            a.dy = c2[1] - c1[1];
+            a.out = (double*)pist;
+            e = qrfs::launch_series_diff(a, stream_);
+            if (e != hipSuccess) return hip_fail(e, "time-series launch");
+        } else {
+            qrfs::SumArgs a{};
+            a.K = K;
+            a.fx = fx;
+            a.fy = fy;
+            a.w = w;
+            a.P = P;
+            a.px = px;
+            a.py = py;
+            a.R = rows;
+            a.R_block = R_block;
+            a.seed = rng->seed;
+            a.counter = rng->counter + (uint64_t)r0;
+            a.mode = rng->mode;
+            a.coef = nullptr;
+            a.out = pist;
+            a.partial = nullptr;
+            a.ksplit = 1;
+            a.kspan = K;
+            a.phi_part = nullptr;
+            if ((st = run_sum(precision, qrfs::BASIS_PHASE, qrfs::EPI_STORE, a, ns, stream_)))
+                return st;
+        }
+        e = qrfs::launch_temporal_rows(fp64, series, pist, rows, M, rows_block,
+                                       part + (r0 / rows_block) * M * 2, stream_);
         if (e != hipSuccess) return hip_fail(e, "temporal estimator launch");
     }
     e = qrfs::launch_reduce_sf(part, nb, M, R, sf, sf_stderr, stream_);

@@ -22,6 +22,10 @@ inline double psd_constant(double c, double wavelength) {
     return k;
 }
 
+// Largest grid of one launch: the work-items of a dispatch (blocks x
+// threads, at most 1024 threads per block here) must fit in 32 bits.
+constexpr int64_t kMaxLaunchBlocks = (int64_t)1 << 22;
+
 enum Basis : int {
     BASIS_PHASE = 0,   // (cos, sin)(2 pi f.x_p) w_k
     BASIS_PISTON = 1,  // (cos, sin)(2 pi f.c_p) w_k F(D_p, d_p, |f_k|)
@@ -191,20 +195,42 @@ hipError_t launch_sample_weights(int scheme, uint64_t s0x, uint64_t s0y, uint64_
                                  int has_ap, double D, double d, int f32, double* fx,
                                  double* fy, double* w, hipStream_t st);
 
+// Sums of Eq. 3 in binary64 over points with product structure (a time
+// series): out[r][p] for realisations r < R (sets of R_block) and points
+// p = u V + v at o + p s, minus the sums at those points plus (dx, dy).
+struct SepArgs {
+    int64_t K;
+    const double* fx;
+    const double* fy;
+    const double* w;
+    int64_t R, R_block, P;
+    int64_t r0;              // first realisation of a launch (set by the launcher)
+    uint64_t seed, counter;  // counter: of realisation 0
+    int32_t mode;
+    int32_t V;               // samples per row, a multiple of 32
+    double ox, oy, sx, sy;   // first point and step
+    double dx, dy;
+    double* out;             // [R][P]
+};
+hipError_t launch_series_diff(const SepArgs& a, hipStream_t st);
+
 // Frozen-flow temporal structure function (time series of M <= 4096 points).
 constexpr int TEMPORAL_MAX_M = 4096;
-constexpr int TEMPORAL_ROWS_PER_BLOCK = 8;
+// realisations per block of the estimator; twice as many where the
+// workspace of the smaller blocks would exceed the context's cap
+constexpr int TEMPORAL_ROWS = 4;
+constexpr int TEMPORAL_ROWS_CAPPED = 8;
 // points c1 - v m dt (m < M), then c2 - v m dt
 hipError_t launch_taylor_points(const double c1[2], const double c2[2], const double v[2],
                                 double dt, int64_t M, double* px, double* py, hipStream_t st);
-// blocks of TEMPORAL_ROWS_PER_BLOCK realisations that launch_temporal_rows uses
-int64_t temporal_blocks(int64_t R);
-// pist [R][2][M] (double when fp64, else float) -> part[temporal_blocks(R)][M][2]
-hipError_t launch_temporal_rows(bool fp64, const void* pist, int64_t R, int64_t M, double* part,
-                                hipStream_t st);
+// pist: pistons [R][2][M], or their differences [R][M] when `diff` (double
+// when fp64, else float) -> part[ceil(R / rows)][M][2]
+hipError_t launch_temporal_rows(bool fp64, bool diff, const void* pist, int64_t R, int64_t M,
+                                int rows, double* part, hipStream_t st);
 
-// sf[p] = S2/R, stderr[p] from partial[n_tiles][P][2] in a fixed order.
-hipError_t launch_reduce_sf(const double* partial, int64_t n_tiles, int64_t P, int64_t R,
+// sf[p] = S2/R, stderr[p] from partial[n_tiles][P][2] in a fixed order
+// (partial is overwritten).
+hipError_t launch_reduce_sf(double* partial, int64_t n_tiles, int64_t P, int64_t R,
                             double* sf, double* sf_stderr, hipStream_t st);
 
 }  // namespace qrfs

@@ -1020,58 +1020,140 @@ __global__ void k_reset_counter(unsigned* counter) {
 }
 
 // ----------------------------------------------------- split-K squares ----
-// Block (row block rb, column tile): 256 threads = 8 row groups x 32
-// columns.  Adds the K-range partial sums of each differential piston in a
-// fixed order, then accumulates its square and fourth power per column over
-// the block's rows; the 8 row groups are combined in a fixed order.
-constexpr int SF_ROWS = 64;  // rows per block: ~1600 blocks for 1e5 rows, enough to hide load latency
+// Block (row block rb, column tile): 64 rows x 32 columns on 256 threads,
+// RG = 8 VEC row groups of VEC-wide columns.  Adds the K-range partial sums of
+// each differential piston in a fixed order, then accumulates its square and
+// fourth power per column over the block's rows; the row groups are combined
+// in a fixed order.  Bound by the reads of the partial sums (166 MB at 1e5
+// rows x 32 columns x 13 ranges, 34 us at the 4.9 TB/s of a large copy; 50 us
+// with scalar loads), and by their latency where few rows leave a few blocks
+// (16 us for 300 rows x 8 ranges when every load waited for the one before):
+// a thread issues the loads of up to 8 ranges together, 16 bytes wide where
+// the rows allow it (P a multiple of 4).
+constexpr int SF_ROWS = 64;  // rows per block: ~1600 blocks for 1e5 rows
 
+template <int VEC>
 __global__ __launch_bounds__(256) void k_sfsum_rows(const float* __restrict__ phi, int ksplit,
                                                     int64_t R, int64_t P,
                                                     double* __restrict__ partial) {
+    typedef float fvec __attribute__((ext_vector_type(VEC)));
+    constexpr int RG = 8 * VEC, CL = 32 / VEC;
+    __shared__ double r2[RG][32], r4[RG][32];
+    const int cl = threadIdx.x % CL, rg = threadIdx.x / CL;
+    const int64_t col = (int64_t)blockIdx.y * 32 + cl * VEC;
+    double s2[VEC] = {}, s4[VEC] = {};
+#pragma unroll 2
+    for (int j = 0; j < SF_ROWS / RG; ++j) {
+        const int64_t r = (int64_t)blockIdx.x * SF_ROWS + rg + RG * j;
+        const bool ok = r < R && col < P;
+        double v[VEC] = {};
+        for (int k0 = 0; k0 < ksplit; k0 += 8) {
+            fvec t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                t[i] = fvec(0.0f);
+                if (ok && k0 + i < ksplit)
+                    t[i] = *(const fvec*)&phi[((int64_t)(k0 + i) * R + r) * P + col];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[e] += (double)t[i][e];
+        }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const double v2 = v[e] * v[e];
+            s2[e] += v2;
+            s4[e] += v2 * v2;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        r2[rg][cl * VEC + e] = s2[e];
+        r4[rg][cl * VEC + e] = s4[e];
+    }
+    __syncthreads();
+    // thread (c, q): row groups q, q + 8, ... of column c, then the 8 shares
+    const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+    double t2 = 0.0, t4 = 0.0;
+#pragma unroll
+    for (int g = 0; g < VEC; ++g) {
+        t2 += r2[q + 8 * g][c];
+        t4 += r4[q + 8 * g][c];
+    }
+    if constexpr (VEC > 1) {
+        __syncthreads();
+        r2[q][c] = t2;
+        r4[q][c] = t4;
+        __syncthreads();
+    }
+    const int64_t cc = (int64_t)blockIdx.y * 32 + c;
+    if (q == 0 && cc < P) {
+        for (int g = 1; g < 8; ++g) {
+            t2 += r2[g][c];
+            t4 += r4[g][c];
+        }
+        partial[((int64_t)blockIdx.x * P + cc) * 2] = t2;
+        partial[((int64_t)blockIdx.x * P + cc) * 2 + 1] = t4;
+    }
+}
+
+// ------------------------------------------------------------- reduce ----
+// Long lists of tiles first shrink in place: block b adds tiles
+// [64 b, 64 (b + 1)) of 32 columns (coalesced, 8 loads in flight per thread)
+// in a fixed order and leaves the sum in its first tile, which no other
+// block reads.  One block per column alone reads 16 bytes of every row of
+// tiles: 20000 tiles x 32 columns took 49 us.
+constexpr int RT_TILES = 64;
+
+__global__ __launch_bounds__(256) void k_reduce_tiles(double* __restrict__ partial,
+                                                      int64_t n_tiles, int64_t P) {
     __shared__ double r2[8][32], r4[8][32];
-    const int c = threadIdx.x & 31;
-    const int rg = threadIdx.x >> 5;
+    const int c = threadIdx.x & 31, rg = threadIdx.x >> 5;
     const int64_t col = (int64_t)blockIdx.y * 32 + c;
-    const int64_t r0 = (int64_t)blockIdx.x * SF_ROWS;
-    const int64_t r1 = r0 + SF_ROWS < R ? r0 + SF_ROWS : R;
+    const int64_t t0 = (int64_t)blockIdx.x * RT_TILES;
+    double2* src = (double2*)partial + col;
     double s2 = 0.0, s4 = 0.0;
     if (col < P) {
-        for (int64_t r = r0 + rg; r < r1; r += 8) {
-            double v = 0.0;
-            for (int k = 0; k < ksplit; ++k) v += (double)phi[((int64_t)k * R + r) * P + col];
-            double v2 = v * v;
-            s2 += v2;
-            s4 += v2 * v2;
+        double2 v[RT_TILES / 8];
+#pragma unroll
+        for (int i = 0; i < RT_TILES / 8; ++i) {
+            const int64_t t = t0 + rg + 8 * i;
+            v[i] = t < n_tiles ? src[t * P] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int i = 0; i < RT_TILES / 8; ++i) {
+            s2 += v[i].x;
+            s4 += v[i].y;
         }
     }
     r2[rg][c] = s2;
     r4[rg][c] = s4;
     __syncthreads();
     if (rg == 0 && col < P) {
-        double t2 = 0.0, t4 = 0.0;
-        for (int g = 0; g < 8; ++g) {
-            t2 += r2[g][c];
-            t4 += r4[g][c];
+        for (int g = 1; g < 8; ++g) {
+            s2 += r2[g][c];
+            s4 += r4[g][c];
         }
-        partial[((int64_t)blockIdx.x * P + col) * 2] = t2;
-        partial[((int64_t)blockIdx.x * P + col) * 2 + 1] = t4;
+        src[t0 * P] = make_double2(s2, s4);
     }
 }
 
-// ------------------------------------------------------------- reduce ----
-// One block per column; partial sums over row tiles in a fixed order
-// (strided by thread, then a fixed tree), so results are bit-reproducible.
+// One block per column; partial sums over row tiles (every `step`-th) in a
+// fixed order (strided by thread, then a fixed tree), so results are
+// bit-reproducible.
 __global__ __launch_bounds__(256) void k_reduce_sf(const double* __restrict__ partial,
-                                                   int64_t n_tiles, int64_t P, int64_t R,
-                                                   double* __restrict__ sf,
+                                                   int64_t n_tiles, int64_t step, int64_t P,
+                                                   int64_t R, double* __restrict__ sf,
                                                    double* __restrict__ sf_stderr) {
     __shared__ double r2[256], r4[256];
     const int64_t p = blockIdx.x;
     double s2 = 0.0, s4 = 0.0;
+    const double2* src = (const double2*)partial + p;
     for (int64_t t = threadIdx.x; t < n_tiles; t += 256) {
-        s2 += partial[(t * P + p) * 2];
-        s4 += partial[(t * P + p) * 2 + 1];
+        const double2 v = src[t * step * P];
+        s2 += v.x;
+        s4 += v.y;
     }
     r2[threadIdx.x] = s2;
     r4[threadIdx.x] = s4;
@@ -1097,10 +1179,21 @@ __global__ __launch_bounds__(256) void k_reduce_sf(const double* __restrict__ pa
 // ----------------------------------------------------------- launchers ----
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-hipError_t launch_reduce_sf(const double* partial, int64_t n_tiles, int64_t P, int64_t R,
-                            double* sf, double* sf_stderr, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_sf, dim3((unsigned)P), dim3(256), 0, st, partial, n_tiles, P, R, sf,
-                       sf_stderr);
+hipError_t launch_reduce_sf(double* partial, int64_t n_tiles, int64_t P, int64_t R, double* sf,
+                            double* sf_stderr, hipStream_t st) {
+    // two passes from 1024 tiles on, where one block per column takes 4 or
+    // more dependent rounds of loads
+    int64_t step = 1;
+    const int64_t blocks = cdiv(n_tiles, RT_TILES) * cdiv(P, 32);
+    if (n_tiles >= 1024 && cdiv(P, 32) < 65536 && blocks < ((int64_t)1 << 24)) {
+        step = RT_TILES;
+        hipLaunchKernelGGL(k_reduce_tiles,
+                           dim3((unsigned)cdiv(n_tiles, RT_TILES), (unsigned)cdiv(P, 32)),
+                           dim3(256), 0, st, partial, n_tiles, P);
+        n_tiles = cdiv(n_tiles, RT_TILES);
+    }
+    hipLaunchKernelGGL(k_reduce_sf, dim3((unsigned)P), dim3(256), 0, st, partial, n_tiles, step, P,
+                       R, sf, sf_stderr);
     return hipGetLastError();
 }
 
@@ -1394,7 +1487,10 @@ hipError_t launch_batch(int precision, BatchShape shape, bool has_ap, const SumA
 hipError_t launch_sfsum_rows(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
                              hipStream_t st) {
     dim3 g((unsigned)cdiv(R, SF_ROWS), (unsigned)cdiv(P, 32));
-    hipLaunchKernelGGL(k_sfsum_rows, g, dim3(256), 0, st, phi, ksplit, R, P, partial);
+    if (P % 4 == 0)
+        hipLaunchKernelGGL(k_sfsum_rows<4>, g, dim3(256), 0, st, phi, ksplit, R, P, partial);
+    else
+        hipLaunchKernelGGL(k_sfsum_rows<1>, g, dim3(256), 0, st, phi, ksplit, R, P, partial);
     return hipGetLastError();
 }
 

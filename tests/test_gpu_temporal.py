@@ -122,3 +122,40 @@ def test_paper_configuration_statistics(q, ctx):
     assert np.all(np.abs(z) < 4.5)
     iso = A.temporal_sf(lags * dt, B, v, R0, L0, D, d)
     print("square / isotropic", np.round(ex / iso, 4))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("R,M", [(1, 1), (3, 2), (5, 7), (4, 8), (9, 9), (2, 16), (3, 17), (5, 63),
+                                 (6, 129), (3, 1000), (5, 1024), (2, 1025), (3, 2051), (2, 4096)])
+def test_temporal_sf_tile_edges(q, ctx, dtype, R, M):
+    """The estimator at the edges of its 8 x 8 tiles, of its lag groups and
+    of its two sizes.  Sums of at most 4096 squares in binary64: 1e-12."""
+    rng = np.random.default_rng(M)
+    p = torch.as_tensor(np.cumsum(rng.normal(size=(R, 2, M)), axis=2), dtype=dtype).cuda()
+    print(f"temporal_sf R{R} M{M}", flush=True)
+    sf, se = ctx.temporal_sf(p)
+    rsf, rse = oracle.temporal_sf(host(p).reshape(R, 2, M))
+    assert host(sf)[0] == 0.0
+    assert np.all(np.abs(host(sf) - rsf) <= 1e-12 * np.max(rsf))
+    assert np.all(np.abs(host(se) - rse) <= 1e-7 * np.max(rse) + 1e-300)
+
+
+@pytest.mark.parametrize("M", [64, 65, 96, 1023, 1056])
+@pytest.mark.parametrize("K,R,R_block,mode", [(9, 5, 1, 0), (130, 3, 2, 1), (1225, 4, 1, 0),
+                                              (4, 700, 7, 0)])
+def test_temporal_series_edges(q, ctx, M, K, R, R_block, mode):
+    """FP64 series around the length from which the equal spacing is used
+    (65), ragged tiles of 32 x 32 samples, ragged frequency groups, both
+    block sizes, both coefficient forms; wind and baseline oblique."""
+    N, df, dt = int(math.isqrt(K)) + 1, 0.02, 0.013
+    c1, c2, v = (1.5, -2.0), (40.0, 31.0), (-7.0, 9.5)
+    n_sets = math.ceil(R / R_block)
+    s = q.cartesian_sampler(N, df, index=11)
+    print(f"series M{M} K{K} R{R} Rb{R_block} mode{mode}", flush=True)
+    sf, se = ctx.temporal_piston_structure(q.psd(R0, L0), q.Aperture(D, d), c1, c2, v, dt, M, s,
+                                           K, R, R_block, rng=q.Rng(5, 2, mode), precision=0)
+    fx, fy, area = oracle.sample_cartesian(n_sets, K, N, df, index=11)
+    w = oracle.weights(fx, fy, area, r0=R0, L0=L0, D=D, d=d)
+    rsf, rse = oracle.temporal_experiment(fx, fy, w, c1, c2, v, dt, M, R, R_block, K=K, seed=5,
+                                          counter=2, mode=mode)
+    assert np.max(np.abs(host(sf) - rsf)) <= 1e-9 * np.max(rsf)
