@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqrfs.so")
 PEAKS_LIB = os.path.join(HERE, "libqrfs_peaks.so")
 PEAKS_SOURCES = ["qrfs_peaks.hip"]
-SOURCES = ["qrfs_frequencies.hip", "qrfs_kernels.hip", "qrfs_wide.hip", "qrfs_separable.hip", "qrfs_temporal.hip", "qrfs_measures.hip",
+SOURCES = ["qrfs_frequencies.hip", "qrfs_kernels.hip", "qrfs_wide.hip", "qrfs_f64.hip", "qrfs_separable.hip", "qrfs_temporal.hip", "qrfs_measures.hip",
            "qrfs_pairs.hip", "qrfs_proposal.hip", "qrfs_api.cpp", "qrfs_batch.cpp", "qrfs_proposal_api.cpp",
            "qrfs_plan.cpp"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Werror",

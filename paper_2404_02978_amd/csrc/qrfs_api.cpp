@@ -243,8 +243,8 @@ using qrfs::kMaxLaunchBlocks;
 // kMaxLaunchBlocks blocks.
 qrfs_status run_sum(int precision, int basis, int epi, qrfs::SumArgs a, int64_t n_sets,
                     hipStream_t st) {
-    int64_t rts = qrfs::sum_row_tiles_per_set(precision, basis, a.R_block, a.P);
-    int64_t cts = qrfs::sum_col_tiles(precision, basis, a.R_block, a.P);
+    int64_t rts = qrfs::sum_row_tiles_per_set(precision, basis, a.R, a.R_block, a.P);
+    int64_t cts = qrfs::sum_col_tiles(precision, basis, a.R, a.R_block, a.P);
     int64_t per_set = rts * cts * (a.ksplit > 1 ? a.ksplit : 1);
     int64_t max_sets = kMaxLaunchBlocks / (per_set > 0 ? per_set : 1);
     if (max_sets < 1) return fail(QRFS_ERR_INVALID_ARG, "problem too large for one set");
@@ -663,7 +663,7 @@ qrfs_status qrfs_diff_piston_structure(qrfs_context* ctx, const qrfs_psd* psd,
     if (!g.okay) return fail(QRFS_ERR_DEVICE, "cannot select device %d", ctx->device);
 
     const int64_t n_sets = cdiv(R, R_block);
-    const int64_t rts = qrfs::sum_row_tiles_per_set(precision, qrfs::BASIS_DIFF, R_block, nB);
+    const int64_t rts = qrfs::sum_row_tiles_per_set(precision, qrfs::BASIS_DIFF, R, R_block, nB);
     const qrfs::SfPlan plan = qrfs::sf_plan(precision, K, R, R_block, nB);
     const size_t partial_bytes = align256((size_t)(plan.n_partial_tiles * nB) * 2 * sizeof(double));
     const size_t phi_bytes = align256(plan.phi_floats * sizeof(float));

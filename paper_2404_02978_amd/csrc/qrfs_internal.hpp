@@ -170,10 +170,18 @@ hipError_t launch_set_sf(int64_t n_sets, int64_t K, const double* fx, const doub
 hipError_t launch_sfsum_rows(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
                              hipStream_t st);
 
-// Row tiles one set occupies in `launch_sum` for this precision and R_block
+// Tile of the binary64 contraction of shared sets: rows per wave (16 MR),
+// columns per block (16 NC), row waves that share a basis.
+struct FmShape {
+    int MR, NC, WR;
+};
+FmShape fm_shape(int64_t R, int64_t R_block, int64_t P);
+hipError_t launch_sum_fm(int basis, int epi, const SumArgs& a, hipStream_t st);
+
+// Row tiles one set occupies in `launch_sum` for this precision and problem
 // (needed to size the partial-sum buffer).
-int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R_block, int64_t P);
-int64_t sum_col_tiles(int precision, int basis, int64_t R_block, int64_t P);
+int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R, int64_t R_block, int64_t P);
+int64_t sum_col_tiles(int precision, int basis, int64_t R, int64_t R_block, int64_t P);
 
 hipError_t launch_sum(int precision, int basis, int epi, const SumArgs& a, hipStream_t st);
 

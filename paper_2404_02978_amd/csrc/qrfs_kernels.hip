@@ -1,8 +1,9 @@
 // qrfs_kernels.hip -- gfx950 kernels of the quasi-random frequency sampling
 // path (arXiv 2404.02978): the fused coefficient x basis contraction of
-// Eq. 3 (FP64 vector ALU, FP32 MFMA, split-BF16 and BF16x6 MFMA), its
-// epilogues and the fixed-order structure-function reduction.  The sampler
-// and the weights live in qrfs_frequencies.hip.
+// Eq. 3 (FP32 MFMA, split-BF16, BF16x6 and FP16x3 MFMA, narrow sets on the
+// vector ALU), its epilogues and the fixed-order structure-function
+// reduction.  The sampler and the weights live in qrfs_frequencies.hip, the
+// binary64 contraction of shared sets in qrfs_f64.hip.
 #include "qrfs_device.hpp"
 #include "qrfs_internal.hpp"
 #include "qrfs_mfma.hpp"
@@ -10,183 +11,13 @@
 namespace qrfs {
 
 
-// --------------------------------------------------- tile bookkeeping ----
-struct TileInfo {
-    int64_t sl;         // set index within the launch
-    int64_t rt;         // row tile within the set
-    int64_t ct;         // column tile
-    int64_t row_begin;  // first row of the tile
-    int64_t row_end;    // one past the last valid row of the set
-};
-
-__device__ __forceinline__ TileInfo decode_tile(const SumArgs& a, int64_t row_tiles,
-                                                int64_t col_tiles, int64_t MT) {
-    TileInfo t;
-    int64_t b = blockIdx.x;
-    t.ct = b % col_tiles;
-    b /= col_tiles;
-    t.rt = b % row_tiles;
-    t.sl = b / row_tiles;
-    int64_t s = a.set0 + t.sl;
-    t.row_begin = s * a.R_block + t.rt * MT;
-    int64_t se = (s + 1) * a.R_block;
-    t.row_end = se < a.R ? se : a.R;
-    return t;
-}
-
-// -------------------------------------------------- FP64 vector kernel ----
-// Tile: 32 rows x 32 columns, 256 threads; thread (tp, tg) owns column tp
-// and rows 4 tg .. 4 tg + 3.  Per chunk of 32 frequencies the block builds
-// the FP64 coefficient tile and the FP64 basis tile in LDS, then every
-// thread accumulates its 4 rows in FP64, frequency by frequency.
-constexpr int F64_TP = 32;
-constexpr int F64_TG = 8;
-constexpr int F64_RPT = 4;
-constexpr int F64_TR = F64_TG * F64_RPT;
-constexpr int F64_KC = 32;
-
-template <int BASIS, int EPI>
-__global__ __launch_bounds__(256) void k_sum_f64(SumArgs a, int64_t row_tiles,
-                                                 int64_t col_tiles) {
-    __shared__ double sBc[F64_KC][F64_TP];
-    __shared__ double sBs[F64_KC][F64_TP];
-    __shared__ double sC[F64_TR][2 * F64_KC + 1];
-    __shared__ double sfx[F64_KC], sfy[F64_KC], sw[F64_KC];
-    __shared__ double spx[F64_TP], spy[F64_TP], sD[F64_TP], sd[F64_TP];
-    __shared__ double sred[F64_TG][F64_TP][2];
-
-    const int tid = threadIdx.x;
-    const int tp = tid % F64_TP;
-    const int tg = tid / F64_TP;
-    const TileInfo ti = decode_tile(a, row_tiles, col_tiles, F64_TR);
-    const int64_t col0 = ti.ct * F64_TP;
-    if (tid < F64_TP) {
-        int64_t p = col0 + tid;
-        bool ok = p < a.P;
-        spx[tid] = ok ? a.px[p] : 0.0;
-        spy[tid] = ok ? a.py[p] : 0.0;
-        if (BASIS == BASIS_PISTON) {
-            sD[tid] = ok ? a.apD[p] : 1.0;
-            sd[tid] = ok ? a.apd[p] : 0.0;
-        }
-    }
-    const double* fx = a.fx + ti.sl * a.K;
-    const double* fy = a.fy + ti.sl * a.K;
-    const double* w = a.w + ti.sl * a.K;
-    const int64_t twoK = 2 * a.K;
-
-    double acc[F64_RPT];
-#pragma unroll
-    for (int q = 0; q < F64_RPT; ++q) acc[q] = 0.0;
-
-    for (int64_t k0 = 0; k0 < a.K; k0 += F64_KC) {
-        __syncthreads();
-        if (tid < F64_KC) {
-            int64_t k = k0 + tid;
-            bool ok = k < a.K;
-            sfx[tid] = ok ? fx[k] : 0.0;
-            sfy[tid] = ok ? fy[k] : 0.0;
-            sw[tid] = ok ? w[k] : 0.0;
-        }
-        // coefficients: 32 rows x 16 Philox blocks (4 coefficients each)
-        for (int i = tid; i < F64_TR * (F64_KC / 2); i += 256) {
-            int rr = i / (F64_KC / 2);
-            int bt = i % (F64_KC / 2);
-            int64_t r = ti.row_begin + rr;
-            double g[4] = {0.0, 0.0, 0.0, 0.0};
-            if (r < ti.row_end) {
-                if (a.coef) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        int64_t j = 2 * k0 + 4 * bt + q;
-                        g[q] = j < twoK ? a.coef[r * twoK + j] : 0.0;
-                    }
-                } else {
-                    coef4_f64(a.seed, a.counter + (uint64_t)r, (uint32_t)(k0 / 2 + bt), a.mode, g);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sC[rr][4 * bt + q] = g[q];
-        }
-        __syncthreads();
-        for (int i = tid; i < F64_KC * F64_TP; i += 256) {
-            int kk = i / F64_TP;
-            int pp = i % F64_TP;
-            double t = sfx[kk] * spx[pp] + sfy[kk] * spy[pp];
-            if (BASIS == BASIS_PISTON) t += grad_shift(a.grad);
-            double rf = frac_centered(t);
-            double s, c;
-            if (BASIS == BASIS_DIFF) {
-                // sin and cos of pi rf: cos 2 pi rf - 1 = -2 sin^2, sin 2 pi rf = 2 sin cos
-                double sh, ch;
-                sincos2pi_reduced(0.5 * rf, sh, ch);
-                c = -2.0 * sh * sh;
-                s = 2.0 * sh * ch;
-            } else {
-                sincos2pi_reduced(rf, s, c);
-            }
-            double amp = sw[kk];
-            if (BASIS == BASIS_PISTON)
-                amp *= aperture_filter(sD[pp], sd[pp], sqrt(sfx[kk] * sfx[kk] + sfy[kk] * sfy[kk])) *
-                       grad_factor(a.grad, a.gx, a.gy, sfx[kk], sfy[kk]);
-            sBc[kk][pp] = amp * c;
-            sBs[kk][pp] = amp * s;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int kk = 0; kk < F64_KC; ++kk) {
-            double cb = sBc[kk][tp];
-            double sb = sBs[kk][tp];
-#pragma unroll
-            for (int q = 0; q < F64_RPT; ++q) {
-                const double* cr = sC[tg * F64_RPT + q];
-                acc[q] = fma(cr[2 * kk], cb, fma(cr[2 * kk + 1], sb, acc[q]));
-            }
-        }
-    }
-
-    const int64_t col = col0 + tp;
-    if (EPI == EPI_STORE) {
-        double* out = (double*)a.out;
-#pragma unroll
-        for (int q = 0; q < F64_RPT; ++q) {
-            int64_t r = ti.row_begin + tg * F64_RPT + q;
-            if (r < ti.row_end && col < a.P) out[r * a.P + col] = acc[q];
-        }
-    } else {
-        double s2 = 0.0, s4 = 0.0;
-#pragma unroll
-        for (int q = 0; q < F64_RPT; ++q) {
-            int64_t r = ti.row_begin + tg * F64_RPT + q;
-            if (r < ti.row_end) {
-                double d2 = acc[q] * acc[q];
-                s2 += d2;
-                s4 += d2 * d2;
-            }
-        }
-        sred[tg][tp][0] = s2;
-        sred[tg][tp][1] = s4;
-        __syncthreads();
-        if (tid < F64_TP && col < a.P) {
-            double t2 = 0.0, t4 = 0.0;
-            for (int g = 0; g < F64_TG; ++g) {
-                t2 += sred[g][tid][0];
-                t4 += sred[g][tid][1];
-            }
-            double* dst = a.partial + ((ti.sl * row_tiles + ti.rt) * a.P + col) * 2;
-            dst[0] = t2;
-            dst[1] = t4;
-        }
-    }
-}
-
 // ------------------------------------------- FP64, narrow frequency sets ----
 // Sets of at most 8 realisations (the paper draws fresh frequencies for
 // every realisation: R_block = 1): one point per thread, RB rows per block.
 // Per chunk of 64 frequencies the block stages fx, fy, w and the RB rows'
 // coefficients in LDS (drawn once per block); each thread evaluates its
 // point's basis once per frequency and adds it into its RB rows, in the
-// same order and with the same fused products as k_sum_f64.  A 32-row tile
+// same order for any tiling.  A 16-row matrix tile
 // would spend most of its contraction on rows the set does not have.
 constexpr int F64N_KC = 64;
 
@@ -1220,14 +1051,17 @@ static MfmaShape mfma_shape(int precision, int basis, int64_t R_block, int64_t P
     return s;
 }
 
-int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R_block, int64_t P) {
-    if (precision == 0) return cdiv(R_block, F64_TR);
+int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R, int64_t R_block, int64_t P) {
+    if (precision == 0) {
+        const FmShape f = fm_shape(R, R_block, P);
+        return cdiv(R_block, 16 * f.MR * f.WR);
+    }
     MfmaShape s = mfma_shape(precision, basis, R_block, P);
     return cdiv(R_block, 32 * s.MW * s.WV);
 }
 
-int64_t sum_col_tiles(int precision, int basis, int64_t R_block, int64_t P) {
-    if (precision == 0) return cdiv(P, F64_TP);
+int64_t sum_col_tiles(int precision, int basis, int64_t R, int64_t R_block, int64_t P) {
+    if (precision == 0) return cdiv(P, 16 * fm_shape(R, R_block, P).NC);
     MfmaShape s = mfma_shape(precision, basis, R_block, P);
     return cdiv(P, 32 * s.NB);
 }
@@ -1266,8 +1100,8 @@ SfPlan sf_plan(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P,
                size_t max_bytes) {
     SfPlan p;
     const int64_t n_sets = cdiv(R, R_block);
-    const int64_t rts = sum_row_tiles_per_set(precision, BASIS_DIFF, R_block, P);
-    const int64_t cts = sum_col_tiles(precision, BASIS_DIFF, R_block, P);
+    const int64_t rts = sum_row_tiles_per_set(precision, BASIS_DIFF, R, R_block, P);
+    const int64_t cts = sum_col_tiles(precision, BASIS_DIFF, R, R_block, P);
     const int64_t base = n_sets * rts * cts;
     int64_t ks = 1;
     // one realisation per set: k_sf_one spreads the frequencies over a block
@@ -1319,12 +1153,7 @@ static hipError_t launch_f64(const SumArgs& a, hipStream_t st) {
         if (a.R_block <= 4) return launch_f64n<BASIS, 4>(a, st);
         if (a.R_block <= 8) return launch_f64n<BASIS, 8>(a, st);
     }
-    int64_t row_tiles = cdiv(a.R_block, F64_TR);
-    int64_t col_tiles = cdiv(a.P, F64_TP);
-    int64_t blocks = (a.set1 - a.set0) * row_tiles * col_tiles;
-    hipLaunchKernelGGL((k_sum_f64<BASIS, EPI>), dim3((unsigned)blocks), dim3(256), 0, st, a,
-                       row_tiles, col_tiles);
-    return hipGetLastError();
+    return launch_sum_fm(BASIS, EPI, a, st);
 }
 
 template <int PREC, int BASIS, int EPI, int MW, int NB>

@@ -15,6 +15,14 @@ __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16];
+// element i of the result is D[l / 16 + 4 i][l % 16].
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
 // x = hi + mid (+ lo) in bf16, each part the rounding (to nearest even) of
 // the remainder left by the parts before it; split for two values at once:
 // plane i of (x0, x1) as one packed word, x0 in the low half (the element

@@ -14,14 +14,6 @@
 
 namespace qrfs {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-// v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16];
-// element i of the result is D[l / 16 + 4 i][l % 16].
-__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // Block: one realisation, an output tile of 16 MU rows x 16 NV columns, WV
 // waves that split the frequencies (each wave a range of whole groups of 8)
 // and are summed in a fixed tree through LDS.
