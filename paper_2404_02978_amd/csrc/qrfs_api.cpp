@@ -243,9 +243,10 @@ using qrfs::kMaxLaunchBlocks;
 // kMaxLaunchBlocks blocks.
 qrfs_status run_sum(int precision, int basis, int epi, qrfs::SumArgs a, int64_t n_sets,
                     hipStream_t st) {
-    int64_t rts = qrfs::sum_row_tiles_per_set(precision, basis, a.R, a.R_block, a.P);
-    int64_t cts = qrfs::sum_col_tiles(precision, basis, a.R, a.R_block, a.P);
-    int64_t per_set = rts * cts * (a.ksplit > 1 ? a.ksplit : 1);
+    const int64_t per_set = qrfs::sum_blocks_per_set(precision, basis, a);
+    const int64_t rts = a.partial
+                            ? qrfs::sf_row_tiles_per_set(precision, a.K, a.R, a.R_block, a.P)
+                            : 0;
     int64_t max_sets = kMaxLaunchBlocks / (per_set > 0 ? per_set : 1);
     if (max_sets < 1) return fail(QRFS_ERR_INVALID_ARG, "problem too large for one set");
     const double* fx0 = a.fx;
@@ -263,6 +264,42 @@ qrfs_status run_sum(int precision, int basis, int epi, qrfs::SumArgs a, int64_t 
         hipError_t e = qrfs::launch_sum(precision, basis, epi, a, st);
         if (e != hipSuccess) return hip_fail(e, "kernel launch");
     }
+    return QRFS_OK;
+}
+
+// Most workspace that the partial sums of a stored contraction take.
+constexpr size_t kSplitCap = (size_t)64 << 20;
+
+// Stored sums in the fused kernels.  Where their tiles leave compute units
+// idle, K is cut into ranges whose partial sums go through the workspace; not
+// beyond the context's cap, and not while the stream is being captured (a
+// graph must not hold a workspace that a later call may replace): then one
+// range, which needs none.
+qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a, int64_t n_sets,
+                      hipStream_t st) {
+    size_t room = kSplitCap;
+    if (ctx->ws_cap && ctx->ws_cap < room) room = ctx->ws_cap;
+    qrfs::StoreSplit sp =
+        qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, room);
+    if (sp.ksplit > 1) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusActive;
+        }
+        if (cap != hipStreamCaptureStatusNone || ensure_workspace(ctx, sp.bytes) != QRFS_OK) {
+            (void)hipGetLastError();
+            sp = {1, a.K, 0};
+        }
+    }
+    a.ksplit = sp.ksplit;
+    a.kspan = sp.kspan;
+    a.phi_part = ctx->ws;
+    qrfs_status s = run_sum(precision, basis, qrfs::EPI_STORE, a, n_sets, st);
+    if (s || sp.ksplit == 1) return s;
+    hipError_t e = qrfs::launch_split_sum(precision == QRFS_PREC_FP64, ctx->ws, sp.ksplit,
+                                          a.R * a.P, a.out, st);
+    if (e != hipSuccess) return hip_fail(e, "partial-sum launch");
     return QRFS_OK;
 }
 
@@ -414,7 +451,7 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
     if (use_wide(ctx, precision, P, R, R_block, coef != nullptr))
         s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
     else
-        s = run_sum(precision, basis, qrfs::EPI_STORE, a, cdiv(R, R_block), (hipStream_t)stream);
+        s = fused_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
     if (s) return s;
     return ok();
 }
@@ -663,7 +700,7 @@ qrfs_status qrfs_diff_piston_structure(qrfs_context* ctx, const qrfs_psd* psd,
     if (!g.okay) return fail(QRFS_ERR_DEVICE, "cannot select device %d", ctx->device);
 
     const int64_t n_sets = cdiv(R, R_block);
-    const int64_t rts = qrfs::sum_row_tiles_per_set(precision, qrfs::BASIS_DIFF, R, R_block, nB);
+    const int64_t rts = qrfs::sf_row_tiles_per_set(precision, K, R, R_block, nB);
     const qrfs::SfPlan plan = qrfs::sf_plan(precision, K, R, R_block, nB);
     const size_t partial_bytes = align256((size_t)(plan.n_partial_tiles * nB) * 2 * sizeof(double));
     const size_t phi_bytes = align256(plan.phi_floats * sizeof(float));

@@ -13,7 +13,8 @@ namespace qrfs {
 // of the chunk, j = 4 h + q, which step q consumes together with the basis
 // values (column i, j = 4 h + q) that the lane reads from LDS with two 16-byte
 // loads (the contraction order is permuted, the result is not).  The groups'
-// sums are added in a fixed tree, then stored or squared.
+// sums are added in a fixed tree, then stored (as this frequency range's share
+// when the launch cuts K into ranges) or squared.
 //
 // Bound: the FP64 datapath, shared by the matrix instructions and the vector
 // ALU (measured: the times add).  Per (row, frequency): two coefficients, 86
@@ -50,6 +51,8 @@ __global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row
     int64_t b = blockIdx.x;
     const int64_t ct = b % col_tiles;
     b /= col_tiles;
+    const int64_t ks = b % a.ksplit;  // frequency range
+    b /= a.ksplit;
     const int64_t rt = b % row_tiles;
     const int64_t sl = b / row_tiles;
     const int64_t set = a.set0 + sl;
@@ -60,8 +63,10 @@ __global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row
     const double* fy = a.fy + sl * a.K;
     const double* w = a.w + sl * a.K;
     const int64_t twoK = 2 * a.K;
-    const int64_t nch = (a.K + FM_KC * WK - 1) / (FM_KC * WK);  // chunks per group
-    const int64_t kb = kg * nch * FM_KC;
+    const int64_t kr = ks * a.kspan;
+    const int64_t ke = kr + a.kspan < a.K ? kr + a.kspan : a.K;
+    const int64_t nch = (ke - kr + FM_KC * WK - 1) / (FM_KC * WK);  // chunks per group
+    const int64_t kb = kr + kg * nch * FM_KC;
     double* basis = sB + kg * S::BASIS;
 
     // basis work: this thread's column, frequencies part, part + PARTS, ...
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row
 
     auto load_freq = [&](int64_t ch, double (&f)[3]) {
         const int64_t k = kb + ch * FM_KC + gt;
-        const bool ok = gt < FM_KC && ch < nch && k < a.K;
+        const bool ok = gt < FM_KC && ch < nch && k < ke;
         f[0] = ok ? fx[k] : 0.0;
         f[1] = ok ? fy[k] : 0.0;
         f[2] = ok ? w[k] : 0.0;
@@ -203,7 +208,7 @@ __global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row
     // element i of acc[m][n]: row 16 m + lh + 4 i, column 16 n + li
     if (EPI == EPI_STORE) {
         if (kg == 0) {
-            double* out = (double*)a.out;
+            double* out = a.ksplit > 1 ? (double*)a.phi_part + ks * a.R * a.P : (double*)a.out;
 #pragma unroll
             for (int m = 0; m < MR; ++m)
 #pragma unroll
@@ -258,37 +263,43 @@ __global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row
 static inline int64_t fcdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Tile of a problem: 16 rows per wave where a set has no more, else 32;
-// 16, 32 or 64 columns; and the number of row waves that share a basis, by
-// the time of the fullest compute unit: blocks come in whole rounds of the
-// 256 compute units, a block of WR row waves takes 1 / WK = WR / 8 of the
-// frequencies per wave, and a (row, frequency) costs 86 operations for its
-// coefficients, 2 per column and 40 per column shared by the group's rows.
-// (Fewer row waves: more and shorter blocks that fill the chip evenly, but
-// more basis work.)
-FmShape fm_shape(int64_t R, int64_t R_block, int64_t P) {
-    FmShape s;
+// columns per block and row waves that share a basis by the estimated time
+// of the fullest compute unit.  Blocks come in whole rounds of the 256 compute
+// units; a block's wave takes 16 MR rows and WR / 8 of its range's frequencies,
+// and a (row, frequency) costs 86 operations for its coefficients, 2 per
+// column, and the basis of its columns shared by the group's rows: ~40
+// operations each, ~300 with the binary64 filter of two edges.  (Fewer row
+// waves and columns: more and shorter blocks that fill the chip evenly, but
+// more basis work and coefficients drawn more often.)  A wave instruction
+// takes 4 cycles of a SIMD; the kernel reaches about 0.6 of that at 2.4 GHz.
+FmShape fm_shape(int basis, int64_t K, int64_t R, int64_t R_block, int64_t P, int ksplit) {
+    FmShape s{};
     s.MR = R_block <= 16 ? 1 : 2;
-    s.NC = P <= 16 ? 1 : (P <= 32 ? 2 : 4);
+    s.us = 1e300;
     const int64_t n_sets = fcdiv(R, R_block);
-    double best = 1e300;
-    s.WR = 1;
-    for (int wr = 8; wr >= 1; wr >>= 1) {
-        const int64_t blocks =
-            n_sets * fcdiv(R_block, 16 * s.MR * wr) * fcdiv(P, 16 * s.NC);
-        const double per_row = 86.0 + 32.0 * s.NC + 40.0 * s.NC / (s.MR * wr);
-        const double cost = (double)fcdiv(blocks, 256) * wr * per_row;
-        if (cost < best * 0.97) {
-            best = cost;
-            s.WR = wr;
+    const double col_ops = basis == BASIS_PISTON ? 300.0 : 40.0;
+    const int nc_max = P <= 16 ? 1 : (P <= 32 ? 2 : 4);
+    for (int nc = nc_max; nc >= 1; nc >>= 1)
+        for (int wr = 8; wr >= 1; wr >>= 1) {
+            const int64_t blocks =
+                ksplit * n_sets * fcdiv(R_block, 16 * s.MR * wr) * fcdiv(P, 16 * nc);
+            const double per_row = 86.0 + 32.0 * nc + col_ops * nc / (s.MR * wr);
+            // 8 waves on 4 SIMDs, 16 MR rows on 64 lanes, 4 cycles
+            const double us = (double)fcdiv(blocks, 256) * ((double)K / ksplit) * wr * s.MR *
+                              per_row * (0.25 / 0.6 / 2400.0);
+            if (us < s.us * 0.97) {
+                s.us = us;
+                s.NC = nc;
+                s.WR = wr;
+            }
         }
-    }
     return s;
 }
 
 template <int BASIS, int EPI, int MR, int NC, int WR>
 static hipError_t launch_fm_w(const SumArgs& a, hipStream_t st) {
     const int64_t row_tiles = fcdiv(a.R_block, 16 * MR * WR), col_tiles = fcdiv(a.P, 16 * NC);
-    const dim3 g((unsigned)((a.set1 - a.set0) * row_tiles * col_tiles)), b(64 * FM_WAVES);
+    const dim3 g((unsigned)((a.set1 - a.set0) * row_tiles * col_tiles * a.ksplit)), b(64 * FM_WAVES);
     if (a.coef)
         hipLaunchKernelGGL((k_sum_fm<BASIS, EPI, MR, NC, WR, 2>), g, b, 0, st, a, row_tiles,
                            col_tiles);
@@ -318,7 +329,7 @@ static hipError_t launch_fm_m(const SumArgs& a, const FmShape& s, hipStream_t st
 
 template <int BASIS, int EPI>
 static hipError_t launch_fm_t(const SumArgs& a, hipStream_t st) {
-    const FmShape s = fm_shape(a.R, a.R_block, a.P);
+    const FmShape s = fm_shape(BASIS, a.K, a.R, a.R_block, a.P, a.ksplit);
     return s.MR == 1 ? launch_fm_m<BASIS, EPI, 1>(a, s, st) : launch_fm_m<BASIS, EPI, 2>(a, s, st);
 }
 

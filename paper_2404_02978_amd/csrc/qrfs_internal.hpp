@@ -60,9 +60,10 @@ struct SumArgs {
     const double* coef;  // [R][2K] or nullptr
     void* out;           // EPI_STORE: float or double [R][P]
     double* partial;     // EPI_SFSUM, ksplit == 1: [row tiles of this launch][P][2]
-    int32_t ksplit;      // frequency ranges per row tile (MFMA kernels, EPI_SFSUM)
+    int32_t ksplit;      // frequency ranges per row tile
     int64_t kspan;       // frequencies per range (multiple of the chunk length)
-    float* phi_part;     // EPI_SFSUM, ksplit > 1: [ksplit][R][P] partial sums
+    void* phi_part;      // ksplit > 1: [ksplit][R][P] partial sums, float
+                         // (double from the FP64 kernel)
     // BASIS_PISTON, grad != 0: the gradient of the piston along u (G-tilt)
     // instead of the piston: amplitudes times gx f_x + gy f_y with
     // (gx, gy) = 2 pi u, arguments shifted by a quarter cycle
@@ -171,17 +172,33 @@ hipError_t launch_sfsum_rows(const float* phi, int ksplit, int64_t R, int64_t P,
                              hipStream_t st);
 
 // Tile of the binary64 contraction of shared sets: rows per wave (16 MR),
-// columns per block (16 NC), row waves that share a basis.
+// columns per block (16 NC), row waves that share a basis, and the estimated
+// time (us) of the launch when the frequencies are cut into ksplit ranges.
 struct FmShape {
     int MR, NC, WR;
+    double us;
 };
-FmShape fm_shape(int64_t R, int64_t R_block, int64_t P);
+FmShape fm_shape(int basis, int64_t K, int64_t R, int64_t R_block, int64_t P, int ksplit);
 hipError_t launch_sum_fm(int basis, int epi, const SumArgs& a, hipStream_t st);
 
-// Row tiles one set occupies in `launch_sum` for this precision and problem
-// (needed to size the partial-sum buffer).
-int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R, int64_t R_block, int64_t P);
-int64_t sum_col_tiles(int precision, int basis, int64_t R, int64_t R_block, int64_t P);
+// Frequency ranges for a contraction whose sums are stored (EPI_STORE), so
+// that its blocks fill the chip: ksplit >= 1 and kspan; the partial sums
+// (ksplit > 1) take at most max_bytes.
+struct StoreSplit {
+    int ksplit;
+    int64_t kspan;
+    size_t bytes;  // of partial sums
+};
+StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
+                       size_t max_bytes);
+// out[i] = sum over ranges of part[range][i], i < n, in order, in binary64
+hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, void* out,
+                            hipStream_t st);
+
+// Row tiles one set occupies in `launch_sum` for a structure function (needed
+// to size the partial-sum buffer), and blocks of one set in any launch.
+int64_t sf_row_tiles_per_set(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P);
+int64_t sum_blocks_per_set(int precision, int basis, const SumArgs& a);
 
 hipError_t launch_sum(int precision, int basis, int epi, const SumArgs& a, hipStream_t st);
 

@@ -702,7 +702,8 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
     }
 
     if (EPI == EPI_STORE) {
-        float* out = (float*)a.out;
+        // the sums, or this frequency range's share of them
+        float* out = a.ksplit > 1 ? (float*)a.phi_part + ks * a.R * a.P : (float*)a.out;
 #pragma unroll
         for (int mw = 0; mw < MW; ++mw)
 #pragma unroll
@@ -724,7 +725,8 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     int64_t r = row_begin + (int64_t)(wave * MW + mw) * 32 + 8 * (i / 4) + 4 * lh + (i % 4);
-                    if (r < row_end && col < a.P) a.phi_part[(ks * a.R + r) * a.P + col] = mst[mw][nb][i];
+                    if (r < row_end && col < a.P)
+                        ((float*)a.phi_part)[(ks * a.R + r) * a.P + col] = mst[mw][nb][i];
                 }
             }
     } else {
@@ -1051,19 +1053,22 @@ static MfmaShape mfma_shape(int precision, int basis, int64_t R_block, int64_t P
     return s;
 }
 
-int64_t sum_row_tiles_per_set(int precision, int basis, int64_t R, int64_t R_block, int64_t P) {
+int64_t sf_row_tiles_per_set(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P) {
     if (precision == 0) {
-        const FmShape f = fm_shape(R, R_block, P);
+        const FmShape f = fm_shape(BASIS_DIFF, K, R, R_block, P, 1);
         return cdiv(R_block, 16 * f.MR * f.WR);
     }
-    MfmaShape s = mfma_shape(precision, basis, R_block, P);
+    MfmaShape s = mfma_shape(precision, BASIS_DIFF, R_block, P);
     return cdiv(R_block, 32 * s.MW * s.WV);
 }
 
-int64_t sum_col_tiles(int precision, int basis, int64_t R, int64_t R_block, int64_t P) {
-    if (precision == 0) return cdiv(P, 16 * fm_shape(R, R_block, P).NC);
-    MfmaShape s = mfma_shape(precision, basis, R_block, P);
-    return cdiv(P, 32 * s.NB);
+int64_t sum_blocks_per_set(int precision, int basis, const SumArgs& a) {
+    if (precision == 0) {
+        const FmShape f = fm_shape(basis, a.K, a.R, a.R_block, a.P, a.ksplit);
+        return cdiv(a.R_block, 16 * f.MR * f.WR) * cdiv(a.P, 16 * f.NC) * a.ksplit;
+    }
+    MfmaShape s = mfma_shape(precision, basis, a.R_block, a.P);
+    return cdiv(a.R_block, 32 * s.MW * s.WV) * cdiv(a.P, 32 * s.NB) * a.ksplit;
 }
 
 bool sf_one_realisation(int64_t R_block, int64_t P) { return R_block == 1 && P <= 64; }
@@ -1100,8 +1105,10 @@ SfPlan sf_plan(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P,
                size_t max_bytes) {
     SfPlan p;
     const int64_t n_sets = cdiv(R, R_block);
-    const int64_t rts = sum_row_tiles_per_set(precision, BASIS_DIFF, R, R_block, P);
-    const int64_t cts = sum_col_tiles(precision, BASIS_DIFF, R, R_block, P);
+    const int64_t rts = sf_row_tiles_per_set(precision, K, R, R_block, P);
+    const int64_t cts = precision == 0
+                            ? 1  // no split in binary64
+                            : cdiv(P, 32 * mfma_shape(precision, BASIS_DIFF, R_block, P).NB);
     const int64_t base = n_sets * rts * cts;
     int64_t ks = 1;
     // one realisation per set: k_sf_one spreads the frequencies over a block
@@ -1132,6 +1139,89 @@ SfPlan sf_plan(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P,
         --ks;
     }
     return p;
+}
+
+// ------------------------------------------------ split-K stored sums ----
+// Bound by the reads of the partial sums, 16 bytes wide where the arrays
+// allow it.
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_split_sum(const T* __restrict__ part, int ksplit,
+                                                   int64_t n, T* __restrict__ out) {
+    typedef T tvec __attribute__((ext_vector_type(VEC)));
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
+    if (i >= n) return;
+    double v[VEC] = {};
+    for (int k0 = 0; k0 < ksplit; k0 += 8) {
+        tvec t[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            t[j] = k0 + j < ksplit ? *(const tvec*)&part[(int64_t)(k0 + j) * n + i] : tvec((T)0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) v[e] += (double)t[j][e];
+    }
+    tvec o;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) o[e] = (T)v[e];
+    *(tvec*)&out[i] = o;
+}
+
+template <typename T, int VEC>
+static hipError_t launch_split_sum_t(const void* part, int ksplit, int64_t n, void* out,
+                                     hipStream_t st) {
+    if (n % VEC || ((uintptr_t)out & (sizeof(T) * VEC - 1)))
+        return launch_split_sum_t<T, 1>(part, ksplit, n, out, st);
+    hipLaunchKernelGGL((k_split_sum<T, VEC>), dim3((unsigned)cdiv(n, 256 * VEC)), dim3(256), 0, st,
+                       (const T*)part, ksplit, n, (T*)out);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, void* out,
+                            hipStream_t st) {
+    return fp64 ? launch_split_sum_t<double, 2>(part, ksplit, n, out, st)
+                : launch_split_sum_t<float, 4>(part, ksplit, n, out, st);
+}
+
+// A stored contraction is cut into frequency ranges when its tiles alone leave
+// compute units idle: its partial sums cost a second launch (~5 us) and their
+// traffic, against a range's share of the time.
+StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
+                       size_t max_bytes) {
+    StoreSplit s{1, K, 0};
+    if (R_block <= 8) return s;  // narrow sets: no split in those kernels
+    const size_t one = (size_t)R * P * (precision == 0 ? sizeof(double) : sizeof(float));
+    // written and read once at ~4 TB/s
+    const double pass_us = 2.0 * (double)one / 4e6;
+    double best = 1e300;
+    const int64_t nch = cdiv(K, KC);
+    const int64_t kmax = nch / 2 < 32 ? nch / 2 : 32;  // at least two chunks per range
+    int64_t base = 0, slots = 0;
+    double block_us = 0.0;
+    if (precision != 0) {
+        const MfmaShape m = mfma_shape(precision, basis, R_block, P);
+        base = cdiv(R, R_block) * cdiv(R_block, 32 * m.MW * m.WV) * cdiv(P, 32 * m.NB);
+        // blocks that run at full speed side by side: two waves per SIMD
+        slots = 256 * (8 / m.WV > 1 ? 8 / m.WV : 1);
+        // one chunk of 32 frequencies takes a block about 4 us alone
+        block_us = 4.0 * (double)nch;
+    }
+    for (int64_t k = 1; k <= (kmax < 1 ? 1 : kmax); ++k) {
+        if (k > 1 && (size_t)k * one > max_bytes) break;
+        const double us =
+            (precision == 0 ? fm_shape(basis, K, R, R_block, P, (int)k).us
+                            : (double)cdiv(base * k, slots) * block_us / (double)k) +
+            (k > 1 ? 5.0 + (double)k * pass_us : 0.0);
+        if (us < 0.97 * best) {
+            best = us;
+            s.ksplit = (int)k;
+        }
+    }
+    s.kspan = cdiv(cdiv(K, s.ksplit), KC) * KC;  // whole chunks, even frequency offsets
+    s.ksplit = (int)cdiv(K, s.kspan);            // no empty ranges
+    s.bytes = s.ksplit > 1 ? (size_t)s.ksplit * one : 0;
+    if (s.ksplit == 1) s.kspan = K;
+    return s;
 }
 
 template <int BASIS, int RB>

@@ -1,0 +1,149 @@
+"""Stored contractions whose frequencies are cut into ranges (problems with
+fewer tiles than the chip has room for): against the FP64 oracle at ragged
+ranges, rows and columns, in every precision and basis, with and without
+room for the partial sums, and under graph capture.
+
+Tolerances as for the whole contraction (max error relative to the RMS of
+the oracle's output): 1e-11 (FP64), 1e-5 (FP32, BF16x6, FP16x3), 1e-3
+(split-BF16).
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-11, 1: 1e-5, 2: 1e-3, 3: 1e-5, 4: 1e-5}
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2404_02978_amd as q
+    q.load_library()
+    return q
+
+
+@pytest.fixture(scope="module")
+def ctx(q):
+    c = q.Context(0)
+    yield c
+    c.close()
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.double().cpu().numpy()
+
+
+def problem(ctx, q, K, R, R_block, P, seed=1):
+    rng = np.random.default_rng([K, P, seed])
+    s = q.logpolar_sampler(1e-3, 1e2, index=3)
+    fx, fy, area = ctx.sample_frequencies(s, math.ceil(R / R_block), K)
+    w = ctx.weights(q.psd(0.1, 25.0), fx, fy, area)
+    return fx, fy, w, rng.uniform(-4, 4, P), rng.uniform(-4, 4, P)
+
+
+def check(got, ref, tol):
+    e = np.max(np.abs(got - ref)) / math.sqrt(np.mean(ref * ref))
+    print(f"  eps_max {e:.2e}", flush=True)
+    assert e <= tol
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("K,R,R_block,P,mode", [
+    (65, 9, 9, 1, 0), (128, 40, 17, 4, 1), (1000, 33, 33, 37, 0), (2049, 16, 16, 64, 0),
+    (3000, 150, 75, 130, 1), (4097, 12, 10, 257, 0)])
+def test_phase_ranges(q, ctx, precision, K, R, R_block, P, mode):
+    fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
+    print(f"phase p{precision} K{K} R{R} Rb{R_block} P{P} mode{mode}", flush=True)
+    out = ctx.synthesize_phase(K, fx, fy, w, dev(px), dev(py), R, R_block,
+                               rng=q.Rng(7, 5, mode), precision=precision)
+    ref = oracle.synthesize(host(fx), host(fy), host(w), px, py, R, R_block, K=K, seed=7,
+                            counter=5, mode=mode)
+    check(host(out), ref, TOL[precision])
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("K,R,R_block,P", [(700, 20, 20, 3), (2500, 70, 35, 33)])
+def test_pistons_and_differences(q, ctx, precision, K, R, R_block, P):
+    fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
+    rng = np.random.default_rng(P)
+    D = rng.uniform(0.5, 8.0, P)
+    d = np.where(np.arange(P) % 2, 0.0, 0.14 * D)
+    hf = [host(v) for v in (fx, fy, w)]
+    print(f"basis p{precision} K{K} R{R} Rb{R_block} P{P}", flush=True)
+    g = q.Rng(2, 9, 0)
+    out = ctx.piston(K, fx, fy, w, dev(px), dev(py), dev(D), dev(d), R, R_block, rng=g,
+                     precision=precision)
+    check(host(out), oracle.piston(*hf, px, py, D, d, R, R_block, K=K, seed=2, counter=9),
+          TOL[precision])
+    out = ctx.diff_piston(K, fx, fy, w, dev(px), dev(py), R, R_block, rng=g, precision=precision)
+    at = [oracle.synthesize(*hf, x, y, R, R_block, K=K, seed=2, counter=9)
+          for x, y in ((px, py), (np.zeros(1), np.zeros(1)))]
+    check(host(out), at[0] - at[1], TOL[precision])
+
+
+@pytest.mark.parametrize("precision", [0, 1, 4])
+def test_given_coefficients_and_unaligned_output(q, ctx, precision):
+    K, R, R_block, P = 1300, 24, 12, 28
+    fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
+    coef = np.random.default_rng(3).normal(size=(R, 2 * K))
+    dt = torch.float64 if precision == 0 else torch.float32
+    buf = torch.full((R * P + 3,), 7.0, dtype=dt, device="cuda")
+    out = buf[1:1 + R * P].view(R, P)  # not 16-byte aligned
+    print(f"given p{precision}", flush=True)
+    ctx.synthesize_phase(K, fx, fy, w, dev(px), dev(py), R, R_block, coef=dev(coef),
+                         precision=precision, out=out)
+    ref = oracle.synthesize(host(fx), host(fy), host(w), px, py, R, R_block, K=K, coef=coef)
+    check(host(out), ref, TOL[precision])
+    assert host(buf)[0] == 7.0 and np.all(host(buf)[-2:] == 7.0)
+
+
+@pytest.mark.parametrize("precision", [0, 1, 3, 4])
+@pytest.mark.parametrize("cap", [1, 30000, 1 << 20])
+def test_capped_context_needs_no_room(q, precision, cap):
+    """A cap below the partial sums leaves one range, or fewer of them."""
+    K, R, R_block, P = 2100, 30, 30, 45
+    with q.Context(0, workspace_cap=cap) as c:
+        fx, fy, w, px, py = problem(c, q, K, R, R_block, P)
+        print(f"cap {cap} p{precision}", flush=True)
+        out = c.synthesize_phase(K, fx, fy, w, dev(px), dev(py), R, R_block, rng=q.Rng(1, 2, 0),
+                                 precision=precision)
+        ref = oracle.synthesize(host(fx), host(fy), host(w), px, py, R, R_block, K=K, seed=1,
+                                counter=2)
+        check(host(out), ref, TOL[precision])
+
+
+@pytest.mark.parametrize("precision", [0, 1, 4])
+def test_captured_calls_hold_no_workspace(q, precision):
+    """Captured in a graph, with the context's workspace replaced and eager
+    work between the replays."""
+    K, R, R_block, P = 1500, 40, 20, 60
+    with q.Context(0) as c:
+        fx, fy, w, px, py = problem(c, q, K, R, R_block, P)
+        dx, dy = dev(px), dev(py)
+        ref = oracle.synthesize(host(fx), host(fy), host(w), px, py, R, R_block, K=K, seed=4)
+        out = torch.zeros((R, P), dtype=torch.float64 if precision == 0 else torch.float32,
+                          device="cuda")
+        args = (K, fx, fy, w, dx, dy, R, R_block)
+        print(f"capture p{precision}", flush=True)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            c.synthesize_phase(*args, rng=q.Rng(4, 0, 0), precision=precision, out=out)
+        for i in range(3):
+            out.fill_(float("nan"))
+            g.replay()
+            check(host(out), ref, TOL[precision])
+            # grows (and so replaces) the workspace
+            c.point_set_measures(fx[:1000 * (i + 1)], fy, 500 * (i + 1), 2, -100.0, -100.0, 200.0,
+                                 200.0, 0.1)
+            eager = c.synthesize_phase(*args, rng=q.Rng(4, 0, 0), precision=precision)
+            check(host(eager), ref, TOL[precision])
