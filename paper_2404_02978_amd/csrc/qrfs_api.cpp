@@ -2,6 +2,7 @@
 // its device workspace, and the host-side orchestration of the kernels.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -28,7 +29,13 @@ struct qrfs_context {
     int wide_path = 0;          // QRFS_TUNE_WIDE_PATH
     int64_t range_freqs = 2048;  // QRFS_TUNE_RANGE_FREQS
     size_t tile_cap = (size_t)2 << 30;  // QRFS_TUNE_TILE_BYTES
+    // what the calls find out about their points on the device: a ring, so
+    // that a call's answer outlives its kernels; allocated with the context, so
+    // that captured calls may use it
+    qrfs::GridInfo* grids = nullptr;
+    std::atomic<unsigned> next_grid{0};
 };
+constexpr unsigned kGridRing = 256;
 
 // Scratch of the allocation-free structure-function entry point: a static
 // device array (each GPU the library runs on holds its own copy until the
@@ -295,10 +302,37 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     a.ksplit = sp.ksplit;
     a.kspan = sp.kspan;
     a.phi_part = ctx->ws;
+    // narrow sets: fields on a regular grid go through its product structure,
+    // if the points are one (the general kernel sees the same answer)
+    const double pad = qrfs::grid_max_pad(precision == QRFS_PREC_FP64, a.R_block);
+    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids && a.P >= 171 &&
+        a.P <= ((int64_t)1 << 24)) {
+        qrfs::GridInfo* g = ctx->grids + ctx->next_grid.fetch_add(1) % kGridRing;
+        hipError_t e = qrfs::launch_grid_find(a.px, a.py, a.P, pad, g, st);
+        if (e != hipSuccess) return hip_fail(e, "grid launch");
+        qrfs::SepArgs b{};
+        b.K = a.K;
+        b.fx = a.fx;
+        b.fy = a.fy;
+        b.w = a.w;
+        b.R = a.R;
+        b.R_block = a.R_block;
+        b.P = a.P;
+        b.seed = a.seed;
+        b.counter = a.counter;
+        b.mode = a.mode;
+        b.coef = a.coef;
+        b.px = a.px;
+        b.py = a.py;
+        b.out = a.out;
+        e = qrfs::launch_grid_sum(precision == QRFS_PREC_FP64, b, g, st);
+        if (e != hipSuccess) return hip_fail(e, "grid sum launch");
+        a.grid = g;
+    }
     qrfs_status s = run_sum(precision, basis, qrfs::EPI_STORE, a, n_sets, st);
     if (s || sp.ksplit == 1) return s;
     hipError_t e = qrfs::launch_split_sum(precision == QRFS_PREC_FP64, ctx->ws, sp.ksplit,
-                                          a.R * a.P, a.out, st);
+                                          a.R * a.P, a.out, a.grid, st);
     if (e != hipSuccess) return hip_fail(e, "partial-sum launch");
     return QRFS_OK;
 }
@@ -510,6 +544,13 @@ qrfs_status qrfs_context_create(qrfs_context** out, int32_t device, size_t works
     if (!c) return fail(QRFS_ERR_OUT_OF_MEMORY, "host allocation of the context");
     c->device = device;
     c->ws_cap = workspace_cap_bytes;
+    {
+        DeviceGuard g(device);
+        if (hipMalloc(&c->grids, kGridRing * sizeof(qrfs::GridInfo)) != hipSuccess) {
+            (void)hipGetLastError();
+            c->grids = nullptr;  // the calls then do without
+        }
+    }
     *out = c;
     return ok();
 }
@@ -542,6 +583,11 @@ qrfs_status qrfs_context_destroy(qrfs_context* ctx) {
             hipError_t e = hipDeviceSynchronize();
             if (e != hipSuccess) st = hip_fail(e, "hipDeviceSynchronize in destroy");
             (void)hipFree(ctx->ws);
+        }
+        if (ctx->grids) {
+            hipError_t e = hipDeviceSynchronize();
+            if (e != hipSuccess) st = hip_fail(e, "hipDeviceSynchronize in destroy");
+            (void)hipFree(ctx->grids);
         }
     }
     delete ctx;
@@ -966,7 +1012,7 @@ qrfs_status qrfs_temporal_piston_structure(qrfs_context* ctx, const qrfs_psd* ps
             a.sy = -v[1] * dt;
             a.dx = c2[0] - c1[0];
             a.dy = c2[1] - c1[1];
-            a.out = (double*)pist;
+            a.out = pist;
             e = qrfs::launch_series_diff(a, stream_);
             if (e != hipSuccess) return hip_fail(e, "time-series launch");
         } else {

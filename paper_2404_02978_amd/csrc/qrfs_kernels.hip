@@ -25,10 +25,14 @@ template <int BASIS, int RB>
 __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) {
     __shared__ double sfx[F64N_KC], sfy[F64N_KC], sw[F64N_KC];
     __shared__ double sC[RB][2 * F64N_KC];
+    if (a.grid && grid_ok(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
     const int64_t ct = (int64_t)blockIdx.x % col_tiles;
-    const int64_t sl = (int64_t)blockIdx.x / col_tiles;
+    const int64_t ks = (int64_t)blockIdx.x / col_tiles % a.ksplit;  // frequency range
+    const int64_t sl = (int64_t)blockIdx.x / col_tiles / a.ksplit;
+    const int64_t kr = ks * a.kspan;
+    const int64_t ke = kr + a.kspan < a.K ? kr + a.kspan : a.K;
     const int64_t set = a.set0 + sl;
     const int64_t row_begin = set * a.R_block;
     const int64_t set_end = (set + 1) * a.R_block < a.R ? (set + 1) * a.R_block : a.R;
@@ -50,11 +54,11 @@ __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) 
 #pragma unroll
     for (int q = 0; q < RB; ++q) acc[q] = 0.0;
 
-    for (int64_t k0 = 0; k0 < a.K; k0 += F64N_KC) {
+    for (int64_t k0 = kr; k0 < ke; k0 += F64N_KC) {
         __syncthreads();
         if (tid < F64N_KC) {
             const int64_t k = k0 + tid;
-            const bool ok = k < a.K;
+            const bool ok = k < ke;
             sfx[tid] = ok ? fx[k] : 0.0;
             sfy[tid] = ok ? fy[k] : 0.0;
             sw[tid] = ok ? w[k] : 0.0;
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) 
             for (int q = 0; q < 4; ++q) sC[rr][4 * bt + q] = g[q];
         }
         __syncthreads();
-        const int nk = a.K - k0 < F64N_KC ? (int)(a.K - k0) : F64N_KC;
+        const int nk = ke - k0 < F64N_KC ? (int)(ke - k0) : F64N_KC;
         for (int kk = 0; kk < nk; ++kk) {
             double t = sfx[kk] * px + sfy[kk] * py;
             if (BASIS == BASIS_PISTON) t += grad_shift(a.grad);
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) 
                 acc[q] = fma(sC[q][2 * kk], cb, fma(sC[q][2 * kk + 1], sb, acc[q]));
         }
     }
-    double* out = (double*)a.out;
+    double* out = a.ksplit > 1 ? (double*)a.phi_part + ks * a.R * a.P : (double*)a.out;
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
         const int64_t r = row_begin + q;
@@ -196,10 +200,14 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
     constexpr int KCN = 64;
     __shared__ double sfx[KCN], sfy[KCN], sw[KCN];
     __shared__ float sC[RB][2 * KCN];
+    if (a.grid && grid_ok(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
     const int64_t ct = (int64_t)blockIdx.x % col_tiles;
-    const int64_t sl = (int64_t)blockIdx.x / col_tiles;
+    const int64_t ks = (int64_t)blockIdx.x / col_tiles % a.ksplit;  // frequency range
+    const int64_t sl = (int64_t)blockIdx.x / col_tiles / a.ksplit;
+    const int64_t kr = ks * a.kspan;
+    const int64_t ke = kr + a.kspan < a.K ? kr + a.kspan : a.K;
     const int64_t set = a.set0 + sl;
     const int64_t row_begin = set * a.R_block;
     const int64_t set_end = (set + 1) * a.R_block < a.R ? (set + 1) * a.R_block : a.R;
@@ -220,11 +228,11 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
 #pragma unroll
     for (int q = 0; q < RB; ++q) acc[q] = mst[q] = 0.0f;
 
-    for (int64_t k0 = 0; k0 < a.K; k0 += KCN) {
+    for (int64_t k0 = kr; k0 < ke; k0 += KCN) {
         __syncthreads();
         if (tid < KCN) {
             const int64_t k = k0 + tid;
-            const bool ok = k < a.K;
+            const bool ok = k < ke;
             sfx[tid] = ok ? fx[k] : 0.0;
             sfy[tid] = ok ? fy[k] : 0.0;
             sw[tid] = ok ? w[k] : 0.0;
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
             for (int q = 0; q < 4; ++q) sC[rr][4 * bt + q] = g[q];
         }
         __syncthreads();
-        const int nk = a.K - k0 < KCN ? (int)(a.K - k0) : KCN;
+        const int nk = ke - k0 < KCN ? (int)(ke - k0) : KCN;
         for (int kk = 0; kk < nk; ++kk) {
             const double cfx = sfx[kk], cfy = sfy[kk];
             double t = cfx * px + cfy * py;
@@ -261,7 +269,7 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
             acc[q] = 0.0f;
         }
     }
-    float* out = (float*)a.out;
+    float* out = a.ksplit > 1 ? (float*)a.phi_part + ks * a.R * a.P : (float*)a.out;
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
         const int64_t r = row_begin + q;
@@ -1062,7 +1070,11 @@ int64_t sf_row_tiles_per_set(int precision, int64_t K, int64_t R, int64_t R_bloc
     return cdiv(R_block, 32 * s.MW * s.WV);
 }
 
+// points per block of the narrow kernels
+static int narrow_threads(int64_t P) { return P >= 256 ? 256 : (P >= 128 ? 128 : 64); }
+
 int64_t sum_blocks_per_set(int precision, int basis, const SumArgs& a) {
+    if (!a.partial && a.R_block <= 8) return cdiv(a.P, narrow_threads(a.P)) * a.ksplit;
     if (precision == 0) {
         const FmShape f = fm_shape(basis, a.K, a.R, a.R_block, a.P, a.ksplit);
         return cdiv(a.R_block, 16 * f.MR * f.WR) * cdiv(a.P, 16 * f.NC) * a.ksplit;
@@ -1146,7 +1158,9 @@ SfPlan sf_plan(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P,
 // allow it.
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void k_split_sum(const T* __restrict__ part, int ksplit,
-                                                   int64_t n, T* __restrict__ out) {
+                                                   int64_t n, T* __restrict__ out,
+                                                   const GridInfo* __restrict__ grid) {
+    if (grid && grid_ok(grid)) return;  // k_grid_sum did the work
     typedef T tvec __attribute__((ext_vector_type(VEC)));
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
     if (i >= n) return;
@@ -1169,36 +1183,46 @@ __global__ __launch_bounds__(256) void k_split_sum(const T* __restrict__ part, i
 
 template <typename T, int VEC>
 static hipError_t launch_split_sum_t(const void* part, int ksplit, int64_t n, void* out,
-                                     hipStream_t st) {
+                                     const GridInfo* grid, hipStream_t st) {
     if (n % VEC || ((uintptr_t)out & (sizeof(T) * VEC - 1)))
-        return launch_split_sum_t<T, 1>(part, ksplit, n, out, st);
+        return launch_split_sum_t<T, 1>(part, ksplit, n, out, grid, st);
     hipLaunchKernelGGL((k_split_sum<T, VEC>), dim3((unsigned)cdiv(n, 256 * VEC)), dim3(256), 0, st,
-                       (const T*)part, ksplit, n, (T*)out);
+                       (const T*)part, ksplit, n, (T*)out, grid);
     return hipGetLastError();
 }
 
 hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, void* out,
-                            hipStream_t st) {
-    return fp64 ? launch_split_sum_t<double, 2>(part, ksplit, n, out, st)
-                : launch_split_sum_t<float, 4>(part, ksplit, n, out, st);
+                            const GridInfo* grid, hipStream_t st) {
+    return fp64 ? launch_split_sum_t<double, 2>(part, ksplit, n, out, grid, st)
+                : launch_split_sum_t<float, 4>(part, ksplit, n, out, grid, st);
 }
 
 // A stored contraction is cut into frequency ranges when its tiles alone leave
-// compute units idle: its partial sums cost a second launch (~5 us) and their
-// traffic, against a range's share of the time.
+// compute units idle: its partial sums cost a second launch (8 us with the
+// host's part) and their traffic, against a range's share of the time.
 StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
                        size_t max_bytes) {
     StoreSplit s{1, K, 0};
-    if (R_block <= 8) return s;  // narrow sets: no split in those kernels
     const size_t one = (size_t)R * P * (precision == 0 ? sizeof(double) : sizeof(float));
     // written and read once at ~4 TB/s
     const double pass_us = 2.0 * (double)one / 4e6;
     double best = 1e300;
     const int64_t nch = cdiv(K, KC);
-    const int64_t kmax = nch / 2 < 32 ? nch / 2 : 32;  // at least two chunks per range
+    const int64_t kmax = K / 64 < 32 ? K / 64 : 32;  // at least 64 frequencies per range
     int64_t base = 0, slots = 0;
     double block_us = 0.0;
-    if (precision != 0) {
+    const bool narrow = R_block <= 8;
+    if (narrow) {
+        // one point per thread: 148 cycles of a SIMD per frequency and wave in
+        // binary64 (44 in FP32 class, ~8 more per realisation), more with a
+        // filter, and four waves per SIMD to hide their latency
+        const int nt = narrow_threads(P);
+        base = cdiv(R, R_block) * cdiv(P, nt);
+        slots = 256 * (1024 / nt);
+        const double filter = basis == BASIS_PISTON ? (precision == 0 ? 1000.0 : 400.0) : 0.0;
+        block_us = (double)K * 4.0 *
+                   ((precision == 0 ? 148.0 : 44.0) + 8.0 * (double)R_block + filter) / 2000.0;
+    } else if (precision != 0) {
         const MfmaShape m = mfma_shape(precision, basis, R_block, P);
         base = cdiv(R, R_block) * cdiv(R_block, 32 * m.MW * m.WV) * cdiv(P, 32 * m.NB);
         // blocks that run at full speed side by side: two waves per SIMD
@@ -1209,15 +1233,15 @@ StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R
     for (int64_t k = 1; k <= (kmax < 1 ? 1 : kmax); ++k) {
         if (k > 1 && (size_t)k * one > max_bytes) break;
         const double us =
-            (precision == 0 ? fm_shape(basis, K, R, R_block, P, (int)k).us
+            (precision == 0 && !narrow ? fm_shape(basis, K, R, R_block, P, (int)k).us
                             : (double)cdiv(base * k, slots) * block_us / (double)k) +
-            (k > 1 ? 5.0 + (double)k * pass_us : 0.0);
-        if (us < 0.97 * best) {
+            (k > 1 ? 8.0 + (double)k * pass_us : 0.0);
+        if (us < 0.95 * best) {
             best = us;
             s.ksplit = (int)k;
         }
     }
-    s.kspan = cdiv(cdiv(K, s.ksplit), KC) * KC;  // whole chunks, even frequency offsets
+    s.kspan = cdiv(cdiv(K, s.ksplit), 64) * 64;  // whole chunks of every kernel
     s.ksplit = (int)cdiv(K, s.kspan);            // no empty ranges
     s.bytes = s.ksplit > 1 ? (size_t)s.ksplit * one : 0;
     if (s.ksplit == 1) s.kspan = K;
@@ -1226,9 +1250,9 @@ StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R
 
 template <int BASIS, int RB>
 static hipError_t launch_f64n(const SumArgs& a, hipStream_t st) {
-    const int nt = a.P >= 256 ? 256 : (a.P >= 128 ? 128 : 64);
+    const int nt = narrow_threads(a.P);
     const int64_t col_tiles = cdiv(a.P, nt);
-    const int64_t blocks = (a.set1 - a.set0) * col_tiles;
+    const int64_t blocks = (a.set1 - a.set0) * col_tiles * a.ksplit;
     hipLaunchKernelGGL((k_sum_f64n<BASIS, RB>), dim3((unsigned)blocks), dim3(nt), 0, st, a,
                        col_tiles);
     return hipGetLastError();
@@ -1279,9 +1303,9 @@ static hipError_t launch_mfma(const SumArgs& a, hipStream_t st) {
 
 template <int BASIS, int RB>
 static hipError_t launch_f32n_r(const SumArgs& a, hipStream_t st) {
-    const int nt = a.P >= 256 ? 256 : (a.P >= 128 ? 128 : 64);
+    const int nt = narrow_threads(a.P);
     const int64_t col_tiles = cdiv(a.P, nt);
-    const dim3 g((unsigned)((a.set1 - a.set0) * col_tiles)), b(nt);
+    const dim3 g((unsigned)((a.set1 - a.set0) * col_tiles * a.ksplit)), b(nt);
     if (a.coef)
         hipLaunchKernelGGL((k_sum_f32n<BASIS, RB, 2>), g, b, 0, st, a, col_tiles);
     else if (a.mode == 1)

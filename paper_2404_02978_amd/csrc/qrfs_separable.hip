@@ -50,34 +50,20 @@ struct SepSmem {
     __attribute__((aligned(16))) double d[STAGE > TREE ? STAGE : TREE];
 };
 
-template <bool DIFF, int MU, int NV, int WV>
-__global__ __launch_bounds__(64 * WV) void k_separable(SepArgs a, int ut, int vt) {
-    __shared__ SepSmem<MU, NV, WV> sm;
+// One output tile of realisation r (all threads of the block call it): the
+// lane's rows (rx, ry) and columns (cx, cy), frequencies fx, fy, w of the set.
+// emit(m, n, i, sum) receives element (16 m + lane / 16 + 4 i, 16 n + lane % 16).
+template <bool DIFF, int MU, int NV, int WV, typename Emit>
+__device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r,
+                                         const double (&rx)[MU], const double (&ry)[MU],
+                                         const double (&cx)[NV], const double (&cy)[NV],
+                                         const Emit& emit) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int li = lane & 15, lh = lane >> 4;
-    const int64_t tiles = (int64_t)ut * vt;
-    const int64_t r = a.r0 + (int64_t)blockIdx.x / tiles;
-    const int tile = (int)((int64_t)blockIdx.x % tiles);
-    const int u0 = (tile / vt) * 16 * MU, v0 = (tile % vt) * 16 * NV;
+    const int lh = lane >> 4;
     const int64_t s = r / a.R_block;
     const double* fx = a.fx + s * a.K;
     const double* fy = a.fy + s * a.K;
     const double* w = a.w + s * a.K;
-
-    // the lane's rows and columns
-    double rx[MU], ry[MU], cx[NV], cy[NV];
-#pragma unroll
-    for (int m = 0; m < MU; ++m) {
-        const double t = (double)((u0 + 16 * m + li) * a.V);
-        rx[m] = a.ox + t * a.sx;
-        ry[m] = a.oy + t * a.sy;
-    }
-#pragma unroll
-    for (int n = 0; n < NV; ++n) {
-        const double t = (double)(v0 + 16 * n + li);
-        cx[n] = t * a.sx;
-        cy[n] = t * a.sy;
-    }
     f64x4 acc[MU][NV];
 #pragma unroll
     for (int m = 0; m < MU; ++m)
@@ -87,12 +73,20 @@ __global__ __launch_bounds__(64 * WV) void k_separable(SepArgs a, int ut, int vt
     const int64_t kw = ((a.K + 8 * WV - 1) / (8 * WV)) * 8;
     const int64_t kb = wave * kw;
     const int64_t ke = kb + kw < a.K ? kb + kw : a.K;
-    double* st = sm.d + wave * SEP_KC * 4;
+    double* st = sm + wave * SEP_KC * 4;
     for (int64_t k0 = kb; k0 < ke; k0 += SEP_KC) {
         {
             const int64_t k = k0 + 2 * lane;
             double g[4] = {0.0, 0.0, 0.0, 0.0};
-            if (k < ke) coef4_f64(a.seed, a.counter + (uint64_t)r, (uint32_t)(k >> 1), a.mode, g);
+            if (k < ke) {
+                if (a.coef) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (k + q / 2 < ke) g[q] = a.coef[r * 2 * a.K + 2 * k + q];
+                } else {
+                    coef4_f64(a.seed, a.counter + (uint64_t)r, (uint32_t)(k >> 1), a.mode, g);
+                }
+            }
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const bool ok = k + h < ke;
@@ -147,7 +141,7 @@ __global__ __launch_bounds__(64 * WV) void k_separable(SepArgs a, int ut, int vt
     for (int half = WV / 2; half > 0; half >>= 1) {
         __syncthreads();
         if (wave >= half && wave < 2 * half) {
-            double* dst = sm.d + (wave - half) * (256 * MU * NV) + lane;
+            double* dst = sm + (wave - half) * (256 * MU * NV) + lane;
 #pragma unroll
             for (int m = 0; m < MU; ++m)
 #pragma unroll
@@ -157,7 +151,7 @@ __global__ __launch_bounds__(64 * WV) void k_separable(SepArgs a, int ut, int vt
         }
         __syncthreads();
         if (wave < half) {
-            const double* src = sm.d + wave * (256 * MU * NV) + lane;
+            const double* src = sm + wave * (256 * MU * NV) + lane;
 #pragma unroll
             for (int m = 0; m < MU; ++m)
 #pragma unroll
@@ -167,18 +161,37 @@ __global__ __launch_bounds__(64 * WV) void k_separable(SepArgs a, int ut, int vt
         }
     }
     if (wave == 0) {
-        double* out = a.out + r * a.P;
 #pragma unroll
         for (int m = 0; m < MU; ++m)
 #pragma unroll
             for (int n = 0; n < NV; ++n)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int v = v0 + 16 * n + li;
-                    const int64_t p = (int64_t)(u0 + 16 * m + lh + 4 * i) * a.V + v;
-                    if (v < a.V && p < a.P) out[p] = acc[m][n][i];
-                }
+                for (int i = 0; i < 4; ++i) emit(m, n, i, acc[m][n][i]);
     }
+}
+
+template <int WV>
+__global__ __launch_bounds__(64 * WV) void k_series_diff(SepArgs a, int ut, int vt) {
+    __shared__ SepSmem<2, 2, WV> sm;
+    const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
+    const int64_t tiles = (int64_t)ut * vt;
+    const int64_t r = a.r0 + (int64_t)blockIdx.x / tiles;
+    const int tile = (int)((int64_t)blockIdx.x % tiles);
+    const int u0 = (tile / vt) * 32, v0 = (tile % vt) * 32;
+    double rx[2], ry[2], cx[2], cy[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const double tu = (double)((u0 + 16 * m + li) * a.V), tv = (double)(v0 + 16 * m + li);
+        rx[m] = a.ox + tu * a.sx;
+        ry[m] = a.oy + tu * a.sy;
+        cx[m] = tv * a.sx;
+        cy[m] = tv * a.sy;
+    }
+    double* out = (double*)a.out + r * a.P;
+    sep_tile<true, 2, 2, WV>(sm.d, a, r, rx, ry, cx, cy, [&](int m, int n, int i, double v) {
+        const int64_t p = (int64_t)(u0 + 16 * m + lh + 4 * i) * a.V + v0 + 16 * n + li;
+        if (p < a.P) out[p] = v;
+    });
 }
 
 // Differential pistons of a time series: tiles of 32 x 32 samples (a row is
@@ -192,15 +205,179 @@ hipError_t launch_series_diff(const SepArgs& args, hipStream_t st) {
     for (a.r0 = 0; a.r0 < a.R; a.r0 += step) {
         const int64_t n = (a.R - a.r0 < step ? a.R - a.r0 : step) * tiles;
         if (n >= 512)
-            hipLaunchKernelGGL((k_separable<true, 2, 2, 4>), dim3((unsigned)n), dim3(256), 0, st,
-                               a, ut, vt);
+            hipLaunchKernelGGL(k_series_diff<4>, dim3((unsigned)n), dim3(256), 0, st, a, ut, vt);
         else
-            hipLaunchKernelGGL((k_separable<true, 2, 2, 16>), dim3((unsigned)n), dim3(1024), 0, st,
-                               a, ut, vt);
+            hipLaunchKernelGGL(k_series_diff<16>, dim3((unsigned)n), dim3(1024), 0, st, a, ut, vt);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// ------------------------------------------------------- regular grids ----
+// Whether the points form a grid, decided on the device from their values in
+// every call (the host only has pointers): V = length of the first run of
+// equal y (x varies fastest) or equal x, and every point p equal to
+// (x[p mod V], y[p - p mod V]) (or the other way round), bit for bit up to the
+// sign of zero.  Each block checks a slice and all find V from the first
+// points; consumers combine the slices' answers (grid_ok).
+// max_pad: largest ratio of padded tile area to points that is taken.
+// Rows and columns are padded to whole units: 16, or 32 in the tiles of 64 x 64
+// that grids of at least 4096 points use.
+__host__ __device__ constexpr int grid_unit(int64_t P) { return P >= 4096 ? 32 : 16; }
+
+__global__ __launch_bounds__(1024) void k_grid_find(const double* __restrict__ px,
+                                                    const double* __restrict__ py, int64_t P,
+                                                    double max_pad, GridInfo* __restrict__ g) {
+    __shared__ int s_run[2], s_bad;
+    const int tid = threadIdx.x;
+    if (tid < 2) s_run[tid] = GRID_MAX_V + 1;
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    const double x0 = px[0], y0 = py[0];
+    int ry = GRID_MAX_V + 1, rx = GRID_MAX_V + 1;
+#pragma unroll
+    for (int i = GRID_MAX_V / 1024 - 1; i >= 0; --i) {
+        const int p = 1 + tid + 1024 * i;
+        if (p < P) {
+            if (py[p] != y0) ry = p;
+            if (px[p] != x0) rx = p;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        ry = min(ry, __shfl_xor(ry, off));
+        rx = min(rx, __shfl_xor(rx, off));
+    }
+    if ((tid & 63) == 0) {
+        atomicMin(&s_run[0], ry);
+        atomicMin(&s_run[1], rx);
+    }
+    __syncthreads();
+    const int xfast = s_run[0] > 1 ? 1 : 0;
+    const int V = xfast ? s_run[0] : s_run[1];
+    const int n = (int)P;
+    bool ok = V > 1 && V <= GRID_MAX_V && n % V == 0;
+    if (ok) {
+        const int unit = grid_unit(P);
+        const double u = (double)((n / V + unit - 1) / unit * unit);
+        ok = u * (double)((V + unit - 1) / unit * unit) <= max_pad * (double)P;
+    }
+    if (ok) {
+        bool bad = false;
+        for (int p = (int)blockIdx.x * 1024 + tid; p < n; p += (int)gridDim.x * 1024) {
+            const int v = p % V, u = p - v;
+            bad |= !(px[p] == px[xfast ? v : u]) || !(py[p] == py[xfast ? u : v]);
+        }
+        if (bad) s_bad = 1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        g->ok[blockIdx.x] = ok && !s_bad ? 1 : 0;
+        if (blockIdx.x == 0) {
+            g->V = ok ? V : 1;
+            g->xfast = xfast;
+            g->slices = (int)gridDim.x;
+        }
+    }
+}
+
+template <typename T, int MU, int NV, int WV>
+__device__ __forceinline__ void grid_tile(double* sm, const SepArgs& a, int64_t r, int U, int V,
+                                          int xfast, int u0, int v0) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
+    double rx[MU], ry[MU], cx[NV], cy[NV];
+#pragma unroll
+    for (int m = 0; m < MU; ++m) {
+        const int u = u0 + 16 * m + li;
+        const int64_t p = (int64_t)(u < U ? u : 0) * V;
+        rx[m] = xfast ? 0.0 : a.px[p];
+        ry[m] = xfast ? a.py[p] : 0.0;
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m) {
+        const int v = v0 + 16 * m + li;
+        const int64_t p = v < V ? v : 0;
+        cx[m] = xfast ? a.px[p] : 0.0;
+        cy[m] = xfast ? 0.0 : a.py[p];
+    }
+    T* out = (T*)a.out + r * a.P;
+    sep_tile<false, MU, NV, WV>(sm, a, r, rx, ry, cx, cy, [&](int m, int q, int i, double s) {
+        const int u = u0 + 16 * m + lh + 4 * i, v = v0 + 16 * q + li;
+        if (u < U && v < V) out[(int64_t)u * V + v] = (T)s;
+    });
+}
+
+// Sums on a grid found by k_grid_find: blocks take (realisation, tile) in
+// turn, tiles at the edges in half the size where that holds them; nothing to
+// do where the points are no grid (the general kernel, which follows, then
+// does the work).
+template <typename T, int MU, int NV, int WV>
+__global__ __launch_bounds__(64 * WV) void k_grid_sum(SepArgs a, const GridInfo* __restrict__ g) {
+    __shared__ SepSmem<MU, NV, WV> sm;
+    if (!grid_ok(g)) return;
+    constexpr int HU = MU > 1 ? MU / 2 : 1, HV = NV > 1 ? NV / 2 : 1;
+    const int V = g->V, xfast = g->xfast;
+    const int U = (int)(a.P / V);
+    const int ut = (U + 16 * MU - 1) / (16 * MU), vt = (V + 16 * NV - 1) / (16 * NV);
+    const int64_t tiles = (int64_t)ut * vt, n = a.R * tiles;
+    for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+        const int64_t r = it / tiles;
+        const int tile = (int)(it % tiles);
+        const int u0 = (tile / vt) * 16 * MU, v0 = (tile % vt) * 16 * NV;
+        const bool hu = HU < MU && U - u0 <= 16 * HU, hv = HV < NV && V - v0 <= 16 * HV;
+        if (hu && hv)
+            grid_tile<T, HU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+        else if (hu)
+            grid_tile<T, HU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+        else if (hv)
+            grid_tile<T, MU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+        else
+            grid_tile<T, MU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+        __syncthreads();  // the next item reuses the stage
+    }
+}
+
+double grid_max_pad(bool fp64, int64_t R_block) {
+    // cycles of a SIMD per 64 terms: ~24 here; the general kernels ~180 / R_block
+    // + 8 in binary64 and ~55 / R_block + 5 in FP32
+    if (fp64) return R_block == 1 ? 6.0 : (R_block == 2 ? 3.0 : (R_block <= 4 ? 1.6 : 0.0));
+    return R_block == 1 ? 2.0 : 0.0;
+}
+
+hipError_t launch_grid_find(const double* px, const double* py, int64_t P, double max_pad,
+                            GridInfo* g, hipStream_t st) {
+    const int64_t nb = (P + 4095) / 4096;
+    hipLaunchKernelGGL(k_grid_find, dim3((unsigned)(nb < GRID_SLICES ? nb : GRID_SLICES)),
+                       dim3(1024), 0, st, px, py, P, max_pad, g);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_grid_sum_t(const SepArgs& a, const GridInfo* g, hipStream_t st) {
+    // tiles of 64 x 64 spare sines and cosines on the larger grids (13 cycles
+    // of a SIMD per 64 terms, 17 in tiles of 32 x 32, 21 in 32 x 16); with few
+    // realisations the 16 waves of a block split the frequencies, and where
+    // tiles of 32 x 32 leave half the compute units idle they are halved
+    const int64_t items = a.R * ((a.P + 1023) / 1024);
+    if (grid_unit(a.P) == 32 && a.R * ((a.P + 4095) / 4096) >= 512)
+        hipLaunchKernelGGL((k_grid_sum<T, 4, 4, 4>),
+                           dim3((unsigned)(a.R * (a.P / 4096) < 8192 ? a.R * (a.P / 4096) : 8192)),
+                           dim3(256), 0, st, a, g);
+    else if (items >= 512)
+        hipLaunchKernelGGL((k_grid_sum<T, 2, 2, 4>), dim3((unsigned)(items < 8192 ? items : 8192)),
+                           dim3(256), 0, st, a, g);
+    else if (items > 128)
+        hipLaunchKernelGGL((k_grid_sum<T, 2, 2, 16>), dim3((unsigned)items), dim3(1024), 0, st, a,
+                           g);
+    else
+        hipLaunchKernelGGL((k_grid_sum<T, 2, 1, 16>), dim3((unsigned)(2 * items)), dim3(1024), 0,
+                           st, a, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_sum(bool fp64, const SepArgs& a, const GridInfo* g, hipStream_t st) {
+    return fp64 ? launch_grid_sum_t<double>(a, g, st) : launch_grid_sum_t<float>(a, g, st);
 }
 
 }  // namespace qrfs

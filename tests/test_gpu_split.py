@@ -59,7 +59,8 @@ def check(got, ref, tol):
 
 @pytest.mark.parametrize("precision", [0, 1, 2, 3, 4])
 @pytest.mark.parametrize("K,R,R_block,P,mode", [
-    (65, 9, 9, 1, 0), (128, 40, 17, 4, 1), (1000, 33, 33, 37, 0), (2049, 16, 16, 64, 0),
+    (65, 9, 9, 1, 0), (128, 40, 17, 4, 1), (129, 3, 1, 5, 0), (700, 4, 1, 300, 1),
+    (1025, 7, 2, 128, 0), (640, 11, 4, 70, 1), (3001, 8, 8, 33, 0), (1000, 33, 33, 37, 0), (2049, 16, 16, 64, 0),
     (3000, 150, 75, 130, 1), (4097, 12, 10, 257, 0)])
 def test_phase_ranges(q, ctx, precision, K, R, R_block, P, mode):
     fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
@@ -72,7 +73,8 @@ def test_phase_ranges(q, ctx, precision, K, R, R_block, P, mode):
 
 
 @pytest.mark.parametrize("precision", [0, 1, 2, 3, 4])
-@pytest.mark.parametrize("K,R,R_block,P", [(700, 20, 20, 3), (2500, 70, 35, 33)])
+@pytest.mark.parametrize("K,R,R_block,P", [(700, 20, 20, 3), (2500, 70, 35, 33), (900, 5, 1, 9),
+                                             (333, 6, 3, 65)])
 def test_pistons_and_differences(q, ctx, precision, K, R, R_block, P):
     fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
     rng = np.random.default_rng(P)
