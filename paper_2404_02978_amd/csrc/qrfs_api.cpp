@@ -274,8 +274,18 @@ qrfs_status run_sum(int precision, int basis, int epi, qrfs::SumArgs a, int64_t 
     return QRFS_OK;
 }
 
+// Whether the stream is being captured (or that cannot be told).
+bool is_capturing(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // Most workspace that the partial sums of a stored contraction take.
-constexpr size_t kSplitCap = (size_t)64 << 20;
+constexpr size_t kSplitCap = (size_t)256 << 20;
 
 // Stored sums in the fused kernels.  Where their tiles leave compute units
 // idle, K is cut into ranges whose partial sums go through the workspace; not
@@ -289,23 +299,18 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     qrfs::StoreSplit sp =
         qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, room);
     if (sp.ksplit > 1) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-            (void)hipGetLastError();
-            cap = hipStreamCaptureStatusActive;
-        }
-        if (cap != hipStreamCaptureStatusNone || ensure_workspace(ctx, sp.bytes) != QRFS_OK) {
-            (void)hipGetLastError();
-            sp = {1, a.K, 0};
-        }
+        if (is_capturing(st) || ensure_workspace(ctx, sp.bytes) != QRFS_OK)
+            sp = {1, a.K, 0, 0.0};
     }
     a.ksplit = sp.ksplit;
     a.kspan = sp.kspan;
     a.phi_part = ctx->ws;
     // narrow sets: fields on a regular grid go through its product structure,
     // if the points are one (the general kernel sees the same answer)
+    // where those are worth its two more launches, 5 us when the points turn out
+    // to be none: a grid saves up to 5/6 of the time in binary64, half in FP32
     const double pad = qrfs::grid_max_pad(precision == QRFS_PREC_FP64, a.R_block);
-    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids && a.P >= 171 &&
+    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids && sp.us > (precision == QRFS_PREC_FP64 ? 25.0 : 60.0) && a.P >= 171 &&
         a.P <= ((int64_t)1 << 24)) {
         qrfs::GridInfo* g = ctx->grids + ctx->next_grid.fetch_add(1) % kGridRing;
         hipError_t e = qrfs::launch_grid_find(a.px, a.py, a.P, pad, g, st);
@@ -337,19 +342,156 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     return QRFS_OK;
 }
 
-// Whether the two-phase kernel contracts this problem: MFMA precisions,
-// outputs wide enough to amortise the coefficient tiles, and enough
-// 256 x 256 tiles to fill the chip (or forced by the context).
-bool use_wide(const qrfs_context* ctx, int precision, int64_t P, int64_t R, int64_t R_block,
-              bool caller_coef) {
+// Sizes of the two-phase contraction of a problem.
+struct WidePlan {
+    int KCH;             // frequencies per chunk
+    int64_t nch, nkv;    // chunks, padded contraction length
+    size_t row32;        // bytes of 32 rows of coefficient tiles
+    int64_t cts, rts_set;
+    size_t scale_bytes;  // FP16X3: one scale per set
+    int64_t sets_piece, rows_piece;  // sets, or rows of one set, per piece
+    size_t tile_bytes;   // of the coefficient tiles of a piece
+    int ksplit;          // frequency ranges (one piece only) and
+    int64_t split_ch;    // their chunks
+    size_t part_bytes;   // of partial sums
+    size_t bytes() const { return tile_bytes + 256 + scale_bytes + part_bytes; }
+};
+
+// ksplit: frequency ranges asked for; fewer where their partial sums exceed
+// kSplitCap or the context's cap, or the coefficient tiles need pieces.
+qrfs_status wide_plan(const qrfs_context* ctx, int precision, int64_t K, int64_t P, int64_t R,
+                      int64_t R_block, int ksplit, WidePlan& p) {
+    p.KCH = qrfs::wide_chunk(precision);
+    p.nch = cdiv(K, p.KCH);
+    p.nkv = p.nch * 2 * p.KCH;
+    p.row32 = qrfs::wide_frag_bytes_per_row32(precision, p.nkv);
+    p.cts = cdiv(P, 256);
+    p.rts_set = cdiv(R_block, 256);
+    const int64_t n_sets = cdiv(R, R_block);
+    // coefficient tiles take at most ctx->tile_cap of workspace per piece
+    // (one 256-row block of one set at least); behind them the store sink
+    // (256 B) and, for FP16X3, one scale per set
+    p.scale_bytes =
+        precision == QRFS_PREC_FP16X3 ? align256((size_t)n_sets * sizeof(double)) : 0;
+    size_t cap = ctx->tile_cap;
+    const size_t extra = 512 + p.scale_bytes;
+    if (ctx->ws_cap && ctx->ws_cap < cap + extra)
+        cap = ctx->ws_cap > extra ? ctx->ws_cap - extra : 0;
+    const size_t set_bytes = (size_t)p.rts_set * 8 * p.row32;
+    p.sets_piece = 1;
+    p.rows_piece = R_block;
+    if (set_bytes <= cap) {
+        p.sets_piece = (int64_t)(cap / set_bytes);
+        const int64_t max_blocks = kMaxLaunchBlocks;
+        if (p.sets_piece * p.rts_set * p.cts > max_blocks)
+            p.sets_piece = max_blocks / (p.rts_set * p.cts);
+        if (p.sets_piece < 1) return fail(QRFS_ERR_INVALID_ARG, "problem too large for one set");
+        if (p.sets_piece > n_sets) p.sets_piece = n_sets;
+    } else {
+        int64_t tiles = (int64_t)(cap / (8 * p.row32));
+        p.rows_piece = (tiles < 1 ? 1 : tiles) * 256;
+    }
+    p.tile_bytes = align256((size_t)p.sets_piece * cdiv(p.rows_piece, 256) * 8 * p.row32);
+    p.ksplit = 1;
+    p.split_ch = p.nch;
+    p.part_bytes = 0;
+    const size_t one = (size_t)R * P * sizeof(float);
+    if (p.sets_piece == n_sets && p.rows_piece >= R_block) {
+        while (ksplit > 1 && ((size_t)ksplit * one > kSplitCap ||
+                              (ctx->ws_cap && p.bytes() + (size_t)ksplit * one > ctx->ws_cap)))
+            --ksplit;
+        if (ksplit > 1) {
+            p.split_ch = cdiv(p.nch, ksplit);
+            p.split_ch += p.split_ch & 1;
+            p.ksplit = (int)cdiv(p.nch, p.split_ch);
+            p.part_bytes = p.ksplit > 1 ? (size_t)p.ksplit * one : 0;
+        }
+    }
+    return QRFS_OK;
+}
+
+// Whether a problem has the tiles to fill the chip with the two-phase kernel
+// and the columns and rows to amortise it.
+bool wide_fills(int64_t P, int64_t R, int64_t R_block) {
+    return P >= 1024 && R_block >= 128 &&
+           cdiv(R, R_block) * cdiv(R_block, 256) * cdiv(P, 256) >= 512;
+}
+
+// Frequencies that the two-phase kernel sums in FP32 before it adds them into
+// the output.  Problems that fill the chip: ctx->range_freqs, and all of K in
+// split-BF16, whose operand rounding is the larger error.  Others come here
+// from the fused kernels, which fold their sums every 32 frequencies, and keep
+// those kernels' accuracy: errors against binary64 at K = 1200, 4096, 10007 and
+// 40000 are 2.2, 2.9, 4.0 and 7.4e-7 (BF16x6, one fused launch), here 2.2, 2.4,
+// 3.2 and 7.0e-7 in ranges of K / 80 frequencies within [64, 512] (9.7e-7 at
+// 10007 in ranges of 2048); FP16x3, with half the products, 2.4, 2.4, 3.3 and
+// 4.3e-7 in ranges of K / 32 within [128, 512] (fused 2.2, 2.8, 3.9, 7.2e-7).
+int64_t wide_range(const qrfs_context* ctx, int precision, int64_t K, int64_t P, int64_t R,
+                   int64_t R_block) {
+    if (wide_fills(P, R, R_block))
+        return precision == QRFS_PREC_SPLIT_BF16 ? K : ctx->range_freqs;
+    if (precision == QRFS_PREC_SPLIT_BF16) return ctx->range_freqs < 2048 ? ctx->range_freqs : 2048;
+    const bool f16 = precision == QRFS_PREC_FP16X3;
+    const int64_t least = f16 ? 128 : 64;
+    int64_t r = K / (f16 ? 32 : 80);
+    r = r < least ? least : (r > 512 ? 512 : r);
+    return r < ctx->range_freqs ? r : ctx->range_freqs;
+}
+
+// Whether, and in how many frequency ranges, the two-phase kernel contracts
+// this problem.  Forced by the context, or MFMA precisions by the estimated
+// times of both kernels (us).  Two-phase: a 256 x 256 tile takes a compute
+// unit wide_tile_ns per frequency, mostly for its basis, and every coefficient
+// is drawn once (2.3 ps per padded row and frequency).  Fused: see store_split
+// (coefficients redrawn per column tile).  At 100 realisations (50 per set) of
+// 2500 points x 4096 frequencies in FP16x3 the fused kernel takes 139 us and
+// this one 66, at ten apertures x 1e4 realisations 115 and 433.  Captured calls
+// keep to problems that fill the chip whatever the path: a call that needs no
+// workspace must not take one under capture.
+bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int64_t P, int64_t R,
+              int64_t R_block, bool caller_coef, hipStream_t st, int* ksplit) {
+    *ksplit = 1;
     if (precision == QRFS_PREC_FP64 || ctx->wide_path == 1) return false;
     // FP16X3 scales the coefficient tiles by the largest value the generators
     // can draw; caller-given coefficients contract in the fused kernel
     if (precision == QRFS_PREC_FP16X3 && caller_coef) return false;
     if (P > ((int64_t)1 << 22)) return false;  // 256 rows of output within 32-bit tile offsets
-    if (ctx->wide_path == 2) return true;
     const int64_t tiles = cdiv(R, R_block) * cdiv(R_block, 256) * cdiv(P, 256);
-    return P >= 1024 && R_block >= 128 && tiles >= 512;
+    const bool full = wide_fills(P, R, R_block);
+    const bool capturing = is_capturing(st);
+    if (ctx->wide_path == 0 && !full && (R_block <= 8 || capturing)) return false;
+    if (capturing) return true;
+    const double fused = qrfs::store_split(precision, basis, K, R, R_block, P, kSplitCap).us;
+    double best = 1e300;
+    const double coef = 2.3e-6 * (double)(cdiv(R, R_block) * cdiv(R_block, 256) * 256) * (double)K;
+    const double one_us = 2.0 / 4e6 * (double)R * (double)P * sizeof(float);  // written and read
+    const int64_t range = wide_range(ctx, precision, K, P, R, R_block);
+    // the fullest tile of a set, and the mean over its row tiles
+    const int64_t rest = R_block % 256;
+    const double most = qrfs::wide_tile_ns(precision, basis, R_block);
+    const double mean = (most * (double)(R_block / 256) +
+                         (rest ? qrfs::wide_tile_ns(precision, basis, rest) : 0.0)) /
+                        (double)cdiv(R_block, 256);
+    for (int k = 1; k <= 32 && (k == 1 || (int64_t)k * 64 <= K); ++k) {
+        if (k > 1 && (size_t)k * R * P * sizeof(float) > kSplitCap) break;
+        const int64_t rounds = cdiv(tiles * k, 256);
+        const double ns = rounds > 1 ? std::fmax(most, mean * (double)rounds) : most;
+        // each range after a block's first is added into its tile in memory
+        const int64_t adds = cdiv(cdiv(K, (int64_t)k), range) - 1;
+        const double us = ns * 1e-3 * (double)K / k + coef + 12.0 + (double)(adds * k) * one_us +
+                          (k > 1 ? 8.0 + k * one_us : 0.0);
+        if (us < 0.95 * best) {
+            best = us;
+            *ksplit = k;
+        }
+    }
+    if (ctx->wide_path == 2 || full) return true;
+    WidePlan p;
+    if (best > 0.9 * fused || wide_plan(ctx, precision, K, P, R, R_block, *ksplit, p) != QRFS_OK)
+        return false;
+    // the fused kernel needs no workspace: it stays where this one's would
+    // exceed the cap
+    return !(ctx->ws_cap && p.bytes() > ctx->ws_cap);
 }
 
 // Two-phase contraction (EPI_STORE) over all sets: per piece, the
@@ -357,53 +499,34 @@ bool use_wide(const qrfs_context* ctx, int precision, int64_t P, int64_t R, int6
 // ranges of ctx->range_freqs frequencies in FP32 and add each into the
 // output; split-BF16 uses a single range).
 qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a,
-                     int64_t n_sets, hipStream_t st) {
-    const int KCH = qrfs::wide_chunk(precision);
-    const int64_t nch = cdiv(a.K, KCH);
-    const int64_t nkv = nch * 2 * KCH;
-    const size_t row32 = qrfs::wide_frag_bytes_per_row32(precision, nkv);
-    const int64_t cts = cdiv(a.P, 256);
-    const int64_t rts_set = cdiv(a.R_block, 256);
-    // coefficient tiles take at most ctx->tile_cap of workspace per piece
-    // (one 256-row block of one set at least); behind them the store sink
-    // (256 B) and, for FP16X3, one scale per set
-    const size_t scale_bytes =
-        precision == QRFS_PREC_FP16X3 ? align256((size_t)n_sets * sizeof(double)) : 0;
-    size_t cap = ctx->tile_cap;
-    const size_t extra = 512 + scale_bytes;
-    if (ctx->ws_cap && ctx->ws_cap < cap + extra) cap = ctx->ws_cap > extra ? ctx->ws_cap - extra : 0;
-    const size_t set_bytes = (size_t)rts_set * 8 * row32;
-    int64_t sets_piece = 1, rows_piece = a.R_block;
-    if (set_bytes <= cap) {
-        sets_piece = (int64_t)(cap / set_bytes);
-        const int64_t max_blocks = kMaxLaunchBlocks;
-        if (sets_piece * rts_set * cts > max_blocks) sets_piece = max_blocks / (rts_set * cts);
-        if (sets_piece < 1) return fail(QRFS_ERR_INVALID_ARG, "problem too large for one set");
-        if (sets_piece > n_sets) sets_piece = n_sets;
-    } else {
-        int64_t tiles = (int64_t)(cap / (8 * row32));
-        rows_piece = (tiles < 1 ? 1 : tiles) * 256;
-    }
-    const size_t tile_bytes = align256((size_t)sets_piece * cdiv(rows_piece, 256) * 8 * row32);
-    qrfs_status s = ensure_workspace(ctx, tile_bytes + 256 + scale_bytes);
+                     int64_t n_sets, int ksplit, hipStream_t st) {
+    WidePlan p;
+    qrfs_status s = wide_plan(ctx, precision, a.K, a.P, a.R, a.R_block, ksplit, p);
     if (s) return s;
-    double* ascale = (double*)((char*)ctx->ws + tile_bytes + 256);
+    const int KCH = p.KCH;
+    const int64_t nch = p.nch, sets_piece = p.sets_piece, rows_piece = p.rows_piece;
+    s = ensure_workspace(ctx, p.bytes());
+    if (s) return s;
+    double* ascale = (double*)((char*)ctx->ws + p.tile_bytes + 256);
     if (precision == QRFS_PREC_FP16X3) {
         hipError_t e = qrfs::launch_wide_scale(a.w, a.K, n_sets, ascale, st);
         if (e != hipSuccess) return hip_fail(e, "tile scale launch");
     }
-    // accumulation ranges: whole K for split-BF16, else about
-    // ctx->range_freqs frequencies (an even number of chunks)
-    int64_t rch = precision == QRFS_PREC_SPLIT_BF16 ? nch : cdiv(ctx->range_freqs, KCH);
+    a.ksplit = p.ksplit;
+    a.phi_part = (char*)ctx->ws + p.tile_bytes + 256 + p.scale_bytes;
+    // accumulation ranges, an even number of chunks each
+    const int64_t range = wide_range(ctx, precision, a.K, a.P, a.R, a.R_block);
+    int64_t rch = cdiv(range, KCH);
     rch += rch & 1;
     const double* fx0 = a.fx;
     const double* fy0 = a.fy;
     const double* w0 = a.w;
     qrfs::WideArgs wa{};
-    wa.nkv = nkv;
-    wa.cts = cts;
+    wa.nkv = p.nkv;
+    wa.cts = p.cts;
+    wa.split_ch = p.split_ch;
     wa.ctile = ctx->ws;
-    wa.sink = (float*)((char*)ctx->ws + tile_bytes);
+    wa.sink = (float*)((char*)ctx->ws + p.tile_bytes);
     for (int64_t s0 = 0; s0 < n_sets; s0 += sets_piece) {
         const int64_t s1 = s0 + sets_piece < n_sets ? s0 + sets_piece : n_sets;
         for (int64_t off = 0; off < a.R_block; off += rows_piece) {
@@ -430,8 +553,14 @@ qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs 
             if (e != hipSuccess) return hip_fail(e, "two-phase contraction launch");
         }
     }
+    if (p.ksplit > 1) {
+        hipError_t e = qrfs::launch_split_sum(false, a.phi_part, p.ksplit, a.R * a.P, a.out,
+                                              nullptr, st);
+        if (e != hipSuccess) return hip_fail(e, "partial-sum launch");
+    }
     return QRFS_OK;
 }
+
 
 qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
                       const double* fy, const double* w, int64_t P, const double* px,
@@ -482,8 +611,10 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
         a.gx = 2.0 * M_PI * grad_u[0];
         a.gy = 2.0 * M_PI * grad_u[1];
     }
-    if (use_wide(ctx, precision, P, R, R_block, coef != nullptr))
-        s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
+    int ksplit = 1;
+    if (use_wide(ctx, precision, basis, K, P, R, R_block, coef != nullptr, (hipStream_t)stream,
+                 &ksplit))
+        s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), ksplit, (hipStream_t)stream);
     else
         s = fused_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
     if (s) return s;

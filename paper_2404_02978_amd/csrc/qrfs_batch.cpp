@@ -185,6 +185,7 @@ qrfs_status ensure_wide(qrfs_batch* b) {
         wa.nkv = nch * 2 * KCH;
         wa.ch0 = 0;
         wa.ch1 = nch;
+        wa.split_ch = nch;
         int64_t rch = b->precision == QRFS_PREC_SPLIT_BF16 ? nch : cdiv(b->range_freqs, KCH);
         wa.range_ch = rch + (rch & 1);
         wa.accumulate = 0;

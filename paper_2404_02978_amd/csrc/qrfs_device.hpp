@@ -500,7 +500,22 @@ __device__ __forceinline__ float aperture_filter_f32(double D, double d, double 
     return (float)(2.0 * j1x_pi_f32(D * f));
 }
 
-
+// The same for many frequencies of one aperture: the factors of its edges,
+// 2 D^2 / (D^2 - d^2) and 2 d^2 / (D^2 - d^2), formed once (a binary64 division
+// per value was a fifth of the filter's instructions).
+struct ApertureEdges {
+    double D, d, cD, cd;
+};
+__device__ __forceinline__ ApertureEdges aperture_edges(double D, double d) {
+    const double q = 2.0 / (D * D - d * d);
+    return ApertureEdges{D, d, D * D * q, d * d * q};
+}
+__device__ __forceinline__ float aperture_filter_f32(const ApertureEdges& e, double f) {
+    if (f == 0.0) return 1.0f;
+    double v = e.cD * j1x_pi_f32(e.D * f);
+    if (e.d > 0.0) v -= e.cd * j1x_pi_f32(e.d * f);
+    return (float)v;
+}
 
 // Piston basis: the amplitude factor and the argument shift (cycles) that
 // turn the piston into its gradient along u when `grad` is set, with

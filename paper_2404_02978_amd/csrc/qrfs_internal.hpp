@@ -100,6 +100,8 @@ struct WideArgs {
     int64_t cts;      // 256-column block tiles
     int64_t nkv;      // contraction length 2K padded to whole chunks
     int64_t ch0, ch1; // chunks [ch0, ch1) of frequencies this launch contracts
+    int64_t split_ch; // s.ksplit > 1: chunks (even) of each of the ksplit ranges whose
+                      // sums go to s.phi_part[range][R][P]
     int64_t range_ch; // chunks per accumulation range (even), each ending with
                       // an add of the tile into the output
     int32_t accumulate;  // 0: the first range stores its sums, 1: it adds them
@@ -111,6 +113,9 @@ struct WideArgs {
 // coefficient tiles per 32 rows for a padded contraction length nkv
 int wide_chunk(int precision);
 size_t wide_frag_bytes_per_row32(int precision, int64_t nkv);
+// time (ns) that a 256 x 256 tile with `rows` rows of its set takes a compute
+// unit per frequency, all busy
+double wide_tile_ns(int precision, int basis, int64_t rows);
 hipError_t launch_wide_coef(int precision, const WideArgs& wa, hipStream_t st);
 // FP16x3: per set, the power of two that scales its coefficient tiles into
 // the fp16 range (from the set's largest weight); n_sets blocks.
@@ -203,6 +208,7 @@ struct StoreSplit {
     int ksplit;
     int64_t kspan;
     size_t bytes;  // of partial sums
+    double us;     // estimated time
 };
 StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
                        size_t max_bytes);

@@ -216,11 +216,8 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
     const bool pok = p < a.P;
     const double px = pok ? a.px[p] : 0.0;
     const double py = pok ? a.py[p] : 0.0;
-    double pD = 1.0, pd = 0.0;
-    if (BASIS == BASIS_PISTON && pok) {
-        pD = a.apD[p];
-        pd = a.apd[p];
-    }
+    ApertureEdges ap{};
+    if (BASIS == BASIS_PISTON) ap = aperture_edges(pok ? a.apD[p] : 1.0, pok ? a.apd[p] : 0.0);
     const double* fx = a.fx + sl * a.K;
     const double* fy = a.fy + sl * a.K;
     const double* w = a.w + sl * a.K;
@@ -253,7 +250,7 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
             double t = cfx * px + cfy * py;
             double amp = sw[kk];
             if (BASIS == BASIS_PISTON) {
-                amp *= (double)aperture_filter_f32(pD, pd, sqrt(cfx * cfx + cfy * cfy)) *
+                amp *= (double)aperture_filter_f32(ap, sqrt_f32_nr(cfx * cfx + cfy * cfy)) *
                        grad_factor(a.grad, a.gx, a.gy, cfx, cfy);
                 t += grad_shift(a.grad);
             }
@@ -417,7 +414,8 @@ struct MfmaSmem {
     __attribute__((aligned(16))) float sBf[NBF];
     __attribute__((aligned(16))) __bf16 sBp[NPL][NBH];
     double sred[8][NT][2];
-    double spx[NT], spy[NT], sD[NT], sd[NT];
+    double spx[NT], spy[NT];
+    ApertureEdges sap[NT];
     double smax[8];  // FP16x3: per-wave largest amplitude / coefficient
 };
 
@@ -455,8 +453,6 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
     auto& sred = sm.sred;
     double* spx = sm.spx;
     double* spy = sm.spy;
-    double* sD = sm.sD;
-    double* sd = sm.sd;
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -481,10 +477,8 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
         bool ok = p < a.P;
         spx[i] = ok ? a.px[p] : 0.0;
         spy[i] = ok ? a.py[p] : 0.0;
-        if (BASIS == BASIS_PISTON) {
-            sD[i] = ok ? a.apD[p] : 1.0;
-            sd[i] = ok ? a.apd[p] : 0.0;
-        }
+        if (BASIS == BASIS_PISTON)
+            sm.sap[i] = aperture_edges(ok ? a.apD[p] : 1.0, ok ? a.apd[p] : 0.0);
     }
     __syncthreads();
 
@@ -561,13 +555,13 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
             }
         }
         // basis of this chunk into buffer `buf`
-        const double fmag = BASIS == BASIS_PISTON ? sqrt(cfx * cfx + cfy * cfy) : 0.0;
+        const double fmag = BASIS == BASIS_PISTON ? sqrt_f32_nr(cfx * cfx + cfy * cfy) : 0.0;
         const double gw =
             BASIS == BASIS_PISTON ? cw * grad_factor(a.grad, a.gx, a.gy, cfx, cfy) : cw;
         const double sh = BASIS == BASIS_PISTON ? grad_shift(a.grad) : 0.0;
         for (int pp = pp0; pp < NT; pp += cstep) {
             double amp = gw * (kAmp * wscale);
-            if (BASIS == BASIS_PISTON) amp *= (double)aperture_filter_f32(sD[pp], sd[pp], fmag);
+            if (BASIS == BASIS_PISTON) amp *= (double)aperture_filter_f32(sm.sap[pp], fmag);
             float cb, sb;
             double t = cfx * spx[pp] + cfy * spy[pp];
             if (BASIS == BASIS_PISTON) t += sh;  // (an add of 0 would not fold away)
@@ -1202,39 +1196,53 @@ hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, 
 // host's part) and their traffic, against a range's share of the time.
 StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
                        size_t max_bytes) {
-    StoreSplit s{1, K, 0};
+    StoreSplit s{1, K, 0, 0.0};
     const size_t one = (size_t)R * P * (precision == 0 ? sizeof(double) : sizeof(float));
     // written and read once at ~4 TB/s
     const double pass_us = 2.0 * (double)one / 4e6;
     double best = 1e300;
-    const int64_t nch = cdiv(K, KC);
     const int64_t kmax = K / 64 < 32 ? K / 64 : 32;  // at least 64 frequencies per range
     int64_t base = 0, slots = 0;
     double block_us = 0.0;
-    const bool narrow = R_block <= 8;
-    if (narrow) {
+    const bool vector = R_block <= 8;  // the vector ALU's kernels
+    if (vector) {
         // one point per thread: 148 cycles of a SIMD per frequency and wave in
         // binary64 (44 in FP32 class, ~8 more per realisation), more with a
-        // filter, and four waves per SIMD to hide their latency
+        // filter, at ~2 GHz; a wave alone on its SIMD waits on itself for the
+        // time of another 0.7
         const int nt = narrow_threads(P);
-        base = cdiv(R, R_block) * cdiv(P, nt);
-        slots = 256 * (1024 / nt);
-        const double filter = basis == BASIS_PISTON ? (precision == 0 ? 1000.0 : 400.0) : 0.0;
-        block_us = (double)K * 4.0 *
+        base = cdiv(R, R_block) * cdiv(P, nt) * (nt / 64);  // waves
+        slots = 1024;
+        const double filter = basis == BASIS_PISTON ? (precision == 0 ? 1000.0 : 300.0) : 0.0;
+        block_us = (double)K *
                    ((precision == 0 ? 148.0 : 44.0) + 8.0 * (double)R_block + filter) / 2000.0;
     } else if (precision != 0) {
         const MfmaShape m = mfma_shape(precision, basis, R_block, P);
         base = cdiv(R, R_block) * cdiv(R_block, 32 * m.MW * m.WV) * cdiv(P, 32 * m.NB);
-        // blocks that run at full speed side by side: two waves per SIMD
-        slots = 256 * (8 / m.WV > 1 ? 8 / m.WV : 1);
-        // one chunk of 32 frequencies takes a block about 4 us alone
-        block_us = 4.0 * (double)nch;
+        // a wave takes c ns per frequency for its 32 MW rows x 32 NB columns when
+        // the compute unit runs 4 of them, 1.4 times that with fewer: from the
+        // large screen in the fused kernels (787, 369, 491, 357 ms) and ten
+        // apertures x 1e4 realisations (130, 100, 110, 95 us without the rest of
+        // the call); 12 ns of it (NB = 2, 4 waves) are the block's basis, which
+        // fewer waves share.  LDS holds 2 or 3 blocks of 64 columns (twice as
+        // many of 32): a set of one wave does not fill a compute unit.
+        static const double wide[5] = {0.0, 94.0, 88.0, 117.0, 85.0};
+        static const double narrow[5] = {0.0, 60.0, 40.0, 50.0, 38.0};
+        const double basis_ns = m.NB == 2 ? 48.0 : (basis == BASIS_PISTON ? 160.0 : 24.0);
+        const double c = (m.NB == 2 ? wide[precision] : narrow[precision]) +
+                         basis_ns * (1.0 / m.WV - 0.25) +
+                         (basis == BASIS_PISTON ? 40.0 : 0.0);
+        const int lds = (precision == 3 ? 2 : 3) * (m.NB == 2 ? 1 : 2);
+        const int fit = 4 / m.WV > 1 ? (4 / m.WV < lds ? 4 / m.WV : lds) : 1;
+        slots = 256 * fit;
+        block_us = 1e-3 * c * (double)K * (fit * m.WV < 4 ? 1.4 : 1.0);
     }
     for (int64_t k = 1; k <= (kmax < 1 ? 1 : kmax); ++k) {
         if (k > 1 && (size_t)k * one > max_bytes) break;
         const double us =
-            (precision == 0 && !narrow ? fm_shape(basis, K, R, R_block, P, (int)k).us
-                            : (double)cdiv(base * k, slots) * block_us / (double)k) +
+            (precision == 0 && !vector ? fm_shape(basis, K, R, R_block, P, (int)k).us
+                            : fmax((double)cdiv(base * k, slots), vector ? 1.7 : 1.4) * block_us /
+                                  (double)k) +
             (k > 1 ? 8.0 + (double)k * pass_us : 0.0);
         if (us < 0.95 * best) {
             best = us;
@@ -1243,6 +1251,7 @@ StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R
     }
     s.kspan = cdiv(cdiv(K, s.ksplit), 64) * 64;  // whole chunks of every kernel
     s.ksplit = (int)cdiv(K, s.kspan);            // no empty ranges
+    s.us = best;
     s.bytes = s.ksplit > 1 ? (size_t)s.ksplit * one : 0;
     if (s.ksplit == 1) s.kspan = K;
     return s;

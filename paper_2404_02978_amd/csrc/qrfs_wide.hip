@@ -92,6 +92,16 @@ struct WideCfg<4> {  // FP16x3: fp16 hi + lo planes (coefficients scaled per set
     typedef f16x8 Frag;
 };
 
+double wide_tile_ns(int precision, int basis, int64_t rows) {
+    // {basis, per 64 rows that are summed}: large screen (16 rounds of full
+    // tiles x 65536 frequencies: 521, 158, 297, 170 ms) and sets of 30 rows
+    // (544 tiles x 3000 frequencies: 1.98, 0.75, 1.08, 0.76 ms)
+    static const double ns[5][2] = {{0, 0}, {248, 62}, {107, 11}, {132, 38}, {103, 15}};
+    const int64_t n64 = rows >= 256 ? 4 : (rows + 63) / 64;
+    // pistons evaluate the filter for every column and frequency of a tile
+    return ns[precision][0] + ns[precision][1] * (double)n64 + (basis == BASIS_PISTON ? 250.0 : 0.0);
+}
+
 int wide_chunk(int precision) { return precision == 3 ? 8 : 16; }
 
 size_t wide_frag_bytes_per_row32(int precision, int64_t nkv) {
@@ -251,12 +261,15 @@ struct WideTile {
     const double* fy;
     const double* w;
     const Frag* ap;  // this wave's first fragment
-    double px, py, pD, pd;
+    double px, py;
+    ApertureEdges aper;
+    float* out;
     f32x16 acc[MB][4];
 
     __device__ __forceinline__ WideTile(WideSmem<PREC>& s, const WideArgs& wa, int64_t sl_,
-                                        int64_t rt, int64_t ct)
-        : sm(s), a(wa.s), sl(sl_) {
+                                        int64_t rt, int64_t ct, int64_t ch0, int64_t ch1,
+                                        float* out_)
+        : sm(s), a(wa.s), sl(sl_), out(out_) {
         const int tid = threadIdx.x;
         lane = tid & 63;
         r = lane & 31;
@@ -265,8 +278,8 @@ struct WideTile {
         wm = wave >> 1;
         wn = wave & 1;
         part = __builtin_amdgcn_readfirstlane(tid >> 8);
-        c0 = wa.ch0;
-        nch = wa.ch1 - wa.ch0;
+        c0 = ch0;
+        nch = ch1 - ch0;
         NKB = wa.nkv / C::KB;
         fx = a.fx + sl * a.K;
         fy = a.fy + sl * a.K;
@@ -275,12 +288,8 @@ struct WideTile {
         const bool pok = pcol < a.P;
         px = pok ? a.px[pcol] : 0.0;
         py = pok ? a.py[pcol] : 0.0;
-        pD = 1.0;
-        pd = 0.0;
-        if (BASIS == BASIS_PISTON && pok) {
-            pD = a.apD[pcol];
-            pd = a.apd[pcol];
-        }
+        if (BASIS == BASIS_PISTON)
+            aper = aperture_edges(pok ? a.apD[pcol] : 1.0, pok ? a.apd[pcol] : 0.0);
         ap = (const Frag*)wa.ctile + (sl * wa.rt32 + rt * 8 + wm * MB) * NKB * NPL * 64 + lane;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
@@ -341,7 +350,7 @@ struct WideTile {
             // their aperture's filter (and the gradient factor) here
             double amp = 1.0;
             if (BASIS == BASIS_PISTON) {
-                amp = (double)aperture_filter_f32(pD, pd, sqrt(cfx * cfx + cfy * cfy)) *
+                amp = (double)aperture_filter_f32(aper, sqrt_f32_nr(cfx * cfx + cfy * cfy)) *
                       grad_factor(a.grad, a.gx, a.gy, cfx, cfy);
                 t += grad_shift(a.grad);
             }
@@ -390,12 +399,22 @@ struct WideTile {
         }
     }
 
+    // rows of the set in this launch
+    __device__ __forceinline__ int64_t row_limit(const WideArgs& wa) const {
+        const int64_t set = a.set0 + sl;
+        const int64_t set_rows =
+            a.R - set * a.R_block < a.R_block ? a.R - set * a.R_block : a.R_block;
+        return wa.row_off + wa.rows < set_rows ? wa.row_off + wa.rows : set_rows;
+    }
+
     // one chunk: MFMAs of chunk ch (buffer ch & 1) with the fragments of its
     // steps, which alternate between F[PAR] and F[PAR ^ 1]; each step loads
     // the next step's fragments into the other half.  The basis of chunk
     // ch + 1 (frequencies `fcur`) goes into the other buffer, and chunk
-    // ch + 2's frequencies are loaded into `fnxt`.
-    template <int PAR>
+    // ch + 2's frequencies are loaded into `fnxt`.  ACT: the wave has rows to
+    // sum; a wave whose rows lie past the end of its set only takes its part
+    // of the basis.
+    template <int PAR, bool ACT>
     __device__ __forceinline__ void chunk(int64_t ch, Frag (&F)[2][MB][NPL],
                                           const double (&fcur)[3], double (&fnxt)[3]) {
         const int buf = (int)(ch & 1);
@@ -403,10 +422,10 @@ struct WideTile {
 #pragma unroll
         for (int st = 0; st < NSTEP; ++st) {
             const int64_t kn = (c0 + ch) * NSTEP + st + 1;
-            load_step(kn < (c0 + nch) * NSTEP ? kn : kn - 1, F[(PAR + st + 1) & 1]);
+            if constexpr (ACT) load_step(kn < (c0 + nch) * NSTEP ? kn : kn - 1, F[(PAR + st + 1) & 1]);
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
-                mfma_group(st, nb, buf, F[(PAR + st) & 1]);
+                if constexpr (ACT) mfma_group(st, nb, buf, F[(PAR + st) & 1]);
                 const int s = st * 4 + nb;
                 // the last chunk fills the spare buffer with unused values
 #if QRFS_WIDE_PHASE
@@ -437,16 +456,14 @@ struct WideTile {
     // compiler cannot hoist the element addresses out of the chunk loop.
     __device__ __forceinline__ void store(const WideArgs& wa, int64_t rt, int64_t ct, bool add) {
         const int64_t set = a.set0 + sl;
-        const int64_t set_rows =
-            a.R - set * a.R_block < a.R_block ? a.R - set * a.R_block : a.R_block;
-        const int64_t lim = wa.row_off + wa.rows < set_rows ? wa.row_off + wa.rows : set_rows;
+        const int64_t lim = row_limit(wa);
         const int64_t row0 = wa.row_off + rt * WT + wm * 32 * MB + 4 * h;
         const int64_t col0 = ct * WT + wn * 128 + r;
         int64_t base = (set * a.R_block + row0) * a.P + col0;
         int32_t rrem = (int32_t)(lim - row0 < 256 ? lim - row0 : 256);
         int32_t crem = (int32_t)(a.P - col0 < 256 ? a.P - col0 : 256);
         asm volatile("" : "+v"(base), "+v"(rrem), "+v"(crem));
-        float* o = (float*)a.out + base;
+        float* o = out + base;
         float* sink = wa.sink + lane;
         if constexpr (PREC == 4) {
             // FP16x3: the coefficient tiles' power of two comes off exactly
@@ -500,15 +517,41 @@ struct WideTile {
     }
 };
 
-// One 256 x 256 output tile: rows [rt] of set sl, columns [ct], all
-// chunks of wa; every thread of the block calls it (it synchronises).
+// The ranges of a tile from its second chunk's frequencies on: ranges of
+// wa.range_ch chunks (even, so every range starts with the same buffer
+// parity), each ending with a store or an add of the tile; within a range,
+// chunks in pairs, so that the fragment and frequency buffers are named at
+// compile time (NSTEP steps per chunk flip the fragment half NSTEP times).
+// The pipeline runs on across range ends.
+template <bool ACT, typename Tile, typename Frag, int MB, int NPL>
+__device__ __forceinline__ void wide_ranges(Tile& T, const WideArgs& wa, Frag (&F)[2][MB][NPL],
+                                            double (&fq0)[3], double (&fq1)[3], int64_t rt,
+                                            int64_t ct) {
+    const int64_t nch = T.nch;
+    for (int64_t rs = 0; rs < nch; rs += wa.range_ch) {
+        const int64_t re = rs + wa.range_ch < nch ? rs + wa.range_ch : nch;
+        for (int64_t ch = rs; ch < re; ch += 2) {
+            T.template chunk<0, ACT>(ch, F, fq0, fq1);
+            __syncthreads();
+            if (ch + 1 < re) {
+                T.template chunk<Tile::NSTEP & 1, ACT>(ch + 1, F, fq1, fq0);
+                __syncthreads();
+            }
+        }
+        if constexpr (ACT) T.store(wa, rt, ct, wa.accumulate || rs > 0);
+    }
+}
+
+// One 256 x 256 output tile: rows [rt] of set sl, columns [ct], chunks
+// [ch0, ch1); every thread of the block calls it (it synchronises).
 template <int PREC, int BASIS, int WV>
 __device__ __forceinline__ void wide_tile_run(WideSmem<PREC>& sm, const WideArgs& wa, int64_t sl,
-                                              int64_t rt, int64_t ct) {
+                                              int64_t rt, int64_t ct, int64_t ch0, int64_t ch1,
+                                              float* out) {
     using Tile = WideTile<PREC, BASIS, WV>;
     typedef typename Tile::Frag Frag;
     constexpr int NSTEP = Tile::NSTEP, NPL = Tile::NPL, MB = Tile::MB, NPART = Tile::NPART;
-    Tile T(sm, wa, sl, rt, ct);
+    Tile T(sm, wa, sl, rt, ct, ch0, ch1, out);
     Frag F[2][MB][NPL];
     double fq0[3], fq1[3], fq2[3];
     // prologue: basis of the first chunk, fragments of the first step,
@@ -524,25 +567,11 @@ __device__ __forceinline__ void wide_tile_run(WideSmem<PREC>& sm, const WideArgs
 #pragma unroll
     for (int g = 0; g < Tile::NGRP; ++g) T.produce(g * NPART + T.part, 0, fq2[0], fq2[1], fq2[2]);
     __syncthreads();
-
-    // ranges of wa.range_ch chunks (even, so every range starts with the
-    // same buffer parity), each ending with a store or an add of the tile;
-    // within a range, chunks in pairs, so that the fragment and frequency
-    // buffers are named at compile time (NSTEP steps per chunk flip the
-    // fragment half NSTEP times).  The pipeline runs on across range ends.
-    const int64_t nch = T.nch;
-    for (int64_t rs = 0; rs < nch; rs += wa.range_ch) {
-        const int64_t re = rs + wa.range_ch < nch ? rs + wa.range_ch : nch;
-        for (int64_t ch = rs; ch < re; ch += 2) {
-            T.template chunk<0>(ch, F, fq0, fq1);
-            __syncthreads();
-            if (ch + 1 < re) {
-                T.template chunk<NSTEP & 1>(ch + 1, F, fq1, fq0);
-                __syncthreads();
-            }
-        }
-        T.store(wa, rt, ct, wa.accumulate || rs > 0);
-    }
+    // (wave-uniform; both sides pass the same barriers)
+    if (wa.row_off + rt * WT + __builtin_amdgcn_readfirstlane(T.wm) * 32 * MB < T.row_limit(wa))
+        wide_ranges<true>(T, wa, F, fq0, fq1, rt, ct);
+    else
+        wide_ranges<false>(T, wa, F, fq0, fq1, rt, ct);
 }
 
 template <int PREC, int BASIS, int WV>
@@ -550,15 +579,21 @@ __global__ __launch_bounds__(64 * WV) void k_wide(WideArgs wa) {
     __shared__ WideSmem<PREC> sm;
     // XCD-aware order: consecutive tiles (same row panel, successive column
     // tiles) go to the blocks one XCD runs (blocks are dealt to the 8 XCDs
-    // round robin)
+    // round robin); frequency ranges (few tiles, see WideArgs) one after the other
     const int64_t nblk = gridDim.x;
     const int64_t b = blockIdx.x;
     const int64_t per = nblk / 8;
-    const int64_t t = b < 8 * per ? (b % 8) * per + b / 8 : b;
+    int64_t t = b < 8 * per ? (b % 8) * per + b / 8 : b;
     const int64_t ct = t % wa.cts;
-    const int64_t rt = (t / wa.cts) % wa.rts;
-    const int64_t sl = t / (wa.cts * wa.rts);
-    wide_tile_run<PREC, BASIS, WV>(sm, wa, sl, rt, ct);
+    t /= wa.cts;
+    const int64_t rt = t % wa.rts;
+    t /= wa.rts;
+    const int64_t n_sets = wa.s.set1 - wa.s.set0;
+    const int64_t sl = t % n_sets, ks = t / n_sets;
+    const int64_t c0 = wa.ch0 + ks * wa.split_ch;
+    const int64_t c1 = c0 + wa.split_ch < wa.ch1 ? c0 + wa.split_ch : wa.ch1;
+    float* out = wa.s.ksplit > 1 ? (float*)wa.s.phi_part + ks * wa.s.R * wa.s.P : (float*)wa.s.out;
+    wide_tile_run<PREC, BASIS, WV>(sm, wa, sl, rt, ct, c0, c1, out);
 }
 
 // Persistent batch of uneven instances (two-phase form): one block per CU
@@ -586,9 +621,11 @@ __global__ __launch_bounds__(64 * WV) void k_wide_batch(const WideArgs* __restri
         bool piston = false;
         if constexpr (AP) piston = wa.s.apD != nullptr;
         if (piston)
-            wide_tile_run<PREC, BASIS_PISTON, WV>(sm, wa, w.set, w.rt, w.ct);
+            wide_tile_run<PREC, BASIS_PISTON, WV>(sm, wa, w.set, w.rt, w.ct, wa.ch0, wa.ch1,
+                                                  (float*)wa.s.out);
         else
-            wide_tile_run<PREC, BASIS_PHASE, WV>(sm, wa, w.set, w.rt, w.ct);
+            wide_tile_run<PREC, BASIS_PHASE, WV>(sm, wa, w.set, w.rt, w.ct, wa.ch0, wa.ch1,
+                                                 (float*)wa.s.out);
         __syncthreads();
     }
 }
@@ -630,7 +667,7 @@ hipError_t launch_wide_scale(const double* w, int64_t K, int64_t n_sets, double*
 template <int PREC, int BASIS>
 static hipError_t launch_sum_t(const WideArgs& wa, hipStream_t st) {
     constexpr int WV = QRFS_WIDE_WAVES;
-    const int64_t blocks = (wa.s.set1 - wa.s.set0) * wa.rts * wa.cts;
+    const int64_t blocks = (wa.s.set1 - wa.s.set0) * wa.rts * wa.cts * wa.s.ksplit;
     hipLaunchKernelGGL((k_wide<PREC, BASIS, WV>), dim3((unsigned)blocks), dim3(64 * WV), 0, st,
                        wa);
     return hipGetLastError();
