@@ -418,8 +418,9 @@ bool wide_fills(int64_t P, int64_t R, int64_t R_block) {
 }
 
 // Frequencies that the two-phase kernel sums in FP32 before it adds them into
-// the output.  Problems that fill the chip: ctx->range_freqs, and all of K in
-// split-BF16, whose operand rounding is the larger error.  Others come here
+// the output.  Problems that fill the chip, and any when this kernel is asked
+// for: ctx->range_freqs, and all of K in split-BF16, whose operand rounding is
+// the larger error.  Others come here
 // from the fused kernels, which fold their sums every 32 frequencies, and keep
 // those kernels' accuracy: errors against binary64 at K = 1200, 4096, 10007 and
 // 40000 are 2.2, 2.9, 4.0 and 7.4e-7 (BF16x6, one fused launch), here 2.2, 2.4,
@@ -428,7 +429,7 @@ bool wide_fills(int64_t P, int64_t R, int64_t R_block) {
 // 4.3e-7 in ranges of K / 32 within [128, 512] (fused 2.2, 2.8, 3.9, 7.2e-7).
 int64_t wide_range(const qrfs_context* ctx, int precision, int64_t K, int64_t P, int64_t R,
                    int64_t R_block) {
-    if (wide_fills(P, R, R_block))
+    if (ctx->wide_path == 2 || wide_fills(P, R, R_block))
         return precision == QRFS_PREC_SPLIT_BF16 ? K : ctx->range_freqs;
     if (precision == QRFS_PREC_SPLIT_BF16) return ctx->range_freqs < 2048 ? ctx->range_freqs : 2048;
     const bool f16 = precision == QRFS_PREC_FP16X3;
@@ -458,9 +459,9 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int6
     if (P > ((int64_t)1 << 22)) return false;  // 256 rows of output within 32-bit tile offsets
     const int64_t tiles = cdiv(R, R_block) * cdiv(R_block, 256) * cdiv(P, 256);
     const bool full = wide_fills(P, R, R_block);
-    const bool capturing = is_capturing(st);
-    if (ctx->wide_path == 0 && !full && (R_block <= 8 || capturing)) return false;
-    if (capturing) return true;
+    if (ctx->wide_path == 2) return true;  // as asked, in one range whatever the cap
+    if (is_capturing(st)) return full;
+    if (!full && R_block <= 8) return false;
     const double fused = qrfs::store_split(precision, basis, K, R, R_block, P, kSplitCap).us;
     double best = 1e300;
     const double coef = 2.3e-6 * (double)(cdiv(R, R_block) * cdiv(R_block, 256) * 256) * (double)K;
@@ -485,7 +486,7 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int6
             *ksplit = k;
         }
     }
-    if (ctx->wide_path == 2 || full) return true;
+    if (full) return true;
     WidePlan p;
     if (best > 0.9 * fused || wide_plan(ctx, precision, K, P, R, R_block, *ksplit, p) != QRFS_OK)
         return false;
@@ -612,10 +613,15 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
         a.gy = 2.0 * M_PI * grad_u[1];
     }
     int ksplit = 1;
-    if (use_wide(ctx, precision, basis, K, P, R, R_block, coef != nullptr, (hipStream_t)stream,
-                 &ksplit))
+    bool wide = use_wide(ctx, precision, basis, K, P, R, R_block, coef != nullptr,
+                         (hipStream_t)stream, &ksplit);
+    if (wide) {
         s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), ksplit, (hipStream_t)stream);
-    else
+        // no memory for its tiles (nothing is enqueued yet): the fused kernel
+        // takes what it took before such problems came here
+        wide = !(s == QRFS_ERR_OUT_OF_MEMORY && ctx->wide_path == 0 && !wide_fills(P, R, R_block));
+    }
+    if (!wide)
         s = fused_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
     if (s) return s;
     return ok();

@@ -93,6 +93,33 @@ def test_pistons_and_differences(q, ctx, precision, K, R, R_block, P):
     check(host(out), at[0] - at[1], TOL[precision])
 
 
+@pytest.mark.parametrize("precision", [1, 2, 3, 4])
+@pytest.mark.parametrize("K,R,R_block,P", [(2603, 60, 30, 1500), (700, 300, 259, 777),
+                                           (5000, 40, 20, 2100), (1030, 530, 265, 513)])
+def test_mid_size_routes(q, ctx, precision, K, R, R_block, P):
+    """Sizes that the estimated times send to the two-phase kernel in
+    frequency ranges, with tiles of few rows and columns, and back to the
+    fused one by a cap without room for its tiles; phases and tilts."""
+    fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
+    hf = [host(v) for v in (fx, fy, w)]
+    D = np.random.default_rng(P).uniform(0.5, 8.0, P)
+    g = q.Rng(8, 4, 0)
+    rows = np.unique(np.r_[0:3, R // 2:R // 2 + 3, R - 3:R])
+    print(f"mid p{precision} K{K} R{R} Rb{R_block} P{P}", flush=True)
+    ref = oracle.synthesize(*hf, px, py, R, R_block, K=K, seed=8, counter=4)
+    with q.Context(0, workspace_cap=1 << 16) as small:
+        for c in (ctx, small):
+            out = c.synthesize_phase(K, fx, fy, w, dev(px), dev(py), R, R_block, rng=g,
+                                     precision=precision)
+            check(host(out), ref, TOL[precision])
+            out = c.tilt(K, fx, fy, w, dev(px), dev(py), dev(D), dev(0 * D), (1.0, 0.0), R,
+                         R_block, rng=g, precision=precision)
+            sel = slice(0, P, 97)
+            rt = oracle.tilt(*hf, px[sel], py[sel], D[sel], 0 * D[sel], R, R_block, axis=0, K=K,
+                             seed=8, counter=4)
+            check(host(out)[:, sel][rows], rt[rows], TOL[precision])
+
+
 @pytest.mark.parametrize("precision", [0, 1, 4])
 def test_given_coefficients_and_unaligned_output(q, ctx, precision):
     K, R, R_block, P = 1300, 24, 12, 28
@@ -125,10 +152,10 @@ def test_capped_context_needs_no_room(q, precision, cap):
 
 
 @pytest.mark.parametrize("precision", [0, 1, 4])
-def test_captured_calls_hold_no_workspace(q, precision):
+@pytest.mark.parametrize("K,R,R_block,P", [(1500, 40, 20, 60), (2603, 60, 30, 1500)])
+def test_captured_calls_hold_no_workspace(q, precision, K, R, R_block, P):
     """Captured in a graph, with the context's workspace replaced and eager
     work between the replays."""
-    K, R, R_block, P = 1500, 40, 20, 60
     with q.Context(0) as c:
         fx, fy, w, px, py = problem(c, q, K, R, R_block, P)
         dx, dy = dev(px), dev(py)
