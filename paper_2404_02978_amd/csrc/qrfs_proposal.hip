@@ -18,395 +18,519 @@
 namespace qrfs {
 namespace prop {
 
-constexpr int ROWS = 64;   // rows per block of the network kernels
-constexpr int HP = 65;     // padded row stride of the activation tiles
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int ROWS = 48;     // rows of a tile: three 16-row matrix tiles
+constexpr int THREADS = 512; // 8 waves, one per 16 hidden units
+constexpr int ST = 132;      // floats per row of the LDS matrices: 16-byte rows, and the 16 lanes
+                             // of a 16-byte operand read on 16 different groups of 4 banks
 
 struct RowSpec {
     // rows [0, n_sample) are training samples of context ctxlist[q / m];
     // rows [n_sample, n_sample + n_grid) are normaliser grid points of
     // context ctxlist[(q - n_sample) / G]
-    int64_t n_sample, n_grid, m;
-    int G;
+    uint32_t n_sample, n_grid, m, G, n_ctx;
     const int32_t* ctxlist;
     const double* ctx4;     // [n_ctx][4] = D, L0, |B|, theta_B
     const double* ell;      // training rows
     const double* theta;
     const double* h;
-    const float* wgrid;     // dL/do0 of grid rows
-    const double* invH;     // 1 / sum of h over the step's sample rows
+    // per context slot, written by k_grid: sum of h, log Z, the four features
+    // of its geometry; per grid row: exp(o0) / sum of exp(o0)
+    double* Hc;
+    double* logZ;
+    float* feat;
+    double* soft;
     double lmin, Lw;
 };
 
-__device__ __forceinline__ void features(double ell, const double* c, double lmin, double Lw,
-                                         float x[5]) {
-    x[0] = (float)(2.0 * (ell - lmin) / Lw - 1.0);
-    x[1] = (float)(2.0 * c[3] / 3.141592653589793 - 1.0);
-    x[2] = (float)(log(c[0]) / 4.0);
-    x[3] = (float)(log(c[1]) / 4.0 - 1.0);
-    x[4] = (float)(log(c[2]) / 4.0 - 0.5);
+// The network inputs that depend on the context only (x[1..4]).
+__device__ __forceinline__ void context_features(const double* c, float x[4]) {
+    x[0] = (float)(2.0 * c[3] / 3.141592653589793 - 1.0);
+    x[1] = (float)(log(c[0]) / 4.0);
+    x[2] = (float)(log(c[1]) / 4.0 - 1.0);
+    x[3] = (float)(log(c[2]) / 4.0 - 0.5);
+}
+__device__ __forceinline__ float ell_feature(double ell, double lmin, double Lw) {
+    return (float)(2.0 * (ell - lmin) / Lw - 1.0);
+}
+
+// tanh in binary32: below 5/8 an odd polynomial (least squares fit of
+// (tanh(x)/x - 1)/x^2 in x^2, relative error 2e-10 before rounding), above
+// 1 - 2 / (exp(2 |x|) + 1) with the hardware exponential and reciprocal;
+// within 2 units in the last place, at about 20 vector instructions.
+__device__ __forceinline__ float tanh_f32(float x) {
+    const float a = fabsf(x), z = x * x;
+    float p = 2.14280e-3f;
+    p = fmaf(p, z, -8.17709e-3f);
+    p = fmaf(p, z, 2.17005e-2f);
+    p = fmaf(p, z, -5.39467e-2f);
+    p = fmaf(p, z, 0.13333205f);
+    p = fmaf(p, z, -0.33333331f);
+    const float small = fmaf(x * z, p, x);
+    const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * a);
+    const float big = copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f), x);
+    return a < 0.625f ? small : big;
 }
 
 struct NetSmem {
-    float W1[HID * 5];
-    float b1[HID];
-    float W2T[HID][HID];   // W2T[k][i] = W2[i][k]
-    float b2[HID];
+    __attribute__((aligned(16))) float W2[HID * ST];  // row i: weights of hidden unit i
+    __attribute__((aligned(16))) float h1[ROWS * ST]; // activations, row-major
+    __attribute__((aligned(16))) float h2[ROWS * ST]; // layer 2, then dL/d(pre-activation 1)
     float W3[2 * HID];
+    float b2[HID];
     float b3[2];
-    float h1T[HID][HP];    // activations, unit-major, padded
-    float h2T[HID][HP];    // layer-2 activations, then dL/d(pre-activation 2)
-    float x[ROWS][5];
-    float dout[ROWS][2];
-    float red[4][ROWS][2];
+    float x[ROWS][8];
 };
 
-__device__ void load_params(const float* __restrict__ prm, NetSmem& s) {
-    for (int i = threadIdx.x; i < HID * 5; i += blockDim.x) s.W1[i] = prm[OFF_W1 + i];
-    for (int i = threadIdx.x; i < HID; i += blockDim.x) {
-        s.b1[i] = prm[OFF_B1 + i];
-        s.b2[i] = prm[OFF_B2 + i];
+// What a thread keeps of layer 1: the weights of hidden unit t % 128.
+struct Layer1 {
+    float w[5], b;
+};
+
+__device__ __forceinline__ Layer1 load_params(const float* __restrict__ prm, NetSmem& s) {
+    const int t = threadIdx.x;
+    for (int i = t; i < HID * HID / 2; i += THREADS) {  // pairs (OFF_W2 is even)
+        const float2 v = ((const float2*)(prm + OFF_W2))[i];
+        *(float2*)&s.W2[(2 * i / HID) * ST + 2 * i % HID] = v;
     }
-    for (int i = threadIdx.x; i < HID * HID; i += blockDim.x) {
-        const int r = i / HID, k = i % HID;  // W2[r][k]
-        s.W2T[k][r] = prm[OFF_W2 + i];
-    }
-    for (int i = threadIdx.x; i < 2 * HID; i += blockDim.x) s.W3[i] = prm[OFF_W3 + i];
-    if (threadIdx.x < 2) s.b3[threadIdx.x] = prm[OFF_B3 + threadIdx.x];
+    if (t < 2 * HID) s.W3[t] = prm[OFF_W3 + t];
+    if (t < HID) s.b2[t] = prm[OFF_B2 + t];
+    if (t < 2) s.b3[t] = prm[OFF_B3 + t];
+    Layer1 l;
+    const int i = t % HID;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) l.w[j] = prm[OFF_W1 + i * 5 + j];
+    l.b = prm[OFF_B1 + i];
+    return l;
 }
 
-// forward of the block's rows (features already in s.x); thread t owns row
-// r = t % 64 and units [32 g, 32 g + 32), g = t / 64.  Leaves h1T, h2T and
-// writes o[r][2] through `red`.
-__device__ void forward_block(NetSmem& s, float o[2]) {
-    const int r = threadIdx.x % ROWS;
-    const int g = threadIdx.x / ROWS;
-    float xr[5];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) xr[j] = s.x[r][j];
+__device__ __forceinline__ f32x4 mfma_16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Forward of the tile's rows (inputs in s.x, a barrier after them).  Leaves h1
+// and h2 and returns, in thread (r = t / 8 < ROWS, t % 8 = 0), the outputs of row
+// r.  Hidden layer: wave w computes units [16 w, 16 w + 16) of all rows with
+// v_mfma_f32_16x16x4 (lane l: operand row l % 16, contraction values 4 (l / 16)
+// + q of each 16, in steps q; result rows 4 (l / 16) + i, column l % 16): FP32
+// products and sums at twice the rate of the vector ALU, whose one thread per
+// (row, 32 units) this replaces.
+__device__ __forceinline__ void forward_tile(NetSmem& s, const Layer1& l1, float o[2]) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, li = lane & 15, lh = lane >> 4;
+    {
+        const int i = t % HID;
 #pragma unroll 4
-    for (int ii = 0; ii < 32; ++ii) {
-        const int i = 32 * g + ii;
-        float a = s.b1[i];
+        for (int j = 0; j < ROWS / 4; ++j) {
+            const int r = t / HID + 4 * j;
+            float a = l1.b;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) a = fmaf(s.W1[i * 5 + j], xr[j], a);
-        s.h1T[i][r] = tanhf(a);
-    }
-    __syncthreads();
-    float acc[32];
-#pragma unroll
-    for (int ii = 0; ii < 32; ++ii) acc[ii] = s.b2[32 * g + ii];
-    for (int k = 0; k < HID; ++k) {
-        const float hv = s.h1T[k][r];
-#pragma unroll
-        for (int ii = 0; ii < 32; ++ii) acc[ii] = fmaf(s.W2T[k][32 * g + ii], hv, acc[ii]);
-    }
-    float p0 = 0.0f, p1 = 0.0f;
-#pragma unroll
-    for (int ii = 0; ii < 32; ++ii) {
-        const int i = 32 * g + ii;
-        const float hv = tanhf(acc[ii]);
-        s.h2T[i][r] = hv;
-        p0 = fmaf(s.W3[i], hv, p0);
-        p1 = fmaf(s.W3[HID + i], hv, p1);
-    }
-    s.red[g][r][0] = p0;
-    s.red[g][r][1] = p1;
-    __syncthreads();
-    o[0] = s.b3[0] + s.red[0][r][0] + s.red[1][r][0] + s.red[2][r][0] + s.red[3][r][0];
-    o[1] = s.b3[1] + s.red[0][r][1] + s.red[1][r][1] + s.red[2][r][1] + s.red[3][r][1];
-}
-
-__device__ void row_input(const RowSpec& rs, int64_t q, double& ell, const double*& c) {
-    if (q < rs.n_sample) {
-        const int64_t cs = q / rs.m;
-        const int64_t i = (int64_t)rs.ctxlist[cs] * rs.m + q % rs.m;
-        ell = rs.ell[i];
-        c = rs.ctx4 + 4 * rs.ctxlist[cs];
-    } else {
-        const int64_t gq = q - rs.n_sample;
-        const int64_t cs = gq / rs.G;
-        const int j = (int)(gq % rs.G);
-        ell = rs.lmin + (j + 0.5) * rs.Lw / rs.G;
-        c = rs.ctx4 + 4 * rs.ctxlist[cs];
-    }
-}
-
-// Forward only: out[q][2] for rows q < n_rows (ell[q], ctx4[q]) or, with
-// rs given, for the training/grid rows it describes.
-__global__ __launch_bounds__(256) void k_forward(const float* __restrict__ prm, int64_t n_rows,
-                                                 const double* __restrict__ ell,
-                                                 const double* __restrict__ ctx4, double lmin,
-                                                 double Lw, float* __restrict__ out) {
-    __shared__ NetSmem s;
-    load_params(prm, s);
-    const int64_t base = (int64_t)blockIdx.x * ROWS;
-    if (threadIdx.x < ROWS) {
-        const int64_t q = base + threadIdx.x;
-        float x[5] = {0, 0, 0, 0, 0};
-        if (q < n_rows) features(ell[q], ctx4 + 4 * q, lmin, Lw, x);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) s.x[threadIdx.x][j] = x[j];
-    }
-    __syncthreads();
-    float o[2];
-    forward_block(s, o);
-    const int64_t q = base + threadIdx.x % ROWS;
-    if (threadIdx.x < ROWS && q < n_rows) {
-        out[2 * q] = o[0];
-        out[2 * q + 1] = o[1];
-    }
-}
-
-// Grid rows of a step: o0 for every (context slot, grid point).
-__global__ __launch_bounds__(256) void k_forward_grid(const float* __restrict__ prm,
-                                                      RowSpec rs, float* __restrict__ og) {
-    __shared__ NetSmem s;
-    load_params(prm, s);
-    const int64_t base = (int64_t)blockIdx.x * ROWS;
-    if (threadIdx.x < ROWS) {
-        const int64_t gq = base + threadIdx.x;
-        float x[5] = {0, 0, 0, 0, 0};
-        if (gq < rs.n_grid) {
-            double ell;
-            const double* c;
-            row_input(rs, rs.n_sample + gq, ell, c);
-            features(ell, c, rs.lmin, rs.Lw, x);
+            for (int q = 0; q < 5; ++q) a = fmaf(l1.w[q], s.x[r][q], a);
+            s.h1[r * ST + i] = tanh_f32(a);
         }
+    }
+    __syncthreads();
+    f32x4 acc[3] = {};
+    const int u = 16 * wave + li;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) s.x[threadIdx.x][j] = x[j];
+    for (int g = 0; g < HID / 16; ++g) {
+        const f32x4 B = *(const f32x4*)&s.W2[u * ST + 16 * g + 4 * lh];
+        f32x4 A[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+            A[m] = *(const f32x4*)&s.h1[(16 * m + li) * ST + 16 * g + 4 * lh];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) acc[m] = mfma_16(A[m][q], B[q], acc[m]);
     }
+    const float b2 = s.b2[u];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            s.h2[(16 * m + 4 * lh + i) * ST + u] = tanh_f32(acc[m][i] + b2);
     __syncthreads();
-    float o[2];
-    forward_block(s, o);
-    const int64_t gq = base + threadIdx.x % ROWS;
-    if (threadIdx.x < ROWS && gq < rs.n_grid) og[gq] = o[0];
-}
-
-// H_c: sum of h over the sample rows of context slot blockIdx.x (fixed order).
-__global__ __launch_bounds__(256) void k_hsum(RowSpec rs, double* __restrict__ Hc) {
-    __shared__ double r[256];
-    const int64_t cs = blockIdx.x;
-    const int64_t base = (int64_t)rs.ctxlist[cs] * rs.m;
-    double a = 0.0;
-    for (int64_t i = threadIdx.x; i < rs.m; i += 256) a += rs.h[base + i];
-    r[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) r[threadIdx.x] += r[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) Hc[cs] = r[0];
-}
-
-// One block: H = sum H_c, 1/H, per context logZ_c = log(sum_j exp(o0_j) Lw/G),
-// dL/do0 of the grid rows (H_c/H) softmax_j, and the loss constant
-// sum_c (H_c/H) logZ_c.
-__global__ __launch_bounds__(256) void k_grid_prep(int64_t n_ctx, int G, double Lw,
-                                                   const double* __restrict__ Hc,
-                                                   const float* __restrict__ og,
-                                                   float* __restrict__ wgrid,
-                                                   double* __restrict__ invH,
-                                                   double* __restrict__ loss_const) {
-    __shared__ double s_invH;
-    __shared__ double s_lz[1024];
-    if (threadIdx.x == 0) {
-        double H = 0.0;
-        for (int64_t c = 0; c < n_ctx; ++c) H += Hc[c];
-        s_invH = H > 0.0 ? 1.0 / H : 0.0;
-        *invH = s_invH;
-    }
-    __syncthreads();
-    for (int64_t c = threadIdx.x; c < n_ctx; c += 256) {
-        const float* o = og + c * G;
-        double mx = -1e300;
-        for (int j = 0; j < G; ++j) mx = fmax(mx, (double)o[j]);
-        double se = 0.0;
-        for (int j = 0; j < G; ++j) se += exp((double)o[j] - mx);
-        const double wc = Hc[c] * s_invH;
-        for (int j = 0; j < G; ++j) wgrid[c * G + j] = (float)(wc * exp((double)o[j] - mx) / se);
-        if (c < 1024) s_lz[c] = wc * (mx + log(se * Lw / G));
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double L = 0.0;
-        for (int64_t c = 0; c < n_ctx && c < 1024; ++c) L += s_lz[c];
-        *loss_const = L;
-    }
-}
-
-// Fused forward + backward over the step's rows; writes this block's
-// gradient contribution gpart[block][NPARAM] and loss contribution.
-__global__ __launch_bounds__(256) void k_train(const float* __restrict__ prm, RowSpec rs,
-                                               float* __restrict__ gpart,
-                                               double* __restrict__ lpart) {
-    __shared__ NetSmem s;
-    __shared__ float s_wg[ROWS], s_wa[ROWS], s_C[ROWS], s_lw[ROWS];
-    __shared__ double s_loss[ROWS];
-    load_params(prm, s);
-    const int64_t n_rows = rs.n_sample + rs.n_grid;
-    const int64_t base = (int64_t)blockIdx.x * ROWS;
-    if (threadIdx.x < ROWS) {
-        const int64_t q = base + threadIdx.x;
-        float x[5] = {0, 0, 0, 0, 0};
-        float wg = 0.0f, wa = 0.0f, C = 0.0f, lw = 0.0f;
-        if (q < n_rows) {
-            double ell;
-            const double* c;
-            row_input(rs, q, ell, c);
-            features(ell, c, rs.lmin, rs.Lw, x);
-            if (q < rs.n_sample) {
-                const int64_t cs = q / rs.m;
-                const int64_t i = (int64_t)rs.ctxlist[cs] * rs.m + q % rs.m;
-                const double wi = -rs.h[i] * (*rs.invH);
-                wg = (float)wi;
-                wa = (float)wi;
-                lw = (float)wi;
-                C = (float)cos(2.0 * (rs.theta[i] - c[3]));
-            } else {
-                wg = rs.wgrid[q - rs.n_sample];
+    // outputs: 8 threads per row, 16 units each, added in a fixed tree
+    const int r = t >> 3, part = t & 7;
+    float p0 = 0.0f, p1 = 0.0f;
+    if (r < ROWS) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 16 * part + 4 * j;
+            const f32x4 hv = *(const f32x4*)&s.h2[r * ST + k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                p0 = fmaf(s.W3[k + e], hv[e], p0);
+                p1 = fmaf(s.W3[HID + k + e], hv[e], p1);
             }
         }
+    }
 #pragma unroll
-        for (int j = 0; j < 5; ++j) s.x[threadIdx.x][j] = x[j];
-        s_wg[threadIdx.x] = wg;
-        s_wa[threadIdx.x] = wa;
-        s_C[threadIdx.x] = C;
-        s_lw[threadIdx.x] = lw;
+    for (int off = 1; off < 8; off <<= 1) {
+        p0 += __shfl_xor(p0, off);
+        p1 += __shfl_xor(p1, off);
     }
-    __syncthreads();
-    float o[2];
-    forward_block(s, o);
-    const int r = threadIdx.x % ROWS;
-    const int g = threadIdx.x / ROWS;
-    if (g == 0) {
-        const float ta = tanhf(o[1]);
-        const float alpha = 0.9f * ta;
-        const float C = s_C[r];
-        s.dout[r][0] = s_wg[r];
-        s.dout[r][1] = s_wa[r] * C / (1.0f + alpha * C) * 0.9f * (1.0f - ta * ta);
-        s_loss[r] = (double)s_lw[r] * ((double)o[0] + log(1.0 + (double)alpha * (double)C));
-    }
-    __syncthreads();
-    float* gp = gpart + (int64_t)blockIdx.x * NPARAM;
-    // layer 3: W3[c][i], b3
-    {
-        const int c = threadIdx.x / HID, i = threadIdx.x % HID;
-        float a = 0.0f;
-        for (int rr = 0; rr < ROWS; ++rr) a = fmaf(s.dout[rr][c], s.h2T[i][rr], a);
-        gp[OFF_W3 + c * HID + i] = a;
-        if (threadIdx.x < 2) {
-            float b = 0.0f;
-            for (int rr = 0; rr < ROWS; ++rr) b += s.dout[rr][threadIdx.x];
-            gp[OFF_B3 + threadIdx.x] = b;
+    o[0] = s.b3[0] + p0;
+    o[1] = s.b3[1] + p1;
+}
+
+// Forward only: out[q][2] for rows q < n_rows (ell[q], ctx4[q]).  Blocks walk
+// tiles, so the parameters are loaded once per block.
+__global__ __launch_bounds__(THREADS) void k_forward(const float* __restrict__ prm, int64_t n_rows,
+                                                     const double* __restrict__ ell,
+                                                     const double* __restrict__ ctx4, double lmin,
+                                                     double Lw, float* __restrict__ out) {
+    __shared__ NetSmem s;
+    const Layer1 l1 = load_params(prm, s);
+    const int64_t n_tiles = (n_rows + ROWS - 1) / ROWS;
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t base = tile * ROWS;
+        if (threadIdx.x < ROWS) {
+            const int64_t q = base + threadIdx.x;
+            float x[5] = {0, 0, 0, 0, 0};
+            if (q < n_rows) {
+                x[0] = ell_feature(ell[q], lmin, Lw);
+                context_features(ctx4 + 4 * q, x + 1);
+            }
+#pragma unroll
+            for (int j = 0; j < 5; ++j) s.x[threadIdx.x][j] = x[j];
         }
-    }
-    __syncthreads();
-    // dL/d(pre-activation 2), overwriting h2T
-#pragma unroll 4
-    for (int ii = 0; ii < 32; ++ii) {
-        const int i = 32 * g + ii;
-        const float hv = s.h2T[i][r];
-        const float d = s.dout[r][0] * s.W3[i] + s.dout[r][1] * s.W3[HID + i];
-        s.h2T[i][r] = d * (1.0f - hv * hv);
-    }
-    __syncthreads();
-    // layer 2: W2[i][k] += sum_r d2[r][i] h1[r][k]; 8 x 8 tile per thread
-    {
-        const int i0 = (threadIdx.x / 16) * 8, k0 = (threadIdx.x % 16) * 8;
-        float acc[8][8];
-#pragma unroll
-        for (int a = 0; a < 8; ++a)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] = 0.0f;
-        for (int rr = 0; rr < ROWS; ++rr) {
-            float dv[8], hv[8];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) dv[a] = s.h2T[i0 + a][rr];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) hv[b] = s.h1T[k0 + b][rr];
-#pragma unroll
-            for (int a = 0; a < 8; ++a)
-#pragma unroll
-                for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(dv[a], hv[b], acc[a][b]);
+        __syncthreads();
+        float o[2];
+        forward_tile(s, l1, o);
+        const int64_t q = base + (threadIdx.x >> 3);
+        if ((threadIdx.x & 7) == 0 && threadIdx.x < 8 * ROWS && q < n_rows) {
+            out[2 * q] = o[0];
+            out[2 * q + 1] = o[1];
         }
-#pragma unroll
-        for (int a = 0; a < 8; ++a)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) gp[OFF_W2 + (i0 + a) * HID + k0 + b] = acc[a][b];
-        if (threadIdx.x < HID) {
-            float b = 0.0f;
-            for (int rr = 0; rr < ROWS; ++rr) b += s.h2T[threadIdx.x][rr];
-            gp[OFF_B2 + threadIdx.x] = b;
-        }
-    }
-    // dL/d(pre-activation 1): d1[r][k] = (sum_i W2[i][k] d2[r][i]) (1 - h1^2)
-    float d1[32];
-#pragma unroll
-    for (int kk = 0; kk < 32; ++kk) d1[kk] = 0.0f;
-    for (int i = 0; i < HID; ++i) {
-        const float dv = s.h2T[i][r];
-#pragma unroll
-        for (int kk = 0; kk < 32; ++kk) d1[kk] = fmaf(s.W2T[32 * g + kk][i], dv, d1[kk]);
-    }
-    __syncthreads();  // every thread done reading h1T / h2T as layer-2 inputs
-#pragma unroll
-    for (int kk = 0; kk < 32; ++kk) {
-        const int k = 32 * g + kk;
-        const float hv = s.h1T[k][r];
-        s.h2T[k][r] = d1[kk] * (1.0f - hv * hv);  // reuse h2T for d1
-    }
-    __syncthreads();
-    // layer 1: W1[k][j] += sum_r d1[r][k] x[r][j]; b1
-    for (int e = threadIdx.x; e < HID * 6; e += blockDim.x) {
-        const int k = e / 6, j = e % 6;
-        float a = 0.0f;
-        if (j < 5) {
-            for (int rr = 0; rr < ROWS; ++rr) a = fmaf(s.h2T[k][rr], s.x[rr][j], a);
-            gp[OFF_W1 + k * 5 + j] = a;
-        } else {
-            for (int rr = 0; rr < ROWS; ++rr) a += s.h2T[k][rr];
-            gp[OFF_B1 + k] = a;
-        }
-    }
-    if (threadIdx.x == 0) {
-        double L = 0.0;
-        for (int rr = 0; rr < ROWS; ++rr) L += s_loss[rr];
-        lpart[blockIdx.x] = L;
+        // (the barrier after the next inputs separates this tile's reads of h1, h2)
+        __syncthreads();
     }
 }
 
-// grad[p] = sum over blocks (fixed order); loss = sum lpart + loss_const.
-__global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ gpart,
-                                                     int64_t n_blocks,
-                                                     const double* __restrict__ lpart,
-                                                     const double* __restrict__ loss_const,
-                                                     float* __restrict__ grad,
-                                                     double* __restrict__ loss) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < NPARAM) {
+// Per context slot c of a step.  Block c: the grid points' o0, log Z =
+// log(sum_j exp(o0_j) Lw / G), the softmax over the grid and the context's
+// features; block n_ctx + c: H_c, the sum of h over its sample rows.  All in a
+// fixed order.
+__global__ __launch_bounds__(THREADS) void k_grid(const float* __restrict__ prm, RowSpec rs,
+                                                  float* __restrict__ og) {
+    __shared__ NetSmem s;
+    __shared__ double red[THREADS];
+    const int t = threadIdx.x;
+    if (blockIdx.x >= rs.n_ctx) {
+        const uint32_t c = blockIdx.x - rs.n_ctx;
+        const double* h = rs.h + (int64_t)rs.ctxlist[c] * rs.m;
         double a = 0.0;
-        for (int64_t b = 0; b < n_blocks; ++b) a += (double)gpart[b * NPARAM + p];
-        grad[p] = (float)a;
+        uint32_t i = t;
+        for (; i + 3 * THREADS < rs.m; i += 4 * THREADS) {
+            double v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = h[i + e * THREADS];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a += v[e];
+        }
+        for (; i < rs.m; i += THREADS) a += h[i];
+        red[t] = a;
+        __syncthreads();
+        for (int w = THREADS / 2; w > 0; w >>= 1) {
+            if (t < w) red[t] += red[t + w];
+            __syncthreads();
+        }
+        if (t == 0) rs.Hc[c] = red[0];
+        return;
     }
-    if (p == 0 && loss) {
-        double L = *loss_const;
-        for (int64_t b = 0; b < n_blocks; ++b) L += lpart[b];
-        *loss = L;
+    const uint32_t c = blockIdx.x;
+    const Layer1 l1 = load_params(prm, s);
+    float f[4];
+    context_features(rs.ctx4 + 4 * (int64_t)rs.ctxlist[c], f);
+    if (t == 0)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rs.feat[4 * c + j] = f[j];
+    float* o = og + (size_t)c * rs.G;
+    for (uint32_t g0 = 0; g0 < rs.G; g0 += ROWS) {
+        if (t < ROWS) {
+            const uint32_t j = g0 + t;
+            s.x[t][0] = j < rs.G ? ell_feature(rs.lmin + (j + 0.5) * rs.Lw / rs.G, rs.lmin, rs.Lw)
+                                 : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s.x[t][1 + e] = f[e];
+        }
+        __syncthreads();
+        float ov[2];
+        forward_tile(s, l1, ov);
+        const uint32_t j = g0 + (t >> 3);
+        if ((t & 7) == 0 && t < 8 * ROWS && j < rs.G) o[j] = ov[0];
+        __syncthreads();
     }
+    // this block's o0 back from memory (written by itself, before a barrier)
+    __threadfence_block();
+    double mx = -1e300;
+    for (uint32_t j = t; j < rs.G; j += THREADS) mx = fmax(mx, (double)o[j]);
+    red[t] = mx;
+    __syncthreads();
+    for (int w = THREADS / 2; w > 0; w >>= 1) {
+        if (t < w) red[t] = fmax(red[t], red[t + w]);
+        __syncthreads();
+    }
+    mx = red[0];
+    __syncthreads();
+    double se = 0.0;
+    for (uint32_t j = t; j < rs.G; j += THREADS) se += exp((double)o[j] - mx);
+    red[t] = se;
+    __syncthreads();
+    for (int w = THREADS / 2; w > 0; w >>= 1) {
+        if (t < w) red[t] += red[t + w];
+        __syncthreads();
+    }
+    se = red[0];
+    for (uint32_t j = t; j < rs.G; j += THREADS)
+        rs.soft[(size_t)c * rs.G + j] = exp((double)o[j] - mx) / se;
+    if (t == 0) rs.logZ[c] = mx + log(se * rs.Lw / rs.G);
 }
 
-// Adam (Kingma & Ba, 2015) with bias correction, step t >= 1.
-__global__ void k_adam(float* __restrict__ prm, float* __restrict__ m1, float* __restrict__ m2,
-                       const float* __restrict__ grad, float lr, float b1, float b2, float eps,
-                       float c1, float c2) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NPARAM) return;
-    const float g = grad[p];
-    const float a = b1 * m1[p] + (1.0f - b1) * g;
-    const float v = b2 * m2[p] + (1.0f - b2) * g * g;
-    m1[p] = a;
-    m2[p] = v;
-    prm[p] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
+// 1 / sum of H_c (0 if the sum is not positive), in a fixed order.
+__device__ __forceinline__ double inverse_H(const RowSpec& rs) {
+    double H = 0.0;
+    for (uint32_t c = 0; c < rs.n_ctx; ++c) H += rs.Hc[c];
+    return H > 0.0 ? 1.0 / H : 0.0;
+}
+
+// Fused forward + backward over rows [block * chunk, (block + 1) * chunk) of
+// the step in tiles of 48; the block's gradient stays in registers over its
+// tiles and goes to gpart[block][NPARAM] once, with its loss.  One block per
+// compute unit (its parameters and activations take 145 KB of LDS).  Matrix
+// work per row: 3 x 2 x 128^2 flops (hidden layer forward, its weight gradient
+// and the gradient of layer 1's activations), all on v_mfma_f32_16x16x4: 23 us
+// for 33792 rows at its rate, tanh and the small layers beside them.
+__global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm, RowSpec rs,
+                                                   uint32_t chunk, float* __restrict__ gpart,
+                                                   double* __restrict__ lpart) {
+    __shared__ NetSmem s;
+    __shared__ __attribute__((aligned(16))) float d2[ROWS * ST];  // dL/d(pre-activation 2)
+    __shared__ float dout[ROWS][2];
+    __shared__ double s_w[ROWS], s_C[ROWS], s_loss[ROWS];
+    __shared__ double s_invH;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, li = lane & 15, lh = lane >> 4;
+    const Layer1 l1 = load_params(prm, s);
+    if (t == 0) s_invH = inverse_H(rs);
+    __syncthreads();
+    const double invH = s_invH;
+    const uint32_t n_rows = rs.n_sample + rs.n_grid;
+    const uint32_t r0 = blockIdx.x * chunk;
+    const uint32_t r1 = r0 + chunk < n_rows ? r0 + chunk : n_rows;
+    const int u0 = (wave & 3) * 32, k0 = (wave >> 2) * 64;  // tile of the W2 gradient
+    f32x4 gW2[2][4] = {};
+    float gA = 0.0f, gB = 0.0f, gC = 0.0f, gC1 = 0.0f;  // of the small layers, see below
+    double loss = 0.0;
+
+    for (uint32_t base = r0; base < r1; base += ROWS) {
+        if (t < ROWS) {
+            const uint32_t q = base + t;
+            float x[5] = {0, 0, 0, 0, 0};
+            double w = 0.0, C = 0.0;
+            if (q < r1) {
+                const bool sample = q < rs.n_sample;
+                const uint32_t n = sample ? q : q - rs.n_sample, per = sample ? rs.m : rs.G;
+                const uint32_t cs = n / per, j = n % per;
+                double ell;
+                if (sample) {
+                    const int64_t i = (int64_t)rs.ctxlist[cs] * rs.m + j;
+                    ell = rs.ell[i];
+                    w = -rs.h[i] * invH;
+                    C = cos(2.0 * (rs.theta[i] - rs.ctx4[4 * (int64_t)rs.ctxlist[cs] + 3]));
+                } else {
+                    ell = rs.lmin + (j + 0.5) * rs.Lw / rs.G;
+                    w = rs.Hc[cs] * invH * rs.soft[n];  // dL/do0 of the normaliser
+                    C = 2.0;                            // marks a grid row
+                }
+                x[0] = ell_feature(ell, rs.lmin, rs.Lw);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[1 + e] = rs.feat[4 * cs + e];
+            }
+#pragma unroll
+            for (int j = 0; j < 5; ++j) s.x[t][j] = x[j];
+            s_w[t] = w;
+            s_C[t] = C;
+        }
+        __syncthreads();
+        float o[2];
+        forward_tile(s, l1, o);
+        if ((t & 7) == 0 && t < 8 * ROWS) {
+            const int r = t >> 3;
+            const bool sample = !(s_C[r] > 1.5);
+            const float wg = (float)s_w[r], C = sample ? (float)s_C[r] : 0.0f;
+            const float ta = tanh_f32(o[1]);
+            const float alpha = 0.9f * ta;
+            dout[r][0] = wg;
+            dout[r][1] = sample ? wg * C / (1.0f + alpha * C) * 0.9f * (1.0f - ta * ta) : 0.0f;
+            s_loss[r] =
+                sample ? (double)wg * ((double)o[0] + log(1.0 + (double)alpha * (double)C)) : 0.0;
+        }
+        __syncthreads();
+        // layer 3: thread c HID + i: W3[c][i]; threads 256, 257: b3
+        if (t < 2 * HID) {
+            const int c = t / HID, i = t % HID;
+#pragma unroll 8
+            for (int r = 0; r < ROWS; ++r) gA = fmaf(dout[r][c], s.h2[r * ST + i], gA);
+        } else if (t < 2 * HID + 2) {
+            for (int r = 0; r < ROWS; ++r) gA += dout[r][t - 2 * HID];
+        } else if (t == THREADS - 1) {
+            for (int r = 0; r < ROWS; ++r) loss += s_loss[r];
+        }
+        {
+            const int i = t % HID;
+            const float w0 = s.W3[i], w1 = s.W3[HID + i];
+#pragma unroll 4
+            for (int j = 0; j < ROWS / 4; ++j) {
+                const int r = t / HID + 4 * j;
+                const float hv = s.h2[r * ST + i];
+                d2[r * ST + i] = (dout[r][0] * w0 + dout[r][1] * w1) * (1.0f - hv * hv);
+            }
+        }
+        __syncthreads();
+        // hidden layer's weights: gradient [u][k] = sum_r d2[r][u] h1[r][k], the
+        // wave's 32 x 64 of it
+#pragma unroll 4
+        for (int g = 0; g < ROWS / 4; ++g) {
+            const int r = 4 * g + lh;
+            float A[2], B[4];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) A[e] = d2[r * ST + u0 + 16 * e + li];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) B[e] = s.h1[r * ST + k0 + 16 * e + li];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int f = 0; f < 4; ++f) gW2[e][f] = mfma_16(A[e], B[f], gW2[e][f]);
+        }
+        if (t < HID) {
+#pragma unroll 8
+            for (int r = 0; r < ROWS; ++r) gB += d2[r * ST + t];  // b2
+        }
+        // dL/d(pre-activation 1): sum_u d2[r][u] W2[u][k], the wave's 16 k
+        {
+            f32x4 acc[3] = {};
+            const int k = 16 * wave + li;
+#pragma unroll
+            for (int g = 0; g < HID / 16; ++g) {
+                f32x4 A[3];
+#pragma unroll
+                for (int m = 0; m < 3; ++m)
+                    A[m] = *(const f32x4*)&d2[(16 * m + li) * ST + 16 * g + 4 * lh];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float B = s.W2[(16 * g + 4 * lh + q) * ST + k];
+#pragma unroll
+                    for (int m = 0; m < 3; ++m) acc[m] = mfma_16(A[m][q], B, acc[m]);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 16 * m + 4 * lh + i;
+                    const float hv = s.h1[r * ST + k];
+                    s.h2[r * ST + k] = acc[m][i] * (1.0f - hv * hv);
+                }
+        }
+        __syncthreads();
+        // layer 1: threads (k, 0): W1[k][0], W1[k][1]; (k, 1): W1[k][2], W1[k][3];
+        // (k, 2): W1[k][4]; (k, 3): b1[k]
+        {
+            const int k = t % HID, part = t / HID;
+#pragma unroll 4
+            for (int r = 0; r < ROWS; ++r) {
+                const float d = s.h2[r * ST + k];
+                gC = fmaf(d, part < 3 ? s.x[r][2 * part] : 1.0f, gC);
+                if (part < 2) gC1 = fmaf(d, s.x[r][2 * part + 1], gC1);
+            }
+        }
+        __syncthreads();
+    }
+    float* gp = gpart + (int64_t)blockIdx.x * NPARAM;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                gp[OFF_W2 + (u0 + 16 * e + 4 * lh + i) * HID + k0 + 16 * f + li] = gW2[e][f][i];
+    if (t < 2 * HID) gp[OFF_W3 + t] = gA;
+    else if (t < 2 * HID + 2) gp[OFF_B3 + t - 2 * HID] = gA;
+    if (t < HID) gp[OFF_B2 + t] = gB;
+    const int k = t % HID, part = t / HID;
+    if (part < 2) {
+        gp[OFF_W1 + k * 5 + 2 * part] = gC;
+        gp[OFF_W1 + k * 5 + 2 * part + 1] = gC1;
+    } else if (part == 2) {
+        gp[OFF_W1 + k * 5 + 4] = gC;
+    } else {
+        gp[OFF_B1 + k] = gC;
+    }
+    if (t == THREADS - 1) lpart[blockIdx.x] = loss;
+}
+
+// grad[p] = sum over blocks (fixed order, binary64); loss = sum of lpart plus
+// sum_c (H_c / H) log Z_c; with ADAM (Kingma & Ba, 2015, bias correction, step
+// t >= 1) the update of parameter p follows at once.  256 threads share 32
+// parameters: 8 groups of blocks each, 8 loads in flight per thread (one thread
+// per parameter over all blocks waited on every load: 149 us for 528 blocks).
+struct AdamArgs {
+    float* m1;
+    float* m2;
+    float lr, b1, b2, eps, c1, c2;
+};
+constexpr int GR_P = 32;
+
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ gpart, int n_blocks,
+                                                     const double* __restrict__ lpart, RowSpec rs,
+                                                     float* __restrict__ grad,
+                                                     double* __restrict__ loss,
+                                                     float* __restrict__ prm, AdamArgs ad) {
+    __shared__ double red[8][GR_P];
+    const int t = threadIdx.x, pl = t % GR_P, g = t / GR_P;
+    const int p = blockIdx.x * GR_P + pl;
+    double a = 0.0;
+    if (p < NPARAM) {
+        int b = g;
+        for (; b + 7 * 8 < n_blocks; b += 64) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = gpart[(int64_t)(b + 8 * e) * NPARAM + p];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a += (double)v[e];
+        }
+        for (; b < n_blocks; b += 8) a += (double)gpart[(int64_t)b * NPARAM + p];
+    }
+    red[g][pl] = a;
+    __syncthreads();
+    if (g == 0 && p < NPARAM) {
+        for (int e = 1; e < 8; ++e) a += red[e][pl];
+        const float gr = (float)a;
+        grad[p] = gr;
+        if constexpr (ADAM) {
+            const float m = ad.b1 * ad.m1[p] + (1.0f - ad.b1) * gr;
+            const float v = ad.b2 * ad.m2[p] + (1.0f - ad.b2) * gr * gr;
+            ad.m1[p] = m;
+            ad.m2[p] = v;
+            prm[p] -= ad.lr * (m / ad.c1) / (sqrtf(v / ad.c2) + ad.eps);
+        }
+    }
+    if (loss && blockIdx.x == 0) {
+        // one wave: the blocks' shares and the contexts' constants, strided by
+        // lane, then a fixed tree
+        if (t < 64) {
+            const double invH = inverse_H(rs);
+            double L = 0.0;
+            for (int b = t; b < n_blocks; b += 64) L += lpart[b];
+            for (uint32_t c = t; c < rs.n_ctx; c += 64) L += rs.Hc[c] * invH * rs.logZ[c];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off);
+            if (t == 0) *loss = L;
+        }
+    }
 }
 
 // Training rows: context c, row r uses R2 point index + 1 + c m + r;
@@ -529,10 +653,21 @@ __global__ __launch_bounds__(256) void k_sample_learned(
 // ----------------------------------------------------------- launchers ----
 static inline int64_t cdivp(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// compute units of the current device (blocks of the persistent kernels)
+static int prop_units() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+        n = 256;
+    return n;
+}
+
 hipError_t prop_launch_forward(const float* prm, int64_t n, const double* ell, const double* ctx4,
                                double lmin, double Lw, float* out, hipStream_t st) {
-    hipLaunchKernelGGL(prop::k_forward, dim3((unsigned)cdivp(n, prop::ROWS)), dim3(256), 0, st,
-                       prm, n, ell, ctx4, lmin, Lw, out);
+    const int64_t tiles = cdivp(n, prop::ROWS);
+    const int units = prop_units();
+    hipLaunchKernelGGL(prop::k_forward, dim3((unsigned)(tiles < units ? tiles : units)),
+                       dim3(prop::THREADS), 0, st, prm, n, ell, ctx4, lmin, Lw, out);
     return hipGetLastError();
 }
 
@@ -546,53 +681,69 @@ hipError_t prop_launch_rows(uint64_t s0x, uint64_t s0y, uint64_t index, int64_t 
     return hipGetLastError();
 }
 
-size_t prop_step_scratch_floats(int64_t n_sample, int64_t n_grid) {
-    return (size_t)cdivp(n_sample + n_grid, prop::ROWS) * NPARAM;
+// Rows per block of a step's n rows: one block per compute unit, whole
+// 16-row matrix tiles.
+static int64_t step_chunk(int64_t n, int units) {
+    const int64_t chunk = cdivp(n, units);
+    return chunk <= prop::ROWS ? prop::ROWS : cdivp(chunk, 16) * 16;
 }
 
-hipError_t prop_launch_loss_grad(const float* prm, int64_t n_ctx, int64_t m, const int32_t* ctxlist,
-                                 const double* ctx4, const double* ell, const double* theta,
-                                 const double* h, int G, double lmin, double Lw, float* og,
-                                 float* wgrid, double* dscratch, float* gpart, float* grad,
-                                 double* loss, hipStream_t st) {
-    // dscratch: [n_ctx] Hc, invH, loss_const, [n_blocks] lpart
+StepSizes prop_step_sizes(int64_t n_ctx, int64_t m, int64_t G) {
+    StepSizes z;
+    const int64_t n = n_ctx * (m + G);
+    z.chunk = step_chunk(n, prop_units());
+    z.blocks = cdivp(n, z.chunk);
+    z.doubles = (size_t)(2 * n_ctx + n_ctx * G + z.blocks);
+    z.floats = (size_t)(4 * n_ctx + n_ctx * G);
+    return z;
+}
+
+hipError_t prop_launch_step(float* prm, const StepSizes& z, int64_t n_ctx, int64_t m,
+                            const int32_t* ctxlist, const double* ctx4, const double* ell,
+                            const double* theta, const double* h, int G, double lmin, double Lw,
+                            double* dscratch, float* fscratch, float* gpart, float* grad,
+                            double* loss, float* m1, float* m2, float lr, int64_t t,
+                            hipStream_t st) {
     prop::RowSpec rs;
-    rs.n_sample = n_ctx * m;
-    rs.n_grid = n_ctx * G;
-    rs.m = m;
-    rs.G = G;
+    rs.n_sample = (uint32_t)(n_ctx * m);
+    rs.n_grid = (uint32_t)(n_ctx * G);
+    rs.m = (uint32_t)m;
+    rs.G = (uint32_t)G;
+    rs.n_ctx = (uint32_t)n_ctx;
     rs.ctxlist = ctxlist;
     rs.ctx4 = ctx4;
     rs.ell = ell;
     rs.theta = theta;
     rs.h = h;
-    rs.wgrid = wgrid;
+    rs.Hc = dscratch;
+    rs.logZ = dscratch + n_ctx;
+    rs.soft = dscratch + 2 * n_ctx;
+    double* lpart = rs.soft + n_ctx * G;
+    rs.feat = fscratch;
+    float* og = fscratch + 4 * n_ctx;
     rs.lmin = lmin;
     rs.Lw = Lw;
-    double* Hc = dscratch;
-    double* invH = dscratch + n_ctx;
-    double* lconst = invH + 1;
-    double* lpart = lconst + 1;
-    rs.invH = invH;
-    const int64_t n_blocks = cdivp(rs.n_sample + rs.n_grid, prop::ROWS);
-    hipLaunchKernelGGL(prop::k_forward_grid, dim3((unsigned)cdivp(rs.n_grid, prop::ROWS)),
-                       dim3(256), 0, st, prm, rs, og);
-    hipLaunchKernelGGL(prop::k_hsum, dim3((unsigned)n_ctx), dim3(256), 0, st, rs, Hc);
-    hipLaunchKernelGGL(prop::k_grid_prep, dim3(1), dim3(256), 0, st, n_ctx, G, Lw, Hc, og, wgrid,
-                       invH, lconst);
-    hipLaunchKernelGGL(prop::k_train, dim3((unsigned)n_blocks), dim3(256), 0, st, prm, rs, gpart,
-                       lpart);
-    hipLaunchKernelGGL(prop::k_grad_reduce, dim3((unsigned)cdivp(NPARAM, 256)), dim3(256), 0, st,
-                       gpart, n_blocks, lpart, lconst, grad, loss);
-    return hipGetLastError();
-}
-
-hipError_t prop_launch_adam(float* prm, float* m1, float* m2, const float* grad, float lr,
-                            int64_t t, hipStream_t st) {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    hipLaunchKernelGGL(prop::k_adam, dim3((unsigned)cdivp(NPARAM, 256)), dim3(256), 0, st, prm, m1,
-                       m2, grad, lr, b1, b2, eps, c1, c2);
+    hipLaunchKernelGGL(prop::k_grid, dim3((unsigned)(2 * n_ctx)), dim3(prop::THREADS), 0, st, prm,
+                       rs, og);
+    hipLaunchKernelGGL(prop::k_train, dim3((unsigned)z.blocks), dim3(prop::THREADS), 0, st, prm, rs,
+                       (uint32_t)z.chunk, gpart, lpart);
+    prop::AdamArgs ad{};
+    const dim3 g((unsigned)cdivp(NPARAM, prop::GR_P));
+    if (m1) {
+        ad.m1 = m1;
+        ad.m2 = m2;
+        ad.lr = lr;
+        ad.b1 = 0.9f;
+        ad.b2 = 0.999f;
+        ad.eps = 1e-8f;
+        ad.c1 = 1.0f - powf(ad.b1, (float)t);
+        ad.c2 = 1.0f - powf(ad.b2, (float)t);
+        hipLaunchKernelGGL(prop::k_grad_reduce<true>, g, dim3(256), 0, st, gpart, (int)z.blocks,
+                           lpart, rs, grad, loss, prm, ad);
+    } else {
+        hipLaunchKernelGGL(prop::k_grad_reduce<false>, g, dim3(256), 0, st, gpart, (int)z.blocks,
+                           lpart, rs, grad, loss, prm, ad);
+    }
     return hipGetLastError();
 }
 

@@ -22,14 +22,21 @@ hipError_t prop_launch_forward(const float* prm, int64_t n, const double* ell, c
 hipError_t prop_launch_rows(uint64_t s0x, uint64_t s0y, uint64_t index, int64_t n_ctx, int64_t m,
                             const double* ctx4, double c_psd, double r0, double fmin, double fmax,
                             double* ell, double* theta, double* h, hipStream_t st);
-size_t prop_step_scratch_floats(int64_t n_sample, int64_t n_grid);
-hipError_t prop_launch_loss_grad(const float* prm, int64_t n_ctx, int64_t m, const int32_t* ctxlist,
-                                 const double* ctx4, const double* ell, const double* theta,
-                                 const double* h, int G, double lmin, double Lw, float* og,
-                                 float* wgrid, double* dscratch, float* gpart, float* grad,
-                                 double* loss, hipStream_t st);
-hipError_t prop_launch_adam(float* prm, float* m1, float* m2, const float* grad, float lr,
-                            int64_t t, hipStream_t st);
+// One loss / gradient evaluation over n_ctx contexts of m samples and G grid
+// points: rows per block, blocks (each with NPARAM gradient partials), and the
+// doubles and floats of scratch beside those.
+struct StepSizes {
+    int64_t chunk, blocks;
+    size_t doubles, floats;
+};
+StepSizes prop_step_sizes(int64_t n_ctx, int64_t m, int64_t G);
+// m1 != NULL: followed by step t of Adam on prm (moments m1, m2, rate lr).
+hipError_t prop_launch_step(float* prm, const StepSizes& z, int64_t n_ctx, int64_t m,
+                            const int32_t* ctxlist, const double* ctx4, const double* ell,
+                            const double* theta, const double* h, int G, double lmin, double Lw,
+                            double* dscratch, float* fscratch, float* gpart, float* grad,
+                            double* loss, float* m1, float* m2, float lr, int64_t t,
+                            hipStream_t st);
 hipError_t prop_launch_table(const float* o, int64_t nB, int n_cells, const double* bth,
                              double Lw, double beta, double* p, double* alpha, double* phi,
                              double* cdf, double* scratch, hipStream_t st);

@@ -81,34 +81,30 @@ size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // scratch of one loss/gradient evaluation over n_ctx contexts
 struct StepScratch {
-    float* og;
-    float* wgrid;
+    qrfs::StepSizes z;
     double* dscr;
+    float* fscr;
     float* gpart;
     int32_t* ctxlist;
 };
 
 qrfs_status step_scratch(qrfs_proposal* p, int64_t n_ctx, int64_t m, int G, int64_t list_len,
                          StepScratch& s) {
-    const int64_t n_grid = n_ctx * G;
-    const int64_t n_blocks = (n_ctx * m + n_grid + 63) / 64;
+    s.z = qrfs::prop_step_sizes(n_ctx, m, G);
     size_t o = 0;
-    const size_t og = o;
-    o += a256(sizeof(float) * n_grid);
-    const size_t wg = o;
-    o += a256(sizeof(float) * n_grid);
     const size_t ds = o;
-    o += a256(sizeof(double) * (n_ctx + 2 + n_blocks));
+    o += a256(sizeof(double) * s.z.doubles);
+    const size_t fs = o;
+    o += a256(sizeof(float) * s.z.floats);
     const size_t gp = o;
-    o += a256(sizeof(float) * qrfs::prop_step_scratch_floats(n_ctx * m, n_grid));
+    o += a256(sizeof(float) * (size_t)s.z.blocks * qrfs::NPARAM);
     const size_t cl = o;
     o += a256(sizeof(int32_t) * list_len);
     qrfs_status st = workspace(p, o);
     if (st) return st;
     char* b = (char*)p->ws;
-    s.og = (float*)(b + og);
-    s.wgrid = (float*)(b + wg);
     s.dscr = (double*)(b + ds);
+    s.fscr = (float*)(b + fs);
     s.gpart = (float*)(b + gp);
     s.ctxlist = (int32_t*)(b + cl);
     return QRFS_OK;
@@ -275,9 +271,9 @@ qrfs_status qrfs_proposal_loss_grad(qrfs_proposal* p, int64_t n_ctx, int64_t m,
                                   hipMemcpyHostToDevice, strm);
     if (e == hipSuccess) e = hipStreamSynchronize(strm);
     if (e == hipSuccess)
-        e = qrfs::prop_launch_loss_grad(p->prm, n_ctx, m, s.ctxlist, ctx4, ell, theta, h, G,
-                                        p->lmin, p->Lw, s.og, s.wgrid, s.dscr, s.gpart, grad,
-                                        loss, strm);
+        e = qrfs::prop_launch_step(p->prm, s.z, n_ctx, m, s.ctxlist, ctx4, ell, theta, h, G,
+                                   p->lmin, p->Lw, s.dscr, s.fscr, s.gpart, grad, loss, nullptr,
+                                   nullptr, 0.0f, 0, strm);
     return e == hipSuccess ? api_ok() : hfail(e, "loss/gradient");
 }
 
@@ -322,14 +318,12 @@ qrfs_status qrfs_proposal_train(qrfs_proposal* p, int64_t n_ctx, int64_t m, cons
     if (e == hipSuccess) e = hipStreamSynchronize(strm);
     if (e != hipSuccess) return hfail(e, "upload of the context order");
     for (int64_t k = 0; k < steps; ++k) {
-        e = qrfs::prop_launch_loss_grad(p->prm, ctx_per_step, m, s.ctxlist + k * ctx_per_step,
-                                        ctx4, ell, theta, h, G, p->lmin, p->Lw, s.og, s.wgrid,
-                                        s.dscr, s.gpart, p->grad,
-                                        loss_log ? loss_log + k : nullptr, strm);
-        if (e != hipSuccess) return hfail(e, "training step");
         p->t += 1;
-        e = qrfs::prop_launch_adam(p->prm, p->m1, p->m2, p->grad, (float)lr, p->t, strm);
-        if (e != hipSuccess) return hfail(e, "Adam step");
+        e = qrfs::prop_launch_step(p->prm, s.z, ctx_per_step, m, s.ctxlist + k * ctx_per_step, ctx4,
+                                   ell, theta, h, G, p->lmin, p->Lw, s.dscr, s.fscr, s.gpart,
+                                   p->grad, loss_log ? loss_log + k : nullptr, p->m1, p->m2,
+                                   (float)lr, p->t, strm);
+        if (e != hipSuccess) return hfail(e, "training step");
     }
     return api_ok();
 }
