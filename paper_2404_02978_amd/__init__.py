@@ -239,8 +239,16 @@ def _check(status):
         raise QrfsError(status, lib.qrfs_last_error_detail().decode())
 
 
+# The current stream's handle without building a torch.cuda.Stream for it: 0.2
+# instead of 2.9 us per call, a quarter of a small call's host time.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _dev_f64(t, name, n=None):

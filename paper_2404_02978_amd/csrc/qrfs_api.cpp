@@ -74,7 +74,8 @@ struct DeviceGuard {
     bool okay = false;
     explicit DeviceGuard(int dev) {
         if (hipGetDevice(&prev) != hipSuccess) prev = -1;
-        okay = hipSetDevice(dev) == hipSuccess;
+        okay = prev == dev || hipSetDevice(dev) == hipSuccess;
+        if (prev == dev) prev = -1;  // nothing to restore
     }
     ~DeviceGuard() {
         if (prev >= 0) (void)hipSetDevice(prev);

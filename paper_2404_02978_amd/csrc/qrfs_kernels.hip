@@ -4,6 +4,8 @@
 // vector ALU), its epilogues and the fixed-order structure-function
 // reduction.  The sampler and the weights live in qrfs_frequencies.hip, the
 // binary64 contraction of shared sets in qrfs_f64.hip.
+#include <atomic>
+
 #include "qrfs_device.hpp"
 #include "qrfs_internal.hpp"
 #include "qrfs_mfma.hpp"
@@ -1090,8 +1092,17 @@ static int64_t sf_resident_slots(int precision, int64_t R_block, int64_t P) {
     else if (precision == 2) kern = (const void*)k_sum_mfma<2, BASIS_DIFF, EPI_SFSUM, 1, 1, 0>;
     else if (precision == 3) kern = (const void*)k_sum_mfma<3, BASIS_DIFF, EPI_SFSUM, 1, 1, 0>;
     else kern = (const void*)k_sum_mfma<4, BASIS_DIFF, EPI_SFSUM, 1, 1, 0>;
+    // a constant of the device, the kernel and the block size, asked for once
+    static std::atomic<int64_t> known[16][5][9];
     int dev = 0, ncu = 0, nb = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
+    const bool have_dev = hipGetDevice(&dev) == hipSuccess;
+    std::atomic<int64_t>* slot =
+        have_dev && dev >= 0 && dev < 16 ? &known[dev][precision][s.WV] : nullptr;
+    if (slot) {
+        const int64_t v = slot->load(std::memory_order_relaxed);
+        if (v) return v;
+    }
+    if (!have_dev ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         ncu < 1)
         ncu = 256;
@@ -1099,6 +1110,7 @@ static int64_t sf_resident_slots(int precision, int64_t R_block, int64_t P) {
         nb < 1)
         nb = 1;
     (void)hipGetLastError();
+    if (slot) slot->store((int64_t)ncu * nb, std::memory_order_relaxed);
     return (int64_t)ncu * nb;
 }
 
