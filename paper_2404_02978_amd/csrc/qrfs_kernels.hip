@@ -474,6 +474,7 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
     const int kk = threadIdx.x % KC;
     const int pp0 = threadIdx.x / KC;
     const int cstep = blockDim.x / KC;
+    const int ncols = a.P - col0 < NT ? (int)(a.P - col0) : NT;
     for (int i = threadIdx.x; i < NT; i += blockDim.x) {
         int64_t p = col0 + i;
         bool ok = p < a.P;
@@ -561,7 +562,9 @@ __device__ __forceinline__ void sum_tile(const SumArgs& a, int64_t row_tiles, in
         const double gw =
             BASIS == BASIS_PISTON ? cw * grad_factor(a.grad, a.gx, a.gy, cfx, cfy) : cw;
         const double sh = BASIS == BASIS_PISTON ? grad_shift(a.grad) : 0.0;
-        for (int pp = pp0; pp < NT; pp += cstep) {
+        // (columns past the points are left as they are: they only feed sums
+        // that are never stored)
+        for (int pp = pp0; pp < ncols; pp += cstep) {
             double amp = gw * (kAmp * wscale);
             if (BASIS == BASIS_PISTON) amp *= (double)aperture_filter_f32(sm.sap[pp], fmag);
             float cb, sb;
@@ -785,14 +788,15 @@ constexpr int sum_mfma_min_waves() {
     return (EPI == EPI_SFSUM && MW * NB == 1 && (PREC < 3 || CSRC == 0)) ? (PREC == 4 ? 6 : 5) : 1;
 }
 
-// Blocks of the difference basis may hold 8 waves (256 rows), the others 4.
-template <int BASIS>
+// Blocks of the difference and piston bases may hold 8 waves (256 rows of up
+// to 32 columns), the others 4.
+template <int BASIS, int NB>
 constexpr int sum_mfma_max_threads() {
-    return BASIS == BASIS_DIFF ? 512 : 256;
+    return BASIS == BASIS_DIFF || (BASIS == BASIS_PISTON && NB == 1) ? 512 : 256;
 }
 
 template <int PREC, int BASIS, int EPI, int MW, int NB, int CSRC>
-__global__ __launch_bounds__(sum_mfma_max_threads<BASIS>()) __attribute__((
+__global__ __launch_bounds__((sum_mfma_max_threads<BASIS, NB>())) __attribute__((
     amdgpu_waves_per_eu(sum_mfma_min_waves<PREC, EPI, MW, NB, CSRC>(), 8))) void
 k_sum_mfma(SumArgs a, int64_t row_tiles, int64_t col_tiles) {
     __shared__ MfmaSmem<PREC, NB> sm;
@@ -1052,8 +1056,12 @@ static MfmaShape mfma_shape(int precision, int basis, int64_t R_block, int64_t P
     int64_t wv = cdiv(R_block, 32 * s.MW);
     s.WV = (int)(wv > 4 ? 4 : wv);
     // differential pistons of at most 32 baselines: one block covers 256
-    // rows, so each set's difference basis is built once per 256 rows
+    // rows, so each set's difference basis is built once per 256 rows; pistons
+    // likewise, whose basis holds the filter (ten apertures x 1e4 realisations at
+    // 250 per set, FP32: a call takes 118 us, 144 with 4 waves and the basis of
+    // all 32 columns)
     if (precision >= 2 && basis == BASIS_DIFF && P <= 32 && wv >= 8) s.WV = 8;
+    if (basis == BASIS_PISTON && wv >= 8) s.WV = 8;
     return s;
 }
 
@@ -1247,7 +1255,8 @@ StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R
         const int lds = (precision == 3 ? 2 : 3) * (m.NB == 2 ? 1 : 2);
         const int fit = 4 / m.WV > 1 ? (4 / m.WV < lds ? 4 / m.WV : lds) : 1;
         slots = 256 * fit;
-        block_us = 1e-3 * c * (double)K * (fit * m.WV < 4 ? 1.4 : 1.0);
+        block_us = 1e-3 * c * (double)K *
+                   (m.WV > 4 ? (double)m.WV / 4.0 : (fit * m.WV < 4 ? 1.4 : 1.0));
     }
     for (int64_t k = 1; k <= (kmax < 1 ? 1 : kmax); ++k) {
         if (k > 1 && (size_t)k * one > max_bytes) break;

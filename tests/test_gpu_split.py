@@ -176,3 +176,19 @@ def test_captured_calls_hold_no_workspace(q, precision, K, R, R_block, P):
                                  200.0, 0.1)
             eager = c.synthesize_phase(*args, rng=q.Rng(4, 0, 0), precision=precision)
             check(host(eager), ref, TOL[precision])
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("K,R,R_block,P", [(300, 450, 225, 1), (129, 514, 257, 10),
+                                           (700, 250, 250, 31), (65, 600, 600, 33)])
+def test_pistons_of_many_rows(q, ctx, precision, K, R, R_block, P):
+    """Blocks of 225 rows and more (eight waves), with few real columns."""
+    fx, fy, w, px, py = problem(ctx, q, K, R, R_block, P)
+    D = np.random.default_rng(P).uniform(0.5, 8.0, P)
+    d = 0.2 * D
+    print(f"rows p{precision} K{K} R{R} Rb{R_block} P{P}", flush=True)
+    out = ctx.piston(K, fx, fy, w, dev(px), dev(py), dev(D), dev(d), R, R_block,
+                     rng=q.Rng(3, 1, 0), precision=precision)
+    ref = oracle.piston(host(fx), host(fy), host(w), px, py, D, d, R, R_block, K=K, seed=3,
+                        counter=1)
+    check(host(out), ref, TOL[precision])
