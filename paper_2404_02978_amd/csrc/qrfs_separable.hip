@@ -29,9 +29,11 @@ namespace qrfs {
 // Bound: the FP64 datapath, which the matrix instructions share with the
 // vector ALU (measured: the times add).  Per step a 2 x 2 wave spends 8
 // matrix instructions (64 cycles each) and 4 sine / cosine pairs (~35
-// instructions of 4 cycles).  2000 realisations x 1936 frequencies x 1024
-// differential samples: 0.60 ms (the matrix instructions alone 0.43 ms at
-// 73.7 TFLOP/s), against 9.4 ms for both telescopes in the general kernel.
+// instructions of 4 cycles), in a series 2 pairs and 2 rotations by turns that
+// are staged with the frequency.  2000 realisations x 1936 frequencies x 1024
+// differential samples: 0.50 ms (the matrix instructions alone 0.22 ms at
+// 73.7 TFLOP/s; 0.60 with 4 pairs), against 9.4 ms for both telescopes in the
+// general kernel.
 //
 // DIFF: the sums at x minus the sums at x + delta (the differential piston
 // of two telescopes): the coefficients are first turned by delta,
@@ -44,11 +46,18 @@ constexpr int SEP_KC = 128;  // frequencies a wave stages at a time
 template <int MU, int NV, int WV>
 struct SepSmem {
     static constexpr int TILE = 256 * MU * NV;
-    static constexpr int STAGE = WV * SEP_KC * 4;
+    static constexpr int STAGE = WV * SEP_KC * 8;
     static constexpr int TREE = (WV / 2) * TILE;
     // the staged frequencies, then (after the loop) the partial tiles
     __attribute__((aligned(16))) double d[STAGE > TREE ? STAGE : TREE];
 };
+
+// (sn, cs) turned by the angle of (sin, cos) = (t.x, t.y).
+__device__ __forceinline__ void turn(const double2& t, double& sn, double& cs) {
+    const double s = fma(sn, t.y, cs * t.x);
+    cs = fma(cs, t.y, -(sn * t.x));
+    sn = s;
+}
 
 // One output tile of realisation r (all threads of the block call it): the
 // lane's rows (rx, ry) and columns (cx, cy), frequencies fx, fy, w of the set.
@@ -73,7 +82,8 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
     const int64_t kw = ((a.K + 8 * WV - 1) / (8 * WV)) * 8;
     const int64_t kb = wave * kw;
     const int64_t ke = kb + kw < a.K ? kb + kw : a.K;
-    double* st = sm + wave * SEP_KC * 4;
+    constexpr int FS = DIFF ? 8 : 4;  // doubles per staged frequency
+    double* st = sm + wave * SEP_KC * FS;
     for (int64_t k0 = kb; k0 < ke; k0 += SEP_KC) {
         {
             const int64_t k = k0 + 2 * lane;
@@ -101,9 +111,18 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
                     cb = fma(cb, oc, ca * sd);
                     ca = ta;
                 }
-                double2* dst = (double2*)(st + (2 * lane + h) * 4);
+                double2* dst = (double2*)(st + (2 * lane + h) * FS);
                 dst[0] = make_double2(f0, f1);
                 dst[1] = make_double2(ca, cb);
+                if constexpr (DIFF) {
+                    // the turns from the first 16 rows and columns to the next
+                    double s1, c1;
+                    const double step = fma(f0, a.sx, f1 * a.sy);
+                    sincos2pi_reduced(frac_centered(step * (16.0 * a.V)), s1, c1);
+                    dst[2] = make_double2(s1, c1);
+                    sincos2pi_reduced(frac_centered(step * 16.0), s1, c1);
+                    dst[3] = make_double2(s1, c1);
+                }
             }
         }
         // the wave's own stage: written and read by the same wave
@@ -112,20 +131,27 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
         const int64_t left = ke - k0;
         const int steps = left >= SEP_KC ? SEP_KC / 4 : (int)((left + 3) / 4);
         for (int g = 0; g < steps; ++g) {
-            const double2* src = (const double2*)(st + (4 * g + lh) * 4);
+            const double2* src = (const double2*)(st + (4 * g + lh) * FS);
             const double2 f = src[0], c = src[1];
             double A[MU], B[MU];
+            double sn = 0.0, cs = 0.0;
 #pragma unroll
             for (int m = 0; m < MU; ++m) {
-                double sn, cs;
-                sincos2pi_reduced(frac_centered(fma(f.x, rx[m], f.y * ry[m])), sn, cs);
+                if (DIFF && m > 0) {
+                    turn(src[2], sn, cs);
+                } else {
+                    sincos2pi_reduced(frac_centered(fma(f.x, rx[m], f.y * ry[m])), sn, cs);
+                }
                 A[m] = fma(c.x, cs, c.y * sn);
                 B[m] = fma(c.y, cs, -(c.x * sn));
             }
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
-                double sn, cs;
-                sincos2pi_reduced(frac_centered(fma(f.x, cx[n], f.y * cy[n])), sn, cs);
+                if (DIFF && n > 0) {
+                    turn(src[3], sn, cs);
+                } else {
+                    sincos2pi_reduced(frac_centered(fma(f.x, cx[n], f.y * cy[n])), sn, cs);
+                }
 #pragma unroll
                 for (int m = 0; m < MU; ++m) acc[m][n] = mfma_f64(A[m], cs, acc[m][n]);
 #pragma unroll
