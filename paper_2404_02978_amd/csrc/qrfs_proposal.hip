@@ -20,7 +20,8 @@ namespace prop {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int ROWS = 48;     // rows of a tile: three 16-row matrix tiles
+constexpr int ROWS = 48;     // rows of a training tile: three 16-row matrix tiles
+constexpr int ROWS_F = 64;   // rows of a tile of the forward-only kernels, which keep one matrix less
 constexpr int THREADS = 512; // 8 waves, one per 16 hidden units
 constexpr int ST = 132;      // floats per row of the LDS matrices: 16-byte rows, and the 16 lanes
                              // of a 16-byte operand read on 16 different groups of 4 banks
@@ -73,22 +74,28 @@ __device__ __forceinline__ float tanh_f32(float x) {
     return a < 0.625f ? small : big;
 }
 
+// Inputs of a row: the 5 features, 1 (for the bias of layer 1), 0, 0.
+constexpr int XW = 8;
+
+template <int NR>
 struct NetSmem {
     __attribute__((aligned(16))) float W2[HID * ST];  // row i: weights of hidden unit i
-    __attribute__((aligned(16))) float h1[ROWS * ST]; // activations, row-major
-    __attribute__((aligned(16))) float h2[ROWS * ST]; // layer 2, then dL/d(pre-activation 1)
+    __attribute__((aligned(16))) float h1[NR * ST];   // activations, row-major
+    __attribute__((aligned(16))) float h2[NR * ST];
     float W3[2 * HID];
     float b2[HID];
     float b3[2];
-    float x[ROWS][8];
+    float x[NR][XW];
 };
 
-// What a thread keeps of layer 1: the weights of hidden unit t % 128.
+// What a lane keeps of layer 1: the column of [W1 b1 0 0] that it feeds to the
+// matrix instructions, of hidden unit 16 (t / 64) + t % 16.
 struct Layer1 {
-    float w[5], b;
+    float w[2];
 };
 
-__device__ __forceinline__ Layer1 load_params(const float* __restrict__ prm, NetSmem& s) {
+template <int NR>
+__device__ __forceinline__ Layer1 load_params(const float* __restrict__ prm, NetSmem<NR>& s) {
     const int t = threadIdx.x;
     for (int i = t; i < HID * HID / 2; i += THREADS) {  // pairs (OFF_W2 is even)
         const float2 v = ((const float2*)(prm + OFF_W2))[i];
@@ -97,56 +104,68 @@ __device__ __forceinline__ Layer1 load_params(const float* __restrict__ prm, Net
     if (t < 2 * HID) s.W3[t] = prm[OFF_W3 + t];
     if (t < HID) s.b2[t] = prm[OFF_B2 + t];
     if (t < 2) s.b3[t] = prm[OFF_B3 + t];
+    const int u = 16 * (t >> 6) + (t & 15), lh = (t & 63) >> 4;
     Layer1 l;
-    const int i = t % HID;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) l.w[j] = prm[OFF_W1 + i * 5 + j];
-    l.b = prm[OFF_B1 + i];
+    l.w[0] = prm[OFF_W1 + u * 5 + lh];
+    l.w[1] = lh == 0 ? prm[OFF_W1 + u * 5 + 4] : lh == 1 ? prm[OFF_B1 + u] : 0.0f;
     return l;
+}
+
+__device__ __forceinline__ void put_inputs(float (&x)[XW], float x0, const float f[4]) {
+    x[0] = x0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[1 + j] = f[j];
+    x[5] = 1.0f;
+    x[6] = x[7] = 0.0f;
 }
 
 __device__ __forceinline__ f32x4 mfma_16(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Forward of the tile's rows (inputs in s.x, a barrier after them).  Leaves h1
-// and h2 and returns, in thread (r = t / 8 < ROWS, t % 8 = 0), the outputs of row
-// r.  Hidden layer: wave w computes units [16 w, 16 w + 16) of all rows with
-// v_mfma_f32_16x16x4 (lane l: operand row l % 16, contraction values 4 (l / 16)
-// + q of each 16, in steps q; result rows 4 (l / 16) + i, column l % 16): FP32
-// products and sums at twice the rate of the vector ALU, whose one thread per
-// (row, 32 units) this replaces.
-__device__ __forceinline__ void forward_tile(NetSmem& s, const Layer1& l1, float o[2]) {
+// Forward of the tile's rows (inputs in x, a barrier after them).  Leaves h1
+// and h2 and returns, in the 8 threads of row r = t / 8, its outputs.  Wave w
+// computes units [16 w, 16 w + 16) of all rows of both hidden layers with
+// v_mfma_f32_16x16x4 (lane l: operand row l % 16; layer 1: contraction value
+// 4 q + l / 16 in step q; layer 2: 4 (l / 16) + q of each 16; result rows
+// 4 (l / 16) + i, column l % 16): FP32 products and sums at twice the rate of
+// the vector ALU, whose one thread per (row, 32 units) this replaces.
+template <int NR>
+__device__ __forceinline__ void forward_tile(NetSmem<NR>& s, const float (*x)[XW],
+                                             const Layer1& l1, float o[2]) {
+    constexpr int MT = NR / 16;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, li = lane & 15, lh = lane >> 4;
+    const int u = 16 * wave + li;
     {
-        const int i = t % HID;
-#pragma unroll 4
-        for (int j = 0; j < ROWS / 4; ++j) {
-            const int r = t / HID + 4 * j;
-            float a = l1.b;
+        f32x4 acc[MT] = {};
 #pragma unroll
-            for (int q = 0; q < 5; ++q) a = fmaf(l1.w[q], s.x[r][q], a);
-            s.h1[r * ST + i] = tanh_f32(a);
-        }
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+                acc[m] = mfma_16(x[16 * m + li][4 * q + lh], l1.w[q], acc[m]);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                s.h1[(16 * m + 4 * lh + i) * ST + u] = tanh_f32(acc[m][i]);
     }
     __syncthreads();
-    f32x4 acc[3] = {};
-    const int u = 16 * wave + li;
+    f32x4 acc[MT] = {};
 #pragma unroll
     for (int g = 0; g < HID / 16; ++g) {
         const f32x4 B = *(const f32x4*)&s.W2[u * ST + 16 * g + 4 * lh];
-        f32x4 A[3];
+        f32x4 A[MT];
 #pragma unroll
-        for (int m = 0; m < 3; ++m)
+        for (int m = 0; m < MT; ++m)
             A[m] = *(const f32x4*)&s.h1[(16 * m + li) * ST + 16 * g + 4 * lh];
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int m = 0; m < 3; ++m) acc[m] = mfma_16(A[m][q], B[q], acc[m]);
+            for (int m = 0; m < MT; ++m) acc[m] = mfma_16(A[m][q], B[q], acc[m]);
     }
     const float b2 = s.b2[u];
 #pragma unroll
-    for (int m = 0; m < 3; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             s.h2[(16 * m + 4 * lh + i) * ST + u] = tanh_f32(acc[m][i] + b2);
@@ -154,7 +173,7 @@ __device__ __forceinline__ void forward_tile(NetSmem& s, const Layer1& l1, float
     // outputs: 8 threads per row, 16 units each, added in a fixed tree
     const int r = t >> 3, part = t & 7;
     float p0 = 0.0f, p1 = 0.0f;
-    if (r < ROWS) {
+    if (r < NR) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int k = 16 * part + 4 * j;
@@ -181,26 +200,25 @@ __global__ __launch_bounds__(THREADS) void k_forward(const float* __restrict__ p
                                                      const double* __restrict__ ell,
                                                      const double* __restrict__ ctx4, double lmin,
                                                      double Lw, float* __restrict__ out) {
-    __shared__ NetSmem s;
+    __shared__ NetSmem<ROWS_F> s;
     const Layer1 l1 = load_params(prm, s);
-    const int64_t n_tiles = (n_rows + ROWS - 1) / ROWS;
+    const int64_t n_tiles = (n_rows + ROWS_F - 1) / ROWS_F;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t base = tile * ROWS;
-        if (threadIdx.x < ROWS) {
+        const int64_t base = tile * ROWS_F;
+        if (threadIdx.x < ROWS_F) {
             const int64_t q = base + threadIdx.x;
-            float x[5] = {0, 0, 0, 0, 0};
+            float x0 = 0.0f, f[4] = {0, 0, 0, 0};
             if (q < n_rows) {
-                x[0] = ell_feature(ell[q], lmin, Lw);
-                context_features(ctx4 + 4 * q, x + 1);
+                x0 = ell_feature(ell[q], lmin, Lw);
+                context_features(ctx4 + 4 * q, f);
             }
-#pragma unroll
-            for (int j = 0; j < 5; ++j) s.x[threadIdx.x][j] = x[j];
+            put_inputs(s.x[threadIdx.x], x0, f);
         }
         __syncthreads();
         float o[2];
-        forward_tile(s, l1, o);
+        forward_tile(s, s.x, l1, o);
         const int64_t q = base + (threadIdx.x >> 3);
-        if ((threadIdx.x & 7) == 0 && threadIdx.x < 8 * ROWS && q < n_rows) {
+        if ((threadIdx.x & 7) == 0 && q < n_rows) {
             out[2 * q] = o[0];
             out[2 * q + 1] = o[1];
         }
@@ -209,14 +227,31 @@ __global__ __launch_bounds__(THREADS) void k_forward(const float* __restrict__ p
     }
 }
 
+// The block's maximum or sum of v in a fixed order (red: one entry per wave).
+template <bool MAX>
+__device__ __forceinline__ double block_reduce(double v, double* red) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double u = __shfl_xor(v, off);
+        v = MAX ? fmax(v, u) : v + u;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = red[0];
+#pragma unroll
+    for (int w = 1; w < THREADS / 64; ++w) v = MAX ? fmax(v, red[w]) : v + red[w];
+    return v;
+}
+
 // Per context slot c of a step.  Block c: the grid points' o0, log Z =
 // log(sum_j exp(o0_j) Lw / G), the softmax over the grid and the context's
 // features; block n_ctx + c: H_c, the sum of h over its sample rows.  All in a
 // fixed order.
 __global__ __launch_bounds__(THREADS) void k_grid(const float* __restrict__ prm, RowSpec rs,
                                                   float* __restrict__ og) {
-    __shared__ NetSmem s;
-    __shared__ double red[THREADS];
+    __shared__ NetSmem<ROWS_F> s;
+    __shared__ double red[THREADS / 64];
     const int t = threadIdx.x;
     if (blockIdx.x >= rs.n_ctx) {
         const uint32_t c = blockIdx.x - rs.n_ctx;
@@ -231,13 +266,8 @@ __global__ __launch_bounds__(THREADS) void k_grid(const float* __restrict__ prm,
             for (int e = 0; e < 4; ++e) a += v[e];
         }
         for (; i < rs.m; i += THREADS) a += h[i];
-        red[t] = a;
-        __syncthreads();
-        for (int w = THREADS / 2; w > 0; w >>= 1) {
-            if (t < w) red[t] += red[t + w];
-            __syncthreads();
-        }
-        if (t == 0) rs.Hc[c] = red[0];
+        a = block_reduce<false>(a, red);
+        if (t == 0) rs.Hc[c] = a;
         return;
     }
     const uint32_t c = blockIdx.x;
@@ -248,147 +278,155 @@ __global__ __launch_bounds__(THREADS) void k_grid(const float* __restrict__ prm,
 #pragma unroll
         for (int j = 0; j < 4; ++j) rs.feat[4 * c + j] = f[j];
     float* o = og + (size_t)c * rs.G;
-    for (uint32_t g0 = 0; g0 < rs.G; g0 += ROWS) {
-        if (t < ROWS) {
+    for (uint32_t g0 = 0; g0 < rs.G; g0 += ROWS_F) {
+        if (t < ROWS_F) {
             const uint32_t j = g0 + t;
-            s.x[t][0] = j < rs.G ? ell_feature(rs.lmin + (j + 0.5) * rs.Lw / rs.G, rs.lmin, rs.Lw)
-                                 : 0.0f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s.x[t][1 + e] = f[e];
+            put_inputs(s.x[t],
+                       j < rs.G ? ell_feature(rs.lmin + (j + 0.5) * rs.Lw / rs.G, rs.lmin, rs.Lw)
+                                : 0.0f,
+                       f);
         }
         __syncthreads();
         float ov[2];
-        forward_tile(s, l1, ov);
+        forward_tile(s, s.x, l1, ov);
         const uint32_t j = g0 + (t >> 3);
-        if ((t & 7) == 0 && t < 8 * ROWS && j < rs.G) o[j] = ov[0];
+        if ((t & 7) == 0 && j < rs.G) o[j] = ov[0];
         __syncthreads();
     }
     // this block's o0 back from memory (written by itself, before a barrier)
     __threadfence_block();
     double mx = -1e300;
     for (uint32_t j = t; j < rs.G; j += THREADS) mx = fmax(mx, (double)o[j]);
-    red[t] = mx;
-    __syncthreads();
-    for (int w = THREADS / 2; w > 0; w >>= 1) {
-        if (t < w) red[t] = fmax(red[t], red[t + w]);
-        __syncthreads();
-    }
-    mx = red[0];
-    __syncthreads();
+    mx = block_reduce<true>(mx, red);
     double se = 0.0;
     for (uint32_t j = t; j < rs.G; j += THREADS) se += exp((double)o[j] - mx);
-    red[t] = se;
-    __syncthreads();
-    for (int w = THREADS / 2; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    se = red[0];
+    se = block_reduce<false>(se, red);
     for (uint32_t j = t; j < rs.G; j += THREADS)
         rs.soft[(size_t)c * rs.G + j] = exp((double)o[j] - mx) / se;
     if (t == 0) rs.logZ[c] = mx + log(se * rs.Lw / rs.G);
 }
 
-// 1 / sum of H_c (0 if the sum is not positive), in a fixed order.
+// 1 / sum of H_c (0 if the sum is not positive), in a fixed order; all lanes of
+// a wave call it (one thread that adds H_c by H_c waits on each load: 4 us for
+// 16 contexts).
 __device__ __forceinline__ double inverse_H(const RowSpec& rs) {
     double H = 0.0;
-    for (uint32_t c = 0; c < rs.n_ctx; ++c) H += rs.Hc[c];
+    for (uint32_t c = threadIdx.x & 63; c < rs.n_ctx; c += 64) H += rs.Hc[c];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) H += __shfl_xor(H, off);
     return H > 0.0 ? 1.0 / H : 0.0;
+}
+
+// Inputs of a training tile, row by row: a sample's weight w = -h / H and
+// C = cos 2 (theta - theta_B); a normaliser's w = dL/do0 and C = 2, its mark.
+struct TileRows {
+    float x[ROWS][XW];
+    double w[ROWS], C[ROWS];
+};
+__device__ __forceinline__ void load_row(const RowSpec& rs, double invH, uint32_t q, uint32_t r1,
+                                         int r, TileRows& d) {
+    float x0 = 0.0f, f[4] = {0, 0, 0, 0};
+    double w = 0.0, C = 0.0;
+    if (q < r1) {
+        const bool sample = q < rs.n_sample;
+        const uint32_t n = sample ? q : q - rs.n_sample, per = sample ? rs.m : rs.G;
+        const uint32_t cs = n / per, j = n % per;
+        double ell;
+        if (sample) {
+            const int64_t i = (int64_t)rs.ctxlist[cs] * rs.m + j;
+            ell = rs.ell[i];
+            w = -rs.h[i] * invH;
+            C = cos(2.0 * (rs.theta[i] - rs.ctx4[4 * (int64_t)rs.ctxlist[cs] + 3]));
+        } else {
+            ell = rs.lmin + (j + 0.5) * rs.Lw / rs.G;
+            w = rs.Hc[cs] * invH * rs.soft[n];
+            C = 2.0;
+        }
+        x0 = ell_feature(ell, rs.lmin, rs.Lw);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = rs.feat[4 * cs + e];
+    }
+    put_inputs(d.x[r], x0, f);
+    d.w[r] = w;
+    d.C[r] = C;
 }
 
 // Fused forward + backward over rows [block * chunk, (block + 1) * chunk) of
 // the step in tiles of 48; the block's gradient stays in registers over its
 // tiles and goes to gpart[block][NPARAM] once, with its loss.  One block per
-// compute unit (its parameters and activations take 145 KB of LDS).  Matrix
+// compute unit (its parameters and activations take 150 KB of LDS).  Matrix
 // work per row: 3 x 2 x 128^2 flops (hidden layer forward, its weight gradient
 // and the gradient of layer 1's activations), all on v_mfma_f32_16x16x4: 23 us
-// for 33792 rows at its rate, tanh and the small layers beside them.
+// for 33792 rows at its rate.  The two waves of a SIMD hide little else, so the
+// rest is kept off that path: the small layers' gradients are sums in registers
+// of values that pass by anyway, or 12 more matrix instructions (layer 1), and
+// two waves compute the loss and fetch the next tile's rows beside the other
+// waves' matrix work.  33792 rows: 56 us (68 with loops over the rows in LDS for
+// the small layers).
 __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm, RowSpec rs,
                                                    uint32_t chunk, float* __restrict__ gpart,
                                                    double* __restrict__ lpart) {
-    __shared__ NetSmem s;
+    __shared__ NetSmem<ROWS> s;
     __shared__ __attribute__((aligned(16))) float d2[ROWS * ST];  // dL/d(pre-activation 2)
     __shared__ float dout[ROWS][2];
-    __shared__ double s_w[ROWS], s_C[ROWS], s_loss[ROWS];
-    __shared__ double s_invH;
+    __shared__ double s_o0[ROWS], s_aC[ROWS];
+    __shared__ TileRows rows[2];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, li = lane & 15, lh = lane >> 4;
     const Layer1 l1 = load_params(prm, s);
-    if (t == 0) s_invH = inverse_H(rs);
-    __syncthreads();
-    const double invH = s_invH;
+    const double invH = inverse_H(rs);
     const uint32_t n_rows = rs.n_sample + rs.n_grid;
     const uint32_t r0 = blockIdx.x * chunk;
     const uint32_t r1 = r0 + chunk < n_rows ? r0 + chunk : n_rows;
     const int u0 = (wave & 3) * 32, k0 = (wave >> 2) * 64;  // tile of the W2 gradient
+    const int i2 = t % HID, part2 = t / HID;                // unit and rows part2 + 4 j of d2
     f32x4 gW2[2][4] = {};
-    float gA = 0.0f, gB = 0.0f, gC = 0.0f, gC1 = 0.0f;  // of the small layers, see below
-    double loss = 0.0;
+    f32x4 gX = {};                            // [k = 16 wave + 4 lh + i][li]: W1, b1 in column 5
+    float gA0 = 0.0f, gA1 = 0.0f, gB = 0.0f;  // W3 and b2 of unit i2 over its rows
+    float gO0 = 0.0f, gO1 = 0.0f;             // b3 over row t / 8 of the tiles
+    double loss = 0.0;                        // wave 6: over row `lane` of the tiles
+    if (t < ROWS) load_row(rs, invH, r0 + t, r1, t, rows[0]);
+    __syncthreads();
 
-    for (uint32_t base = r0; base < r1; base += ROWS) {
-        if (t < ROWS) {
-            const uint32_t q = base + t;
-            float x[5] = {0, 0, 0, 0, 0};
-            double w = 0.0, C = 0.0;
-            if (q < r1) {
-                const bool sample = q < rs.n_sample;
-                const uint32_t n = sample ? q : q - rs.n_sample, per = sample ? rs.m : rs.G;
-                const uint32_t cs = n / per, j = n % per;
-                double ell;
-                if (sample) {
-                    const int64_t i = (int64_t)rs.ctxlist[cs] * rs.m + j;
-                    ell = rs.ell[i];
-                    w = -rs.h[i] * invH;
-                    C = cos(2.0 * (rs.theta[i] - rs.ctx4[4 * (int64_t)rs.ctxlist[cs] + 3]));
-                } else {
-                    ell = rs.lmin + (j + 0.5) * rs.Lw / rs.G;
-                    w = rs.Hc[cs] * invH * rs.soft[n];  // dL/do0 of the normaliser
-                    C = 2.0;                            // marks a grid row
-                }
-                x[0] = ell_feature(ell, rs.lmin, rs.Lw);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[1 + e] = rs.feat[4 * cs + e];
-            }
-#pragma unroll
-            for (int j = 0; j < 5; ++j) s.x[t][j] = x[j];
-            s_w[t] = w;
-            s_C[t] = C;
-        }
-        __syncthreads();
+    int b = 0;
+    for (uint32_t base = r0; base < r1; base += ROWS, b ^= 1) {
+        const TileRows& in = rows[b];
         float o[2];
-        forward_tile(s, l1, o);
+        forward_tile(s, in.x, l1, o);
         if ((t & 7) == 0 && t < 8 * ROWS) {
             const int r = t >> 3;
-            const bool sample = !(s_C[r] > 1.5);
-            const float wg = (float)s_w[r], C = sample ? (float)s_C[r] : 0.0f;
+            const bool sample = !(in.C[r] > 1.5);
+            const float wg = (float)in.w[r], C = sample ? (float)in.C[r] : 0.0f;
             const float ta = tanh_f32(o[1]);
             const float alpha = 0.9f * ta;
+            const float g1 = sample ? wg * C / (1.0f + alpha * C) * 0.9f * (1.0f - ta * ta) : 0.0f;
             dout[r][0] = wg;
-            dout[r][1] = sample ? wg * C / (1.0f + alpha * C) * 0.9f * (1.0f - ta * ta) : 0.0f;
-            s_loss[r] =
-                sample ? (double)wg * ((double)o[0] + log(1.0 + (double)alpha * (double)C)) : 0.0;
+            dout[r][1] = g1;
+            gO0 += wg;
+            gO1 += g1;
+            s_o0[r] = (double)o[0];
+            s_aC[r] = (double)alpha * (double)C;
         }
         __syncthreads();
-        // layer 3: thread c HID + i: W3[c][i]; threads 256, 257: b3
-        if (t < 2 * HID) {
-            const int c = t / HID, i = t % HID;
-#pragma unroll 8
-            for (int r = 0; r < ROWS; ++r) gA = fmaf(dout[r][c], s.h2[r * ST + i], gA);
-        } else if (t < 2 * HID + 2) {
-            for (int r = 0; r < ROWS; ++r) gA += dout[r][t - 2 * HID];
-        } else if (t == THREADS - 1) {
-            for (int r = 0; r < ROWS; ++r) loss += s_loss[r];
-        }
         {
-            const int i = t % HID;
-            const float w0 = s.W3[i], w1 = s.W3[HID + i];
+            const float w0 = s.W3[i2], w1 = s.W3[HID + i2];
 #pragma unroll 4
             for (int j = 0; j < ROWS / 4; ++j) {
-                const int r = t / HID + 4 * j;
-                const float hv = s.h2[r * ST + i];
-                d2[r * ST + i] = (dout[r][0] * w0 + dout[r][1] * w1) * (1.0f - hv * hv);
+                const int r = part2 + 4 * j;
+                const float hv = s.h2[r * ST + i2], e0 = dout[r][0], e1 = dout[r][1];
+                const float d = (e0 * w0 + e1 * w1) * (1.0f - hv * hv);
+                d2[r * ST + i2] = d;
+                gA0 = fmaf(e0, hv, gA0);
+                gA1 = fmaf(e1, hv, gA1);
+                gB += d;
             }
         }
         __syncthreads();
+        if (wave == 6 && lane < ROWS) {
+            if (!(in.C[lane] > 1.5))
+                loss += (double)dout[lane][0] * (s_o0[lane] + log(1.0 + s_aC[lane]));
+        } else if (wave == 7 && lane < ROWS && base + ROWS < r1) {
+            load_row(rs, invH, base + ROWS + lane, r1, lane, rows[b ^ 1]);
+        }
         // hidden layer's weights: gradient [u][k] = sum_r d2[r][u] h1[r][k], the
         // wave's 32 x 64 of it
 #pragma unroll 4
@@ -404,11 +442,9 @@ __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm
 #pragma unroll
                 for (int f = 0; f < 4; ++f) gW2[e][f] = mfma_16(A[e], B[f], gW2[e][f]);
         }
-        if (t < HID) {
-#pragma unroll 8
-            for (int r = 0; r < ROWS; ++r) gB += d2[r * ST + t];  // b2
-        }
-        // dL/d(pre-activation 1): sum_u d2[r][u] W2[u][k], the wave's 16 k
+        // dL/d(pre-activation 1): sum_u d2[r][u] W2[u][k], the wave's 16 k; its
+        // results are the next product's operand as they lie (row k = l % 16,
+        // contraction over the rows 16 m + 4 (l / 16) + i)
         {
             f32x4 acc[3] = {};
             const int k = 16 * wave + li;
@@ -431,20 +467,8 @@ __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm
                 for (int i = 0; i < 4; ++i) {
                     const int r = 16 * m + 4 * lh + i;
                     const float hv = s.h1[r * ST + k];
-                    s.h2[r * ST + k] = acc[m][i] * (1.0f - hv * hv);
+                    gX = mfma_16(acc[m][i] * (1.0f - hv * hv), in.x[r][li & 7], gX);
                 }
-        }
-        __syncthreads();
-        // layer 1: threads (k, 0): W1[k][0], W1[k][1]; (k, 1): W1[k][2], W1[k][3];
-        // (k, 2): W1[k][4]; (k, 3): b1[k]
-        {
-            const int k = t % HID, part = t / HID;
-#pragma unroll 4
-            for (int r = 0; r < ROWS; ++r) {
-                const float d = s.h2[r * ST + k];
-                gC = fmaf(d, part < 3 ? s.x[r][2 * part] : 1.0f, gC);
-                if (part < 2) gC1 = fmaf(d, s.x[r][2 * part + 1], gC1);
-            }
         }
         __syncthreads();
     }
@@ -456,19 +480,35 @@ __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 gp[OFF_W2 + (u0 + 16 * e + 4 * lh + i) * HID + k0 + 16 * f + li] = gW2[e][f][i];
-    if (t < 2 * HID) gp[OFF_W3 + t] = gA;
-    else if (t < 2 * HID + 2) gp[OFF_B3 + t - 2 * HID] = gA;
-    if (t < HID) gp[OFF_B2 + t] = gB;
-    const int k = t % HID, part = t / HID;
-    if (part < 2) {
-        gp[OFF_W1 + k * 5 + 2 * part] = gC;
-        gp[OFF_W1 + k * 5 + 2 * part + 1] = gC1;
-    } else if (part == 2) {
-        gp[OFF_W1 + k * 5 + 4] = gC;
-    } else {
-        gp[OFF_B1 + k] = gC;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 16 * wave + 4 * lh + i;
+        if (li < 5) gp[OFF_W1 + k * 5 + li] = gX[i];
+        if (li == 5) gp[OFF_B1 + k] = gX[i];
     }
-    if (t == THREADS - 1) lpart[blockIdx.x] = loss;
+    // the four parts of the units' sums, the rows' sums of b3
+    float* red = d2;
+    red[t] = gA0;
+    red[THREADS + t] = gA1;
+    red[2 * THREADS + t] = gB;
+    if ((t & 7) == 0 && t < 8 * ROWS) {
+        dout[t >> 3][0] = gO0;
+        dout[t >> 3][1] = gO1;
+    }
+    __syncthreads();
+    if (t < 3 * HID) {
+        const float* v = red + (t / HID) * THREADS + i2;
+        const float a = (v[0] + v[HID]) + (v[2 * HID] + v[3 * HID]);
+        gp[t < 2 * HID ? OFF_W3 + t : OFF_B2 + i2] = a;
+    } else if (wave == 6) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+        if (lane == 0) lpart[blockIdx.x] = loss;
+    } else if (lane < 2) {
+        float a = 0.0f;
+        for (int r = 0; r < ROWS; ++r) a += dout[r][lane];
+        gp[OFF_B3 + lane] = a;
+    }
 }
 
 // grad[p] = sum over blocks (fixed order, binary64); loss = sum of lpart plus
@@ -664,7 +704,7 @@ static int prop_units() {
 
 hipError_t prop_launch_forward(const float* prm, int64_t n, const double* ell, const double* ctx4,
                                double lmin, double Lw, float* out, hipStream_t st) {
-    const int64_t tiles = cdivp(n, prop::ROWS);
+    const int64_t tiles = cdivp(n, prop::ROWS_F);
     const int units = prop_units();
     hipLaunchKernelGGL(prop::k_forward, dim3((unsigned)(tiles < units ? tiles : units)),
                        dim3(prop::THREADS), 0, st, prm, n, ell, ctx4, lmin, Lw, out);
