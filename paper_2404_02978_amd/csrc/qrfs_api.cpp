@@ -937,12 +937,11 @@ qrfs_status qrfs_diff_piston_structure(qrfs_context* ctx, const qrfs_psd* psd,
         e = qrfs::launch_sum(precision, qrfs::BASIS_DIFF, qrfs::EPI_SFSUM, a, stream_);
         if (e != hipSuccess) return hip_fail(e, "structure-function launch");
     }
-    if (plan.ksplit > 1) {
-        hipError_t e = qrfs::launch_sfsum_rows(phi, plan.ksplit, R, nB, partial, stream_);
-        if (e != hipSuccess) return hip_fail(e, "split-K square launch");
-    }
-    hipError_t e = qrfs::launch_reduce_sf(partial, plan.n_partial_tiles, nB, R, sf, sf_stderr,
-                                          stream_);
+    hipError_t e =
+        plan.ksplit > 1
+            ? qrfs::launch_split_sf(phi, plan.ksplit, R, nB, partial, plan.n_partial_tiles, sf,
+                                    sf_stderr, stream_)
+            : qrfs::launch_reduce_sf(partial, plan.n_partial_tiles, nB, R, sf, sf_stderr, stream_);
     if (e != hipSuccess) return hip_fail(e, "reduction launch");
     s->index += (uint64_t)(n_sets * K);
     return ok();
@@ -1283,12 +1282,11 @@ qrfs_status sf_sets_enqueue(const qrfs::SfPlan& plan, char* base, int64_t K, con
     a.kspan = plan.kspan;
     a.phi_part = phi;
     if ((st = run_sum(precision, qrfs::BASIS_DIFF, qrfs::EPI_SFSUM, a, n_sets, stream))) return st;
-    if (plan.ksplit > 1) {
-        hipError_t e = qrfs::launch_sfsum_rows(phi, plan.ksplit, R, nB, partial, stream);
-        if (e != hipSuccess) return hip_fail(e, "split-K square launch");
-    }
-    hipError_t e = qrfs::launch_reduce_sf(partial, plan.n_partial_tiles, nB, R, sf, sf_stderr,
-                                          stream);
+    hipError_t e =
+        plan.ksplit > 1
+            ? qrfs::launch_split_sf(phi, plan.ksplit, R, nB, partial, plan.n_partial_tiles, sf,
+                                    sf_stderr, stream)
+            : qrfs::launch_reduce_sf(partial, plan.n_partial_tiles, nB, R, sf, sf_stderr, stream);
     if (e != hipSuccess) return hip_fail(e, "reduction launch");
     return QRFS_OK;
 }

@@ -186,10 +186,10 @@ hipError_t launch_set_sf(int64_t n_sets, int64_t K, const double* fx, const doub
                          const double* w, int64_t nB, const double* bx, const double* by,
                          double* S, hipStream_t st);
 
-// squares of the K-range partial sums, summed per column over blocks of
-// rows: partial[ceil(R/256)][P][2]
-hipError_t launch_sfsum_rows(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
-                             hipStream_t st);
+// structure function from the K-range partial sums phi[ksplit][R][P]; uses
+// partial[n_tiles = ceil(R/64)][P][2] where the rows are many
+hipError_t launch_split_sf(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
+                           int64_t n_tiles, double* sf, double* sf_stderr, hipStream_t st);
 
 // Tile of the binary64 contraction of shared sets: rows per wave (16 MR),
 // columns per block (16 NC), row waves that share a basis, and the estimated

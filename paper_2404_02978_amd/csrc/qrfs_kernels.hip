@@ -860,6 +860,18 @@ __global__ void k_reset_counter(unsigned* counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
 }
 
+// Mean square of R values and its standard error from the sums of their squares
+// and fourth powers.
+__device__ __forceinline__ void store_sf(double S2, double S4, int64_t R, double* sf,
+                                         double* sf_stderr, int64_t p) {
+    double n = (double)R;
+    sf[p] = S2 / n;
+    if (sf_stderr) {
+        double var = R > 1 ? (S4 - S2 * S2 / n) / (n - 1.0) : 0.0;
+        sf_stderr[p] = sqrt(var > 0.0 ? var / n : 0.0);
+    }
+}
+
 // ----------------------------------------------------- split-K squares ----
 // Block (row block rb, column tile): 64 rows x 32 columns on 256 threads,
 // RG = 8 VEC row groups of VEC-wide columns.  Adds the K-range partial sums of
@@ -939,6 +951,60 @@ __global__ __launch_bounds__(256) void k_sfsum_rows(const float* __restrict__ ph
     }
 }
 
+// Both steps in one launch for few rows: block b takes columns [VEC b, VEC (b +
+// 1)) of every row, thread t row t, whose ranges are loaded together.  Bound by
+// latency and the launch it saves (300 rows x 8 ranges x 32 columns: a call of
+// 18.4 us takes 17.0); its reads are 16 bytes of each 128-byte line, so from 512
+// rows on the two steps are as fast.
+constexpr int SF_FEW = 512;
+
+template <int VEC>
+__global__ __launch_bounds__(SF_FEW) void k_sf_few(const float* __restrict__ phi, int ksplit,
+                                                   int64_t R, int64_t P, double* __restrict__ sf,
+                                                   double* __restrict__ sf_stderr) {
+    typedef float fvec __attribute__((ext_vector_type(VEC)));
+    constexpr int NW = SF_FEW / 64;
+    static_assert(2 * VEC <= NW, "one wave per sum");
+    __shared__ double red[2 * VEC][SF_FEW], sum[2 * VEC];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t col = (int64_t)blockIdx.x * VEC;
+    double s[2 * VEC] = {};
+    if (t < R) {
+        double v[VEC] = {};
+        for (int k0 = 0; k0 < ksplit; k0 += 8) {
+            fvec f[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                f[i] = fvec(0.0f);
+                if (k0 + i < ksplit) f[i] = *(const fvec*)&phi[((int64_t)(k0 + i) * R + t) * P + col];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) v[e] += (double)f[i][e];
+        }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            s[e] = v[e] * v[e];
+            s[VEC + e] = s[e] * s[e];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 2 * VEC; ++e) red[e][t] = s[e];
+    __syncthreads();
+    // wave e adds the rows of sum e
+    if (wave < 2 * VEC) {
+        double a = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) a += red[wave][64 * i + lane];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+        if (lane == 0) sum[wave] = a;
+    }
+    __syncthreads();
+    if (t < VEC) store_sf(sum[t], sum[VEC + t], R, sf, sf_stderr, col + t);
+}
+
 // ------------------------------------------------------------- reduce ----
 // Long lists of tiles first shrink in place: block b adds tiles
 // [64 b, 64 (b + 1)) of 32 columns (coalesced, 8 loads in flight per thread)
@@ -1006,15 +1072,7 @@ __global__ __launch_bounds__(256) void k_reduce_sf(const double* __restrict__ pa
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        double S2 = r2[0], S4 = r4[0];
-        double n = (double)R;
-        sf[p] = S2 / n;
-        if (sf_stderr) {
-            double var = R > 1 ? (S4 - S2 * S2 / n) / (n - 1.0) : 0.0;
-            sf_stderr[p] = sqrt(var > 0.0 ? var / n : 0.0);
-        }
-    }
+    if (threadIdx.x == 0) store_sf(r2[0], r4[0], R, sf, sf_stderr, p);
 }
 
 // ----------------------------------------------------------- launchers ----
@@ -1457,14 +1515,26 @@ hipError_t launch_batch(int precision, BatchShape shape, bool has_ap, const SumA
     return launch_batch_p<3>(MW, NB, has_ap, inst, items, n_items, counter, n_blocks, st);
 }
 
-hipError_t launch_sfsum_rows(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
-                             hipStream_t st) {
+hipError_t launch_split_sf(const float* phi, int ksplit, int64_t R, int64_t P, double* partial,
+                           int64_t n_tiles, double* sf, double* sf_stderr, hipStream_t st) {
+    const bool vec = P % 4 == 0;
+    if (R <= SF_FEW) {
+        if (vec)
+            hipLaunchKernelGGL(k_sf_few<4>, dim3((unsigned)(P / 4)), dim3(SF_FEW), 0, st, phi,
+                               ksplit, R, P, sf, sf_stderr);
+        else
+            hipLaunchKernelGGL(k_sf_few<1>, dim3((unsigned)P), dim3(SF_FEW), 0, st, phi, ksplit, R,
+                               P, sf, sf_stderr);
+        return hipGetLastError();
+    }
     dim3 g((unsigned)cdiv(R, SF_ROWS), (unsigned)cdiv(P, 32));
-    if (P % 4 == 0)
+    if (vec)
         hipLaunchKernelGGL(k_sfsum_rows<4>, g, dim3(256), 0, st, phi, ksplit, R, P, partial);
     else
         hipLaunchKernelGGL(k_sfsum_rows<1>, g, dim3(256), 0, st, phi, ksplit, R, P, partial);
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_reduce_sf(partial, n_tiles, P, R, sf, sf_stderr, st);
 }
 
 }  // namespace qrfs

@@ -192,3 +192,26 @@ def test_pistons_of_many_rows(q, ctx, precision, K, R, R_block, P):
     ref = oracle.piston(host(fx), host(fy), host(w), px, py, D, d, R, R_block, K=K, seed=3,
                         counter=1)
     check(host(out), ref, TOL[precision])
+
+
+@pytest.mark.parametrize("precision", [1, 3])
+@pytest.mark.parametrize("P", [1, 4, 31, 33, 64])
+@pytest.mark.parametrize("R", [2, 65, 511, 512, 513, 1100])
+def test_structure_function_finish(q, ctx, precision, R, P):
+    """Structure functions from partial sums, with few rows (one launch) and
+    more, columns a multiple of four or not.  Each difference is within 1e-5
+    of the RMS of all of them (the FP32 class's bound), and so are, through
+    its square, the mean and (a seminorm) the standard error."""
+    K = 900
+    fx, fy, w, px, py = problem(ctx, q, K, R, R, P)
+    print(f"finish p{precision} R{R} P{P}", flush=True)
+    sf, err = ctx.diff_piston_structure_sets(K, fx, fy, w, dev(px), dev(py), R, R, rng=q.Rng(4, 6, 0),
+                                             precision=precision)
+    at = [oracle.synthesize(host(fx), host(fy), host(w), x, y, R, R, K=K, seed=4, counter=6)
+          for x, y in ((px, py), (np.zeros(1), np.zeros(1)))]
+    d = at[0] - at[1]
+    e = 1.0e-5 * math.sqrt(np.mean(d * d))
+    top = np.max(np.abs(d), 0)
+    assert np.all(np.abs(host(sf) - (d * d).mean(0)) <= e * (2 * np.abs(d).mean(0) + e))
+    ref = (d * d).std(0, ddof=1) / math.sqrt(R)
+    assert np.all(np.abs(host(err) - ref) <= e * (2 * top + e) / math.sqrt(R - 1))
