@@ -29,13 +29,8 @@ struct qrfs_context {
     int wide_path = 0;          // QRFS_TUNE_WIDE_PATH
     int64_t range_freqs = 2048;  // QRFS_TUNE_RANGE_FREQS
     size_t tile_cap = (size_t)2 << 30;  // QRFS_TUNE_TILE_BYTES
-    // what the calls find out about their points on the device: a ring, so
-    // that a call's answer outlives its kernels; allocated with the context, so
-    // that captured calls may use it
-    qrfs::GridInfo* grids = nullptr;
-    std::atomic<unsigned> next_grid{0};
+    unsigned long long* grids = nullptr;  // the device's ring of answers, see grid_word
 };
-constexpr unsigned kGridRing = 256;
 
 // Scratch of the allocation-free structure-function entry point: a static
 // device array (each GPU the library runs on holds its own copy until the
@@ -43,7 +38,12 @@ constexpr unsigned kGridRing = 256;
 // `scratch` names a host-side stand-in; kernels get the device address that
 // hipGetSymbolAddress returns for the current device, kept per device.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// Behind it, the words in which calls note whether their points form a grid: one
+// ring for calls as they run, one for captured ones, whose words are then not
+// taken by what runs between the replays.
+constexpr unsigned kGridRing = 512;
+static __device__ __align__(256) unsigned char
+    scratch[kScratchBytes + 2 * kGridRing * sizeof(unsigned long long)];
 
 namespace {
 
@@ -105,6 +105,15 @@ qrfs_status sf_sets_enqueue(const qrfs::SfPlan& plan, char* base, int64_t K, con
                             const double* fy, const double* w, int64_t nB, const double* bx,
                             const double* by, int64_t R, int64_t R_block, const qrfs_rng* rng,
                             int32_t precision, double* sf, double* sf_stderr, hipStream_t stream);
+
+// A word of the ring and an id for one call: calls of any thread, stream and
+// context may share a word (see GridWord).
+qrfs::GridWord grid_word(qrfs_context* ctx, bool captured) {
+    static std::atomic<unsigned long long> next[2];
+    const unsigned long long i = next[captured].fetch_add(1);
+    static std::atomic<unsigned long long> id{1};
+    return {ctx->grids + (captured ? kGridRing : 0) + i % kGridRing, id.fetch_add(1)};
+}
 
 void* scratch_ptr(int device) {
     if (device < 0 || device >= kMaxDevices) return nullptr;
@@ -307,15 +316,13 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     a.kspan = sp.kspan;
     a.phi_part = ctx->ws;
     // narrow sets: fields on a regular grid go through its product structure,
-    // if the points are one (the general kernel sees the same answer)
-    // where those are worth its two more launches, 5 us when the points turn out
-    // to be none: a grid saves up to 5/6 of the time in binary64, half in FP32
+    // if the points are one (the general kernel sees the same answer), where
+    // those are worth its launch, 8 us when the points turn out to be none: a
+    // grid saves up to 5/6 of the time in binary64, half in FP32
     const double pad = qrfs::grid_max_pad(precision == QRFS_PREC_FP64, a.R_block);
-    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids && sp.us > (precision == QRFS_PREC_FP64 ? 25.0 : 60.0) && a.P >= 171 &&
+    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids &&
+        sp.us > (precision == QRFS_PREC_FP64 ? 25.0 : 60.0) && a.P >= 171 &&
         a.P <= ((int64_t)1 << 24)) {
-        qrfs::GridInfo* g = ctx->grids + ctx->next_grid.fetch_add(1) % kGridRing;
-        hipError_t e = qrfs::launch_grid_find(a.px, a.py, a.P, pad, g, st);
-        if (e != hipSuccess) return hip_fail(e, "grid launch");
         qrfs::SepArgs b{};
         b.K = a.K;
         b.fx = a.fx;
@@ -331,9 +338,10 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
         b.px = a.px;
         b.py = a.py;
         b.out = a.out;
-        e = qrfs::launch_grid_sum(precision == QRFS_PREC_FP64, b, g, st);
+        a.grid = grid_word(ctx, is_capturing(st));
+        const hipError_t e =
+            qrfs::launch_grid_sum(precision == QRFS_PREC_FP64, b, pad, a.grid, st);
         if (e != hipSuccess) return hip_fail(e, "grid sum launch");
-        a.grid = g;
     }
     qrfs_status s = run_sum(precision, basis, qrfs::EPI_STORE, a, n_sets, st);
     if (s || sp.ksplit == 1) return s;
@@ -557,7 +565,7 @@ qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs 
     }
     if (p.ksplit > 1) {
         hipError_t e = qrfs::launch_split_sum(false, a.phi_part, p.ksplit, a.R * a.P, a.out,
-                                              nullptr, st);
+                                              {}, st);
         if (e != hipSuccess) return hip_fail(e, "partial-sum launch");
     }
     return QRFS_OK;
@@ -682,13 +690,8 @@ qrfs_status qrfs_context_create(qrfs_context** out, int32_t device, size_t works
     if (!c) return fail(QRFS_ERR_OUT_OF_MEMORY, "host allocation of the context");
     c->device = device;
     c->ws_cap = workspace_cap_bytes;
-    {
-        DeviceGuard g(device);
-        if (hipMalloc(&c->grids, kGridRing * sizeof(qrfs::GridInfo)) != hipSuccess) {
-            (void)hipGetLastError();
-            c->grids = nullptr;  // the calls then do without
-        }
-    }
+    if (char* base = (char*)scratch_ptr(device))
+        c->grids = (unsigned long long*)(base + kScratchBytes);
     *out = c;
     return ok();
 }
@@ -721,11 +724,6 @@ qrfs_status qrfs_context_destroy(qrfs_context* ctx) {
             hipError_t e = hipDeviceSynchronize();
             if (e != hipSuccess) st = hip_fail(e, "hipDeviceSynchronize in destroy");
             (void)hipFree(ctx->ws);
-        }
-        if (ctx->grids) {
-            hipError_t e = hipDeviceSynchronize();
-            if (e != hipSuccess) st = hip_fail(e, "hipDeviceSynchronize in destroy");
-            (void)hipFree(ctx->grids);
         }
     }
     delete ctx;

@@ -37,18 +37,18 @@ enum Epilogue : int {
     EPI_SFSUM = 1,  // per column: sum of squares and fourth powers over rows
 };
 
-// What k_grid_find found about a call's points (device memory): the answers of
-// its slices and, when all are 1, the grid: V points per row, x or y varying
-// along a row.
-constexpr int GRID_SLICES = 32;
-constexpr int GRID_MAX_V = 4096;
-struct GridInfo {
-    int V, xfast, slices, pad;
-    int ok[GRID_SLICES];
+// Whether a call's points form a grid, as k_grid_sum found: a word of device
+// memory that only grows (atomic maximum), 2 id where they do and 2 id + 1 where
+// they do not, with an id of its own for each call.  Should another call take
+// the word meanwhile, the answer reads as no, and the general kernel does the
+// work as well.
+constexpr int GRID_MAX_V = 4096;  // longest row
+struct GridWord {
+    unsigned long long* word;  // NULL: not asked
+    unsigned long long id;
 };
-__device__ __forceinline__ bool grid_ok(const GridInfo* g) {
-    const int lane = threadIdx.x & 63;
-    return __all(lane >= g->slices || g->ok[lane < GRID_SLICES ? lane : 0] != 0);
+__device__ __forceinline__ bool grid_done(const GridWord& g) {
+    return g.word && *g.word == 2 * g.id;
 }
 
 // One launch of the fused coefficient x basis contraction over the sets
@@ -83,7 +83,7 @@ struct SumArgs {
     // (gx, gy) = 2 pi u, arguments shifted by a quarter cycle
     int32_t grad;
     double gx, gy;
-    const GridInfo* grid;  // narrow sets: nothing to do where the points are a grid
+    GridWord grid;  // narrow sets: nothing to do where the points are a grid
 };
 
 // The two-phase contraction (wide point sets) over the sets [s.set0,
@@ -213,9 +213,9 @@ struct StoreSplit {
 StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
                        size_t max_bytes);
 // out[i] = sum over ranges of part[range][i], i < n, in order, in binary64;
-// nothing where `grid` (or NULL) is one
+// nothing where the points are a grid
 hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, void* out,
-                            const GridInfo* grid, hipStream_t st);
+                            GridWord grid, hipStream_t st);
 
 // Row tiles one set occupies in `launch_sum` for a structure function (needed
 // to size the partial-sum buffer), and blocks of one set in any launch.
@@ -245,7 +245,8 @@ hipError_t launch_sample_weights(int scheme, uint64_t s0x, uint64_t s0y, uint64_
 // Sums of Eq. 3 in binary64 over points with product structure, for
 // realisations r < R (sets of R_block).  A time series (launch_series_diff):
 // out[r][p] at o + p s minus the sums at those points plus (dx, dy).  A
-// regular grid (launch_grid_sum): out[r][p] at (px[p], py[p]).
+// regular grid (launch_grid_sum): out[r][p] at (px[p], py[p]), if the points
+// are one, and the answer to that.
 struct SepArgs {
     int64_t K;
     const double* fx;
@@ -268,9 +269,8 @@ hipError_t launch_series_diff(const SepArgs& a, hipStream_t st);
 // largest ratio of padded tile area to points at which a grid is taken in
 // the place of the narrow kernels (0: never)
 double grid_max_pad(bool fp64, int64_t R_block);
-hipError_t launch_grid_find(const double* px, const double* py, int64_t P, double max_pad,
-                            GridInfo* g, hipStream_t st);
-hipError_t launch_grid_sum(bool fp64, const SepArgs& a, const GridInfo* g, hipStream_t st);
+hipError_t launch_grid_sum(bool fp64, const SepArgs& a, double max_pad, GridWord g,
+                           hipStream_t st);
 
 // Frozen-flow temporal structure function (time series of M <= 4096 points).
 constexpr int TEMPORAL_MAX_M = 4096;

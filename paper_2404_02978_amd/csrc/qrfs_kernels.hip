@@ -27,7 +27,7 @@ template <int BASIS, int RB>
 __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) {
     __shared__ double sfx[F64N_KC], sfy[F64N_KC], sw[F64N_KC];
     __shared__ double sC[RB][2 * F64N_KC];
-    if (a.grid && grid_ok(a.grid)) return;  // k_grid_sum did the work
+    if (grid_done(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
     const int64_t ct = (int64_t)blockIdx.x % col_tiles;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
     constexpr int KCN = 64;
     __shared__ double sfx[KCN], sfy[KCN], sw[KCN];
     __shared__ float sC[RB][2 * KCN];
-    if (a.grid && grid_ok(a.grid)) return;  // k_grid_sum did the work
+    if (grid_done(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
     const int64_t ct = (int64_t)blockIdx.x % col_tiles;
@@ -1231,8 +1231,8 @@ SfPlan sf_plan(int precision, int64_t K, int64_t R, int64_t R_block, int64_t P,
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void k_split_sum(const T* __restrict__ part, int ksplit,
                                                    int64_t n, T* __restrict__ out,
-                                                   const GridInfo* __restrict__ grid) {
-    if (grid && grid_ok(grid)) return;  // k_grid_sum did the work
+                                                   GridWord grid) {
+    if (grid_done(grid)) return;  // k_grid_sum did the work
     typedef T tvec __attribute__((ext_vector_type(VEC)));
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
     if (i >= n) return;
@@ -1255,7 +1255,7 @@ __global__ __launch_bounds__(256) void k_split_sum(const T* __restrict__ part, i
 
 template <typename T, int VEC>
 static hipError_t launch_split_sum_t(const void* part, int ksplit, int64_t n, void* out,
-                                     const GridInfo* grid, hipStream_t st) {
+                                     GridWord grid, hipStream_t st) {
     if (n % VEC || ((uintptr_t)out & (sizeof(T) * VEC - 1)))
         return launch_split_sum_t<T, 1>(part, ksplit, n, out, grid, st);
     hipLaunchKernelGGL((k_split_sum<T, VEC>), dim3((unsigned)cdiv(n, 256 * VEC)), dim3(256), 0, st,
@@ -1264,7 +1264,7 @@ static hipError_t launch_split_sum_t(const void* part, int ksplit, int64_t n, vo
 }
 
 hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, void* out,
-                            const GridInfo* grid, hipStream_t st) {
+                            GridWord grid, hipStream_t st) {
     return fp64 ? launch_split_sum_t<double, 2>(part, ksplit, n, out, grid, st)
                 : launch_split_sum_t<float, 4>(part, ksplit, n, out, grid, st);
 }

@@ -43,10 +43,12 @@ namespace qrfs {
 // nothing cancels afterwards.
 constexpr int SEP_KC = 128;  // frequencies a wave stages at a time
 
-template <int MU, int NV, int WV>
+constexpr int sep_stage(bool diff) { return diff ? 8 : 4; }  // doubles per staged frequency
+
+template <bool DIFF, int MU, int NV, int WV>
 struct SepSmem {
     static constexpr int TILE = 256 * MU * NV;
-    static constexpr int STAGE = WV * SEP_KC * 8;
+    static constexpr int STAGE = WV * SEP_KC * sep_stage(DIFF);
     static constexpr int TREE = (WV / 2) * TILE;
     // the staged frequencies, then (after the loop) the partial tiles
     __attribute__((aligned(16))) double d[STAGE > TREE ? STAGE : TREE];
@@ -82,7 +84,7 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
     const int64_t kw = ((a.K + 8 * WV - 1) / (8 * WV)) * 8;
     const int64_t kb = wave * kw;
     const int64_t ke = kb + kw < a.K ? kb + kw : a.K;
-    constexpr int FS = DIFF ? 8 : 4;  // doubles per staged frequency
+    constexpr int FS = sep_stage(DIFF);
     double* st = sm + wave * SEP_KC * FS;
     for (int64_t k0 = kb; k0 < ke; k0 += SEP_KC) {
         {
@@ -138,10 +140,14 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
 #pragma unroll
             for (int m = 0; m < MU; ++m) {
                 if (DIFF && m > 0) {
-                    turn(src[2], sn, cs);
-                } else {
-                    sincos2pi_reduced(frac_centered(fma(f.x, rx[m], f.y * ry[m])), sn, cs);
+                    // (B, A) = (Im, Re) of c e^(-i phase), turned back
+                    A[m] = A[m - 1];
+                    B[m] = -B[m - 1];
+                    turn(src[2], B[m], A[m]);
+                    B[m] = -B[m];
+                    continue;
                 }
+                sincos2pi_reduced(frac_centered(fma(f.x, rx[m], f.y * ry[m])), sn, cs);
                 A[m] = fma(c.x, cs, c.y * sn);
                 B[m] = fma(c.y, cs, -(c.x * sn));
             }
@@ -198,7 +204,7 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
 
 template <int WV>
 __global__ __launch_bounds__(64 * WV) void k_series_diff(SepArgs a, int ut, int vt) {
-    __shared__ SepSmem<2, 2, WV> sm;
+    __shared__ SepSmem<true, 2, 2, WV> sm;
     const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
     const int64_t tiles = (int64_t)ut * vt;
     const int64_t r = a.r0 + (int64_t)blockIdx.x / tiles;
@@ -241,77 +247,60 @@ hipError_t launch_series_diff(const SepArgs& args, hipStream_t st) {
 }
 
 // ------------------------------------------------------- regular grids ----
-// Whether the points form a grid, decided on the device from their values in
-// every call (the host only has pointers): V = length of the first run of
-// equal y (x varies fastest) or equal x, and every point p equal to
-// (x[p mod V], y[p - p mod V]) (or the other way round), bit for bit up to the
-// sign of zero.  Each block checks a slice and all find V from the first
-// points; consumers combine the slices' answers (grid_ok).
+// Whether the points form a grid is decided on the device from their values in
+// every call (the host only has pointers).  V = length of the first run of
+// equal y (x varies fastest) or equal x, which every block finds from the first
+// points; then every point p must equal (x[p mod V], y[p - p mod V]) (or the
+// other way round), bit for bit up to the sign of zero: each tile of the first
+// realisation checks its own points.  Where one fails, the general kernel,
+// which follows, does the work (a kernel of its own that checked all points
+// first took 6 us more).
 // max_pad: largest ratio of padded tile area to points that is taken.
 // Rows and columns are padded to whole units: 16, or 32 in the tiles of 64 x 64
 // that grids of at least 4096 points use.
 __host__ __device__ constexpr int grid_unit(int64_t P) { return P >= 4096 ? 32 : 16; }
 
-__global__ __launch_bounds__(1024) void k_grid_find(const double* __restrict__ px,
-                                                    const double* __restrict__ py, int64_t P,
-                                                    double max_pad, GridInfo* __restrict__ g) {
-    __shared__ int s_run[2], s_bad;
-    const int tid = threadIdx.x;
-    if (tid < 2) s_run[tid] = GRID_MAX_V + 1;
-    if (tid == 0) s_bad = 0;
+// The whole block calls it (P > 1).
+__device__ __forceinline__ bool grid_shape(const double* __restrict__ px,
+                                           const double* __restrict__ py, int64_t P,
+                                           double max_pad, int& V, int& xfast, int* s_run) {
+    const int tid = threadIdx.x, n = (int)P;
+    if (tid == 0) *s_run = GRID_MAX_V + 1;
     __syncthreads();
-    const double x0 = px[0], y0 = py[0];
-    int ry = GRID_MAX_V + 1, rx = GRID_MAX_V + 1;
-#pragma unroll
-    for (int i = GRID_MAX_V / 1024 - 1; i >= 0; --i) {
-        const int p = 1 + tid + 1024 * i;
-        if (p < P) {
-            if (py[p] != y0) ry = p;
-            if (px[p] != x0) rx = p;
-        }
+    xfast = py[1] == py[0] ? 1 : 0;
+    const double* q = xfast ? py : px;
+    const double q0 = q[0];
+    for (int base = 1; base < n && base <= GRID_MAX_V; base += (int)blockDim.x) {
+        const int p = base + tid;
+        const unsigned long long m = __ballot(p < n && q[p < n ? p : 0] != q0);
+        if (m && (tid & 63) == 0) atomicMin(s_run, base + tid + __ffsll(m) - 1);
+        __syncthreads();
+        const bool found = *s_run <= GRID_MAX_V;
+        __syncthreads();
+        if (found) break;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        ry = min(ry, __shfl_xor(ry, off));
-        rx = min(rx, __shfl_xor(rx, off));
-    }
-    if ((tid & 63) == 0) {
-        atomicMin(&s_run[0], ry);
-        atomicMin(&s_run[1], rx);
-    }
-    __syncthreads();
-    const int xfast = s_run[0] > 1 ? 1 : 0;
-    const int V = xfast ? s_run[0] : s_run[1];
-    const int n = (int)P;
-    bool ok = V > 1 && V <= GRID_MAX_V && n % V == 0;
-    if (ok) {
-        const int unit = grid_unit(P);
-        const double u = (double)((n / V + unit - 1) / unit * unit);
-        ok = u * (double)((V + unit - 1) / unit * unit) <= max_pad * (double)P;
-    }
-    if (ok) {
-        bool bad = false;
-        for (int p = (int)blockIdx.x * 1024 + tid; p < n; p += (int)gridDim.x * 1024) {
-            const int v = p % V, u = p - v;
-            bad |= !(px[p] == px[xfast ? v : u]) || !(py[p] == py[xfast ? u : v]);
-        }
-        if (bad) s_bad = 1;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        g->ok[blockIdx.x] = ok && !s_bad ? 1 : 0;
-        if (blockIdx.x == 0) {
-            g->V = ok ? V : 1;
-            g->xfast = xfast;
-            g->slices = (int)gridDim.x;
-        }
-    }
+    V = *s_run;
+    if (V < 2 || V > GRID_MAX_V || n % V) return false;
+    const int unit = grid_unit(P);
+    const double u = (double)((n / V + unit - 1) / unit * unit);
+    return u * (double)((V + unit - 1) / unit * unit) <= max_pad * (double)P;
 }
 
 template <typename T, int MU, int NV, int WV>
 __device__ __forceinline__ void grid_tile(double* sm, const SepArgs& a, int64_t r, int U, int V,
-                                          int xfast, int u0, int v0) {
+                                          int xfast, int u0, int v0, const GridWord& g) {
     const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
+    if (r == 0) {
+        bool bad = false;
+        for (int e = threadIdx.x; e < 256 * MU * NV; e += 64 * WV) {
+            const int u = u0 + e / (16 * NV), v = v0 + e % (16 * NV);
+            if (u < U && v < V) {
+                const int p = u * V + v, head = u * V;
+                bad |= !(a.px[p] == a.px[xfast ? v : head]) || !(a.py[p] == a.py[xfast ? head : v]);
+            }
+        }
+        if (__any(bad) && lane == 0) atomicMax(g.word, 2 * g.id + 1);
+    }
     double rx[MU], ry[MU], cx[NV], cy[NV];
 #pragma unroll
     for (int m = 0; m < MU; ++m) {
@@ -334,16 +323,17 @@ __device__ __forceinline__ void grid_tile(double* sm, const SepArgs& a, int64_t 
     });
 }
 
-// Sums on a grid found by k_grid_find: blocks take (realisation, tile) in
-// turn, tiles at the edges in half the size where that holds them; nothing to
-// do where the points are no grid (the general kernel, which follows, then
-// does the work).
+// Sums on a grid: blocks take (realisation, tile) in turn, tiles at the edges in
+// half the size where that holds them.
 template <typename T, int MU, int NV, int WV>
-__global__ __launch_bounds__(64 * WV) void k_grid_sum(SepArgs a, const GridInfo* __restrict__ g) {
-    __shared__ SepSmem<MU, NV, WV> sm;
-    if (!grid_ok(g)) return;
+__global__ __launch_bounds__(64 * WV) void k_grid_sum(SepArgs a, double max_pad, GridWord g) {
+    __shared__ SepSmem<false, MU, NV, WV> sm;
+    __shared__ int s_run;
+    int V, xfast;
+    const bool ok = grid_shape(a.px, a.py, a.P, max_pad, V, xfast, &s_run);
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicMax(g.word, 2 * g.id + (ok ? 0 : 1));
+    if (!ok) return;
     constexpr int HU = MU > 1 ? MU / 2 : 1, HV = NV > 1 ? NV / 2 : 1;
-    const int V = g->V, xfast = g->xfast;
     const int U = (int)(a.P / V);
     const int ut = (U + 16 * MU - 1) / (16 * MU), vt = (V + 16 * NV - 1) / (16 * NV);
     const int64_t tiles = (int64_t)ut * vt, n = a.R * tiles;
@@ -353,13 +343,13 @@ __global__ __launch_bounds__(64 * WV) void k_grid_sum(SepArgs a, const GridInfo*
         const int u0 = (tile / vt) * 16 * MU, v0 = (tile % vt) * 16 * NV;
         const bool hu = HU < MU && U - u0 <= 16 * HU, hv = HV < NV && V - v0 <= 16 * HV;
         if (hu && hv)
-            grid_tile<T, HU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+            grid_tile<T, HU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0, g);
         else if (hu)
-            grid_tile<T, HU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+            grid_tile<T, HU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0, g);
         else if (hv)
-            grid_tile<T, MU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+            grid_tile<T, MU, HV, WV>(sm.d, a, r, U, V, xfast, u0, v0, g);
         else
-            grid_tile<T, MU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0);
+            grid_tile<T, MU, NV, WV>(sm.d, a, r, U, V, xfast, u0, v0, g);
         __syncthreads();  // the next item reuses the stage
     }
 }
@@ -371,39 +361,36 @@ double grid_max_pad(bool fp64, int64_t R_block) {
     return R_block == 1 ? 2.0 : 0.0;
 }
 
-hipError_t launch_grid_find(const double* px, const double* py, int64_t P, double max_pad,
-                            GridInfo* g, hipStream_t st) {
-    const int64_t nb = (P + 4095) / 4096;
-    hipLaunchKernelGGL(k_grid_find, dim3((unsigned)(nb < GRID_SLICES ? nb : GRID_SLICES)),
-                       dim3(1024), 0, st, px, py, P, max_pad, g);
-    return hipGetLastError();
-}
-
 template <typename T>
-static hipError_t launch_grid_sum_t(const SepArgs& a, const GridInfo* g, hipStream_t st) {
+static hipError_t launch_grid_sum_t(const SepArgs& a, double max_pad, GridWord g,
+                                    hipStream_t st) {
     // tiles of 64 x 64 spare sines and cosines on the larger grids (13 cycles
     // of a SIMD per 64 terms, 17 in tiles of 32 x 32, 21 in 32 x 16); with few
     // realisations the 16 waves of a block split the frequencies, and where
-    // tiles of 32 x 32 leave half the compute units idle they are halved
+    // tiles of 32 x 32 leave half the compute units idle they are halved.  1024
+    // blocks at most, 2 to 4 per compute unit: where the points are no grid every
+    // block only starts and ends (8192 of them took 30 us)
     const int64_t items = a.R * ((a.P + 1023) / 1024);
     if (grid_unit(a.P) == 32 && a.R * ((a.P + 4095) / 4096) >= 512)
         hipLaunchKernelGGL((k_grid_sum<T, 4, 4, 4>),
-                           dim3((unsigned)(a.R * (a.P / 4096) < 8192 ? a.R * (a.P / 4096) : 8192)),
-                           dim3(256), 0, st, a, g);
+                           dim3((unsigned)(a.R * (a.P / 4096) < 1024 ? a.R * (a.P / 4096) : 1024)),
+                           dim3(256), 0, st, a, max_pad, g);
     else if (items >= 512)
-        hipLaunchKernelGGL((k_grid_sum<T, 2, 2, 4>), dim3((unsigned)(items < 8192 ? items : 8192)),
-                           dim3(256), 0, st, a, g);
+        hipLaunchKernelGGL((k_grid_sum<T, 2, 2, 4>), dim3((unsigned)(items < 1024 ? items : 1024)),
+                           dim3(256), 0, st, a, max_pad, g);
     else if (items > 128)
         hipLaunchKernelGGL((k_grid_sum<T, 2, 2, 16>), dim3((unsigned)items), dim3(1024), 0, st, a,
-                           g);
+                           max_pad, g);
     else
         hipLaunchKernelGGL((k_grid_sum<T, 2, 1, 16>), dim3((unsigned)(2 * items)), dim3(1024), 0,
-                           st, a, g);
+                           st, a, max_pad, g);
     return hipGetLastError();
 }
 
-hipError_t launch_grid_sum(bool fp64, const SepArgs& a, const GridInfo* g, hipStream_t st) {
-    return fp64 ? launch_grid_sum_t<double>(a, g, st) : launch_grid_sum_t<float>(a, g, st);
+hipError_t launch_grid_sum(bool fp64, const SepArgs& a, double max_pad, GridWord g,
+                           hipStream_t st) {
+    return fp64 ? launch_grid_sum_t<double>(a, max_pad, g, st)
+                : launch_grid_sum_t<float>(a, max_pad, g, st);
 }
 
 }  // namespace qrfs
