@@ -94,7 +94,10 @@ typedef struct qrfs_context qrfs_context;
  * (0: no bound).  A call whose workspace would exceed it fails with
  * QRFS_ERR_OUT_OF_MEMORY before enqueueing anything; the two-phase kernel
  * cuts its coefficient tiles into pieces that fit the cap when it can (at
- * least one 256-row block of one set).  Batches allocate their own buffers
+ * least one 256-row block of one set).  Fields, pistons and tilts of too few
+ * rows and points to fill the device use up to 256 MiB for partial sums of
+ * frequency ranges; where the cap or the memory has no room for them, and in
+ * captured calls, they do without.  Batches allocate their own buffers
  * (qrfs_batch_create) and are not bounded by it.
  * Errors: out NULL; device out of range; no HIP device (QRFS_ERR_DEVICE). */
 QRFS_API qrfs_status qrfs_context_create(qrfs_context** out, int32_t device,
@@ -105,13 +108,16 @@ QRFS_API qrfs_status qrfs_context_destroy(qrfs_context* ctx);
 /* Launch policy of a context (no paper passage: an implementation knob).
  * QRFS_TUNE_WIDE_PATH selects how FP32 / split-BF16 / BF16x6 phase fields
  * and pistons (qrfs_synthesize_phase, qrfs_piston, qrfs_diff_piston) are
- * contracted: 0 (default) lets the library choose, 1 always uses the fused
+ * contracted: 0 (default) lets the library choose by the estimated times of
+ * both (in captured calls by the size alone), 1 always uses the fused
  * kernel (coefficients drawn in registers per column tile), 2 uses the
  * two-phase kernel (coefficients drawn once into workspace tiles of at most
  * 2 GiB, then 256 x 256 MFMA tiles) whenever the output fits it.
  * QRFS_TUNE_RANGE_FREQS sets how many frequencies the two-phase kernel
  * sums in FP32 before adding them into the output in FP32-class precisions
- * (default 2048, rounded to whole chunks; 0 restores the default).
+ * (default 2048, rounded to whole chunks; 0 restores the default); where the
+ * library chooses that kernel for a problem that does not fill the device, it
+ * takes fewer, down to 64, and never more.
  * QRFS_TUNE_TILE_BYTES caps the workspace the two-phase kernel stages its
  * coefficient tiles in (default 2 GiB, 0 restores it); larger problems are
  * cut into pieces of whole sets, or of 256-row blocks of one set.
@@ -222,15 +228,20 @@ typedef struct {
 
 /* Arithmetic of the sums:
  *   FP64        FP64 range reduction, FP64 sincos, FP64 Box-Muller and
- *               FP64 accumulation (vector ALU); output double.
+ *               FP64 accumulation (vector ALU and, for shared sets, time
+ *               series and regular grids, FP64 matrix instructions); output
+ *               double.
  *   FP32        FP64 range reduction of 2 pi f.x, FP32 sincos and
  *               Box-Muller, FP32 matrix-core (MFMA) contraction with FP32
  *               accumulation, folded into a second FP32 accumulator every
  *               32 frequencies (the two-phase kernel for wide point sets
- *               adds into the output every 2048); output float.
+ *               adds into the output every 2048, see
+ *               QRFS_TUNE_RANGE_FREQS); output float.
  *   (All FP32-class precisions sum sets of at most 8 realisations on the
  *   vector ALU with this FP32 arithmetic: a matrix-core tile needs 32 rows.
- *   The split-BF16 and BF16x6 results are then those FP32 sums.  Their
+ *   The split-BF16 and BF16x6 results are then those FP32 sums.  Fields of
+ *   R_block = 1 whose points form a regular grid, which is found on the
+ *   device, may be summed in binary64 through its rows and columns.  Their
  *   per-aperture filter of Eq. 7 (qrfs_piston, qrfs_tilt) is evaluated to
  *   binary32 accuracy like the basis it scales (the J1 of qrfs_weights'
  *   FP32-class weights); FP64 evaluates it in binary64.)

@@ -1022,7 +1022,10 @@ qrfs_status qrfs_temporal_sf(qrfs_context* ctx, int64_t R, int64_t M, int32_t pr
     DeviceGuard g(ctx->device);
     if (!g.okay) return fail(QRFS_ERR_DEVICE, "cannot select device %d", ctx->device);
     int rows = qrfs::TEMPORAL_ROWS;
-    if (ctx->ws_cap && align256((size_t)cdiv(R, rows) * M * 2 * sizeof(double)) > ctx->ws_cap)
+    // the longer blocks halve the workspace where it is capped, or cannot grow
+    const size_t bytes = align256((size_t)cdiv(R, rows) * M * 2 * sizeof(double));
+    if ((ctx->ws_cap && bytes > ctx->ws_cap) ||
+        (bytes > ctx->ws_size && is_capturing((hipStream_t)stream)))
         rows = qrfs::TEMPORAL_ROWS_CAPPED;
     const int64_t nb = cdiv(R, rows);
     qrfs_status st = ensure_workspace(ctx, align256((size_t)nb * M * 2 * sizeof(double)));
