@@ -15,7 +15,7 @@ namespace qrfs {
 // 1/128 revolution, by the first terms of the series for 1/8.  Over all 2^23 u:
 // radius within 2.2e-16 (relative), sine and cosine within 1.7e-16 of the exact
 // values, at ~50 vector instructions a pair in the place of ~85.  1e5 realisations
-// x 4096 frequencies x 32 baselines: 2.11 ms, 2.70 without the tables.
+// x 4096 frequencies x 32 baselines: 2.07 ms, 2.70 without the tables.
 static __device__ __attribute__((aligned(16))) const double kGaussTab[64][4] = {
     {1.9844961240310077, 1.3707300802357807,
      0.049067674327418015, 0.9987954562051724},
@@ -239,9 +239,17 @@ struct FmSmem {
     static constexpr int TREE = (FM_WAVES / 2) * 256 * MR * NC;  // half the waves' tiles
 };
 
+// Registers for two blocks per compute unit where their sums leave room (32 rows
+// x 64 columns per wave do not: 20 to 30 % slower with the spills).
+template <int MR, int NC, int WR>
+constexpr int fm_min_waves() {
+    return WR >= 2 && MR * NC <= 4 ? 4 : 2;
+}
+
 template <int BASIS, int EPI, int MR, int NC, int WR, int CSRC>
-__global__ __launch_bounds__(64 * FM_WAVES) void k_sum_fm(SumArgs a, int64_t row_tiles,
-                                                          int64_t col_tiles) {
+__global__ __launch_bounds__(64 * FM_WAVES) __attribute__((
+    amdgpu_waves_per_eu(fm_min_waves<MR, NC, WR>(), 8))) void
+k_sum_fm(SumArgs a, int64_t row_tiles, int64_t col_tiles) {
     using S = FmSmem<MR, NC>;
     constexpr int NT = S::NT, WK = FM_WAVES / WR, GT = 64 * WR;
     constexpr int NB = S::BASIS * WK > S::TREE ? S::BASIS * WK : S::TREE;

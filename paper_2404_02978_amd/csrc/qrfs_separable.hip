@@ -31,8 +31,8 @@ namespace qrfs {
 // matrix instructions (64 cycles each) and 4 sine / cosine pairs (~35
 // instructions of 4 cycles), in a series 2 pairs and 2 rotations by turns that
 // are staged with the frequency.  2000 realisations x 1936 frequencies x 1024
-// differential samples: 0.50 ms (the matrix instructions alone 0.22 ms at
-// 73.7 TFLOP/s; 0.60 with 4 pairs), against 9.4 ms for both telescopes in the
+// differential samples: 0.46 ms (the matrix instructions alone 0.22 ms at
+// 73.7 TFLOP/s; 0.50 with 3 waves per SIMD, 0.60 with 4 pairs), against 9.4 ms for both telescopes in the
 // general kernel.
 //
 // DIFF: the sums at x minus the sums at x + delta (the differential piston
@@ -203,7 +203,8 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
 }
 
 template <int WV>
-__global__ __launch_bounds__(64 * WV) void k_series_diff(SepArgs a, int ut, int vt) {
+__global__ __launch_bounds__(64 * WV) __attribute__((
+    amdgpu_waves_per_eu(4, 8))) void k_series_diff(SepArgs a, int ut, int vt) {
     __shared__ SepSmem<true, 2, 2, WV> sm;
     const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
     const int64_t tiles = (int64_t)ut * vt;
@@ -325,8 +326,12 @@ __device__ __forceinline__ void grid_tile(double* sm, const SepArgs& a, int64_t 
 
 // Sums on a grid: blocks take (realisation, tile) in turn, tiles at the edges in
 // half the size where that holds them.
+// Registers for 4 waves per SIMD, 2 in the largest tiles (700 realisations of 64
+// x 64 points x 500 frequencies: 225 us with 2 and 1, 171 so).
 template <typename T, int MU, int NV, int WV>
-__global__ __launch_bounds__(64 * WV) void k_grid_sum(SepArgs a, double max_pad, GridWord g) {
+__global__ __launch_bounds__(64 * WV) __attribute__((
+    amdgpu_waves_per_eu(MU * NV >= 16 ? 2 : 4, 8))) void k_grid_sum(SepArgs a, double max_pad,
+                                                                    GridWord g) {
     __shared__ SepSmem<false, MU, NV, WV> sm;
     __shared__ int s_run;
     int V, xfast;
