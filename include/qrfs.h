@@ -95,9 +95,12 @@ typedef struct qrfs_context qrfs_context;
  * QRFS_ERR_OUT_OF_MEMORY before enqueueing anything; the two-phase kernel
  * cuts its coefficient tiles into pieces that fit the cap when it can (at
  * least one 256-row block of one set).  Fields, pistons and tilts of too few
- * rows and points to fill the device use up to 256 MiB for partial sums of
- * frequency ranges; where the cap or the memory has no room for them, and in
- * captured calls, they do without.  Batches allocate their own buffers
+ * rows and points to fill the device use scratch beside the workspace, within
+ * the same bound: up to 256 MiB for partial sums of frequency ranges, and the
+ * two-phase kernel's tiles.  Where the cap or the memory has no room for it, and
+ * in captured calls, they do without; it grows without waiting for the device
+ * and never replaces the workspace, which captured structure functions, time
+ * series and large screens hold.  Batches allocate their own buffers
  * (qrfs_batch_create) and are not bounded by it.
  * Errors: out NULL; device out of range; no HIP device (QRFS_ERR_DEVICE). */
 QRFS_API qrfs_status qrfs_context_create(qrfs_context** out, int32_t device,

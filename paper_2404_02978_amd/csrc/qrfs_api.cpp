@@ -29,6 +29,17 @@ struct qrfs_context {
     int wide_path = 0;          // QRFS_TUNE_WIDE_PATH
     int64_t range_freqs = 2048;  // QRFS_TUNE_RANGE_FREQS
     size_t tile_cap = (size_t)2 << 30;  // QRFS_TUNE_TILE_BYTES
+    // What eager calls alone use: partial sums of frequency ranges, and the tiles
+    // of two-phase problems that do not fill the device.  In blocks of its own, so
+    // that such a call never replaces the workspace, which a captured graph may
+    // hold.  Every block is at least twice as long as the one before, which is kept
+    // until destroy: work in flight may still use it, and to free it would wait for
+    // the device.
+    void* scratch = nullptr;
+    size_t scratch_size = 0;
+    size_t scratch_total = 0;  // with the outgrown blocks
+    void* outgrown[40] = {};
+    int n_outgrown = 0;
     unsigned long long* grids = nullptr;  // the device's ring of answers, see grid_word
 };
 
@@ -127,6 +138,51 @@ void* scratch_ptr(int device) {
         if (!aligned8(p)) return fail(QRFS_ERR_INVALID_ARG, "%s is not 8-byte aligned", #p); \
     } while (0)
 
+// Frees the scratch blocks; nothing may be in flight.
+void free_scratch(qrfs_context* ctx) {
+    for (int i = 0; i < ctx->n_outgrown; ++i) (void)hipFree(ctx->outgrown[i]);
+    if (ctx->scratch) (void)hipFree(ctx->scratch);
+    ctx->scratch = nullptr;
+    ctx->scratch_size = ctx->scratch_total = 0;
+    ctx->n_outgrown = 0;
+}
+
+// Longest scratch block that the context's cap has room for.
+size_t scratch_room(const qrfs_context* ctx) {
+    if (!ctx->ws_cap) return SIZE_MAX;
+    const size_t held = ctx->ws_size + ctx->scratch_total;
+    const size_t room = held < ctx->ws_cap ? ctx->ws_cap - held : 0;
+    return room > ctx->scratch_size ? room : ctx->scratch_size;
+}
+
+// Scratch of at least `bytes` for an eager call, or NULL where the cap or the
+// memory has no room: the caller does without.  Waits for nothing.
+char* scratch_block(qrfs_context* ctx, size_t bytes) {
+    if (bytes <= ctx->scratch_size) return (char*)ctx->scratch;
+    if (bytes > scratch_room(ctx) || ctx->n_outgrown == 40) return nullptr;
+    size_t sz = (size_t)1 << 20;
+    if (sz < 2 * ctx->scratch_size) sz = 2 * ctx->scratch_size;
+    if (sz < bytes) sz = bytes;
+    if (sz > scratch_room(ctx)) sz = bytes;
+    // this stream is not being captured, but another may be, here or in another
+    // thread: an allocation is no part of that
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, sz);
+    if (e != hipSuccess && sz > bytes) e = hipMalloc(&p, sz = bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (ctx->scratch) ctx->outgrown[ctx->n_outgrown++] = ctx->scratch;
+    ctx->scratch = p;
+    ctx->scratch_size = sz;
+    ctx->scratch_total += sz;
+    return (char*)p;
+}
+
 qrfs_status ensure_workspace(qrfs_context* ctx, size_t bytes) {
     if (bytes <= ctx->ws_size) return QRFS_OK;
     if (ctx->ws_cap && bytes > ctx->ws_cap)
@@ -139,7 +195,14 @@ qrfs_status ensure_workspace(qrfs_context* ctx, size_t bytes) {
     ctx->ws_size = 0;
     size_t sz = bytes < ((size_t)1 << 20) ? ((size_t)1 << 20) : bytes;
     if (ctx->ws_cap && sz > ctx->ws_cap) sz = bytes;
+    // the workspace comes first: the scratch gives way to it
+    if (ctx->ws_cap && sz + ctx->scratch_total > ctx->ws_cap) free_scratch(ctx);
     e = hipMalloc(&ctx->ws, sz);
+    if (e != hipSuccess && ctx->scratch) {
+        (void)hipGetLastError();
+        free_scratch(ctx);
+        e = hipMalloc(&ctx->ws, sz);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(QRFS_ERR_OUT_OF_MEMORY, "workspace of %zu bytes: %s", sz, hipGetErrorString(e));
@@ -298,23 +361,23 @@ bool is_capturing(hipStream_t st) {
 constexpr size_t kSplitCap = (size_t)256 << 20;
 
 // Stored sums in the fused kernels.  Where their tiles leave compute units
-// idle, K is cut into ranges whose partial sums go through the workspace; not
+// idle, K is cut into ranges whose partial sums go through the scratch; not
 // beyond the context's cap, and not while the stream is being captured (a
-// graph must not hold a workspace that a later call may replace): then one
-// range, which needs none.
+// graph must not hold memory that a later call may replace): then one range,
+// which needs none.
 qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a, int64_t n_sets,
                       hipStream_t st) {
-    size_t room = kSplitCap;
-    if (ctx->ws_cap && ctx->ws_cap < room) room = ctx->ws_cap;
+    const size_t room = scratch_room(ctx) < kSplitCap ? scratch_room(ctx) : kSplitCap;
     qrfs::StoreSplit sp =
         qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, room);
+    char* part = nullptr;
     if (sp.ksplit > 1) {
-        if (is_capturing(st) || ensure_workspace(ctx, sp.bytes) != QRFS_OK)
-            sp = {1, a.K, 0, 0.0};
+        part = is_capturing(st) ? nullptr : scratch_block(ctx, sp.bytes);
+        if (!part) sp = {1, a.K, 0, 0.0};
     }
     a.ksplit = sp.ksplit;
     a.kspan = sp.kspan;
-    a.phi_part = ctx->ws;
+    a.phi_part = part;
     // narrow sets: fields on a regular grid go through its product structure,
     // if the points are one (the general kernel sees the same answer), where
     // those are worth its launch, 8 us when the points turn out to be none: a
@@ -345,7 +408,7 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     }
     qrfs_status s = run_sum(precision, basis, qrfs::EPI_STORE, a, n_sets, st);
     if (s || sp.ksplit == 1) return s;
-    hipError_t e = qrfs::launch_split_sum(precision == QRFS_PREC_FP64, ctx->ws, sp.ksplit,
+    hipError_t e = qrfs::launch_split_sum(precision == QRFS_PREC_FP64, part, sp.ksplit,
                                           a.R * a.P, a.out, a.grid, st);
     if (e != hipSuccess) return hip_fail(e, "partial-sum launch");
     return QRFS_OK;
@@ -363,7 +426,7 @@ struct WidePlan {
     int ksplit;          // frequency ranges (one piece only) and
     int64_t split_ch;    // their chunks
     size_t part_bytes;   // of partial sums
-    size_t bytes() const { return tile_bytes + 256 + scale_bytes + part_bytes; }
+    size_t bytes() const { return tile_bytes + 256 + scale_bytes; }  // beside the partial sums
 };
 
 // ksplit: frequency ranges asked for; fewer where their partial sums exceed
@@ -499,15 +562,16 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int6
     WidePlan p;
     if (best > 0.9 * fused || wide_plan(ctx, precision, K, P, R, R_block, *ksplit, p) != QRFS_OK)
         return false;
-    // the fused kernel needs no workspace: it stays where this one's would
-    // exceed the cap
-    return !(ctx->ws_cap && p.bytes() > ctx->ws_cap);
+    // the fused kernel needs no memory: it stays where this one's would exceed
+    // the cap
+    return p.bytes() + p.part_bytes <= scratch_room(ctx);
 }
 
 // Two-phase contraction (EPI_STORE) over all sets: per piece, the
-// coefficient tiles, then one contraction launch (FP32-class precisions sum
-// ranges of ctx->range_freqs frequencies in FP32 and add each into the
-// output; split-BF16 uses a single range).
+// coefficient tiles, then one contraction launch, which sums ranges of
+// wide_range frequencies in FP32 and adds each into the output.  The tiles of
+// problems that fill the device, and of any when this kernel is asked for, lie in
+// the workspace; all else in the scratch.
 qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a,
                      int64_t n_sets, int ksplit, hipStream_t st) {
     WidePlan p;
@@ -515,15 +579,25 @@ qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs 
     if (s) return s;
     const int KCH = p.KCH;
     const int64_t nch = p.nch, sets_piece = p.sets_piece, rows_piece = p.rows_piece;
-    s = ensure_workspace(ctx, p.bytes());
-    if (s) return s;
-    double* ascale = (double*)((char*)ctx->ws + p.tile_bytes + 256);
+    char *base, *part;
+    if (ctx->wide_path == 2 || wide_fills(a.P, a.R, a.R_block)) {
+        s = ensure_workspace(ctx, p.bytes());
+        if (s) return s;
+        base = (char*)ctx->ws;
+        part = p.ksplit > 1 ? scratch_block(ctx, p.part_bytes) : nullptr;
+    } else {
+        base = scratch_block(ctx, p.bytes() + p.part_bytes);
+        part = base + p.bytes();
+    }
+    if (!base || (p.ksplit > 1 && !part))
+        return fail(QRFS_ERR_OUT_OF_MEMORY, "scratch of %zu bytes", p.bytes() + p.part_bytes);
+    double* ascale = (double*)(base + p.tile_bytes + 256);
     if (precision == QRFS_PREC_FP16X3) {
         hipError_t e = qrfs::launch_wide_scale(a.w, a.K, n_sets, ascale, st);
         if (e != hipSuccess) return hip_fail(e, "tile scale launch");
     }
     a.ksplit = p.ksplit;
-    a.phi_part = (char*)ctx->ws + p.tile_bytes + 256 + p.scale_bytes;
+    a.phi_part = part;
     // accumulation ranges, an even number of chunks each
     const int64_t range = wide_range(ctx, precision, a.K, a.P, a.R, a.R_block);
     int64_t rch = cdiv(range, KCH);
@@ -535,8 +609,8 @@ qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs 
     wa.nkv = p.nkv;
     wa.cts = p.cts;
     wa.split_ch = p.split_ch;
-    wa.ctile = ctx->ws;
-    wa.sink = (float*)((char*)ctx->ws + p.tile_bytes);
+    wa.ctile = base;
+    wa.sink = (float*)(base + p.tile_bytes);
     for (int64_t s0 = 0; s0 < n_sets; s0 += sets_piece) {
         const int64_t s1 = s0 + sets_piece < n_sets ? s0 + sets_piece : n_sets;
         for (int64_t off = 0; off < a.R_block; off += rows_piece) {
@@ -720,10 +794,11 @@ qrfs_status qrfs_context_destroy(qrfs_context* ctx) {
     qrfs_status st = QRFS_OK;
     {
         DeviceGuard g(ctx->device);
-        if (ctx->ws) {
+        if (ctx->ws || ctx->scratch) {
             hipError_t e = hipDeviceSynchronize();
             if (e != hipSuccess) st = hip_fail(e, "hipDeviceSynchronize in destroy");
-            (void)hipFree(ctx->ws);
+            if (ctx->ws) (void)hipFree(ctx->ws);
+            free_scratch(ctx);
         }
     }
     delete ctx;

@@ -1,0 +1,129 @@
+"""The memory of calls that fill the device only with the help of frequency
+ranges or of the two-phase kernel's tiles: eager calls must leave the workspace
+that a captured graph holds alone, must not wait for the device, and must do
+without where no memory is to be had.  Fields against the FP64 oracle or, bit for
+bit, against the same call alone; tolerances as for the whole contraction.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-11, 1: 1e-5, 4: 1e-5}
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2404_02978_amd as q
+    q.load_library()
+    return q
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.double().cpu().numpy()
+
+
+def problem(ctx, q, K, R, R_block, P, seed=1):
+    rng = np.random.default_rng([K, P, seed])
+    s = q.logpolar_sampler(1e-3, 1e2, index=3)
+    fx, fy, area = ctx.sample_frequencies(s, math.ceil(R / R_block), K)
+    w = ctx.weights(q.psd(0.1, 25.0), fx, fy, area)
+    return fx, fy, w, dev(rng.uniform(-4, 4, P)), dev(rng.uniform(-4, 4, P))
+
+
+def output(R, P, precision):
+    return torch.zeros((R, P), dtype=torch.float64 if precision == 0 else torch.float32,
+                       device="cuda")
+
+
+@pytest.mark.parametrize("K,R,R_block,P", [(4096, 128, 128, 1024), (10007, 259, 259, 3000)])
+def test_eager_calls_leave_a_captured_workspace_alone(q, K, R, R_block, P):
+    """A captured screen that fills the device holds the workspace; eager calls
+    that want ranges (first case) or two-phase tiles (second) run between its
+    replays, and so do allocations that would take the memory if it were freed."""
+    big = (1000, 256, 256, 131072)
+    with q.Context(0) as c:
+        fx, fy, w, px, py = problem(c, q, *big)
+        out = output(big[1], big[3], 4)
+        args = (big[0], fx, fy, w, px, py, big[1], big[2])
+        kw = dict(rng=q.Rng(5, 0, 0), precision=4, out=out)
+        c.synthesize_phase(*args, **kw)
+        want = out.clone()
+        torch.cuda.synchronize()
+        print(f"capture {big}, eager K{K} R{R} P{P}", flush=True)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            c.synthesize_phase(*args, **kw)
+        small = problem(c, q, K, R, R_block, P, 2)
+        ref = oracle.synthesize(*(host(v) for v in small[:3]), host(small[3])[:64],
+                                host(small[4])[:64], R, R_block, K=K, seed=6)
+        fill = []
+        for _ in range(3):
+            got = c.synthesize_phase(K, *small[:3], *small[3:], R, R_block, rng=q.Rng(6, 0, 0),
+                                     precision=1)
+            e = np.max(np.abs(host(got)[:, :64] - ref)) / math.sqrt(np.mean(ref * ref))
+            assert e <= TOL[1]
+            fill.append(torch.full((3 << 20,), 7.0, dtype=torch.float64, device="cuda"))
+            out.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+            assert all(bool((f == 7.0).all()) for f in fill)
+
+
+def test_scratch_grows_without_waiting(q):
+    """A call that takes ranges for the first time returns while another stream
+    is busy, and may be made while another stream is being captured."""
+    K, R, P = 4096, 16, 512
+    with q.Context(0) as c:
+        fx, fy, w, px, py = problem(c, q, K, R, R, P)
+        args = (K, fx, fy, w, px, py, R, R)
+        busy, done, out = torch.cuda.Stream(), torch.cuda.Event(), output(R, P, 0)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(200_000_000)  # a tenth of a second or more
+            done.record()
+        c.synthesize_phase(*args, rng=q.Rng(1, 0, 0), precision=0, out=out)
+        assert not done.query()
+        want = host(out)
+    with q.Context(0) as c:
+        other, x = torch.cuda.Stream(), torch.zeros(8, device="cuda")
+        out.zero_()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            x += 1.0
+            with torch.cuda.stream(other):
+                c.synthesize_phase(*args, rng=q.Rng(1, 0, 0), precision=0, out=out)
+            x += 1.0
+        g.replay()
+        assert np.array_equal(host(out), want) and float(x[0]) == 2.0
+
+
+@pytest.mark.parametrize("precision", [0, 1, 4])
+def test_capped_scratch_gives_way_to_the_workspace(q, precision):
+    """Scratch first, then a workspace that needs the whole cap, then ranges
+    without room."""
+    K, R, R_block, P = 2100, 30, 30, 45
+    with q.Context(0, workspace_cap=3 << 20) as c:
+        fx, fy, w, px, py = problem(c, q, K, R, R_block, P)
+        ref = oracle.synthesize(host(fx), host(fy), host(w), host(px), host(py), R, R_block, K=K,
+                                seed=1)
+        for n in (0, 90000, 0):
+            if n:  # 4 doubles for every 256 points of a set: 2.9 MB
+                s = q.logpolar_sampler(1e-3, 1e2)
+                gx, gy, _ = c.sample_frequencies(s, n, 4)
+                c.point_set_measures(gx, gy, n, 4, -100.0, -100.0, 200.0, 200.0, 0.1)
+            out = c.synthesize_phase(K, fx, fy, w, px, py, R, R_block, rng=q.Rng(1, 0, 0),
+                                     precision=precision)
+            assert np.max(np.abs(host(out) - ref)) <= TOL[precision] * math.sqrt(np.mean(ref * ref))
