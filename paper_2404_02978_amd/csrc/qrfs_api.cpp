@@ -511,6 +511,23 @@ int64_t wide_range(const qrfs_context* ctx, int precision, int64_t K, int64_t P,
     return r < ctx->range_freqs ? r : ctx->range_freqs;
 }
 
+// Fewest frequencies from which a problem that does not fill the device may go to
+// the two-phase kernel: from there on its error is no larger than the fused
+// kernel's in one range, which grows with K.  Below, the weighted coefficients and
+// the short ranges' sums show: RMS error at K = 600, 1300, 1800, 2500, 3300 in units
+// of the fused kernel's, 300 rows x 6400 points, piston 1.15, 1.05, 1.02, 0.96, 0.90
+// and tilt 1.16, 1.07, 1.03, 0.97, 0.91 (FP32; less in BF16x6); FP16x3: phase 1.15,
+// -, 1.00, 0.92, piston 1.14, 1.03, 1.01, 0.93, 0.86, tilt 1.26, 1.14, 1.10, 1.02,
+// 0.96; phases of BF16x6 0.99 at 1200.  FP16x3 differences never: the basis itself
+// has small values there, which the fused kernel scales with the amplitude and fp16
+// cuts off here (1.03 to 1.05 for baselines of 0.1 m and less).
+int64_t wide_least_freqs(int precision, int basis, bool tilt) {
+    const bool f16 = precision == QRFS_PREC_FP16X3;
+    if (basis == qrfs::BASIS_DIFF && f16) return INT64_MAX;
+    if (basis == qrfs::BASIS_PISTON) return tilt ? 3300 : 2500;
+    return f16 ? 1800 : 1200;
+}
+
 // Whether, and in how many frequency ranges, the two-phase kernel contracts
 // this problem.  Forced by the context, or MFMA precisions by the estimated
 // times of both kernels (us).  Two-phase: a 256 x 256 tile takes a compute
@@ -521,8 +538,8 @@ int64_t wide_range(const qrfs_context* ctx, int precision, int64_t K, int64_t P,
 // this one 66, at ten apertures x 1e4 realisations 115 and 433.  Captured calls
 // keep to problems that fill the chip whatever the path: a call that needs no
 // workspace must not take one under capture.
-bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int64_t P, int64_t R,
-              int64_t R_block, bool caller_coef, hipStream_t st, int* ksplit) {
+bool use_wide(const qrfs_context* ctx, int precision, int basis, bool tilt, int64_t K, int64_t P,
+              int64_t R, int64_t R_block, bool caller_coef, hipStream_t st, int* ksplit) {
     *ksplit = 1;
     if (precision == QRFS_PREC_FP64 || ctx->wide_path == 1) return false;
     // FP16X3 scales the coefficient tiles by the largest value the generators
@@ -533,7 +550,7 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, int64_t K, int6
     const bool full = wide_fills(P, R, R_block);
     if (ctx->wide_path == 2) return true;  // as asked, in one range whatever the cap
     if (is_capturing(st)) return full;
-    if (!full && R_block <= 8) return false;
+    if (!full && (R_block <= 8 || K < wide_least_freqs(precision, basis, tilt))) return false;
     const double fused = qrfs::store_split(precision, basis, K, R, R_block, P, kSplitCap).us;
     double best = 1e300;
     const double coef = 2.3e-6 * (double)(cdiv(R, R_block) * cdiv(R_block, 256) * 256) * (double)K;
@@ -696,8 +713,8 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
         a.gy = 2.0 * M_PI * grad_u[1];
     }
     int ksplit = 1;
-    bool wide = use_wide(ctx, precision, basis, K, P, R, R_block, coef != nullptr,
-                         (hipStream_t)stream, &ksplit);
+    bool wide = use_wide(ctx, precision, basis, grad_u != nullptr, K, P, R, R_block,
+                         coef != nullptr, (hipStream_t)stream, &ksplit);
     if (wide) {
         s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), ksplit, (hipStream_t)stream);
         // no memory for its tiles (nothing is enqueued yet): the fused kernel
