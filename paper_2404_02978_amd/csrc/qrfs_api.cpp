@@ -40,7 +40,7 @@ struct qrfs_context {
     size_t scratch_total = 0;  // with the outgrown blocks
     void* outgrown[40] = {};
     int n_outgrown = 0;
-    unsigned long long* grids = nullptr;  // the device's ring of answers, see grid_word
+    int grid_slot = -1;  // the context's word for grid answers (-1: none), see grid_word
 };
 
 // Scratch of the allocation-free structure-function entry point: a static
@@ -50,17 +50,17 @@ struct qrfs_context {
 // hipGetSymbolAddress returns for the current device, kept per device.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 // Behind it, the words in which calls note whether their points form a grid: one
-// ring for calls as they run, one for captured ones, whose words are then not
-// taken by what runs between the replays.
-constexpr unsigned kGridRing = 512;
+// for each context, then a ring for captured calls.
+constexpr unsigned kGridSlots = 512, kGridRing = 512;
 static __device__ __align__(256) unsigned char
-    scratch[kScratchBytes + 2 * kGridRing * sizeof(unsigned long long)];
+    scratch[kScratchBytes + (kGridSlots + kGridRing) * sizeof(unsigned long long)];
 
 namespace {
 
 constexpr int kMaxDevices = 256;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
+bool g_grid_slots[kMaxDevices][kGridSlots] = {};  // taken by a context
 
 thread_local std::string g_detail;
 
@@ -117,19 +117,42 @@ qrfs_status sf_sets_enqueue(const qrfs::SfPlan& plan, char* base, int64_t K, con
                             const double* by, int64_t R, int64_t R_block, const qrfs_rng* rng,
                             int32_t precision, double* sf, double* sf_stderr, hipStream_t stream);
 
-// A word of the ring and an id for one call: calls of any thread, stream and
-// context may share a word (see GridWord).
-qrfs::GridWord grid_word(qrfs_context* ctx, bool captured) {
-    static std::atomic<unsigned long long> next[2];
-    const unsigned long long i = next[captured].fetch_add(1);
-    static std::atomic<unsigned long long> id{1};
-    return {ctx->grids + (captured ? kGridRing : 0) + i % kGridRing, id.fetch_add(1)};
-}
-
 void* scratch_ptr(int device) {
     if (device < 0 || device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     return g_scratch_ptr[device];
+}
+
+// A context's word among the device's (-1: all taken).
+int take_grid_slot(int device) {
+    if (device < 0 || device >= kMaxDevices) return -1;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    for (unsigned i = 0; i < kGridSlots; ++i)
+        if (!g_grid_slots[device][i]) {
+            g_grid_slots[device][i] = true;
+            return (int)i;
+        }
+    return -1;
+}
+
+void give_grid_slot(int device, int slot) {
+    if (slot < 0) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_grid_slots[device][slot] = false;
+}
+
+// The word and an id for one call (word NULL: it cannot ask).  Eager calls of a
+// context may not overlap, so its word is theirs from the question to the last
+// kernel that reads the answer.  Captured ones have none of their own: a graph may
+// outlive the context, and calls of any graph, thread and stream share the ring
+// (see GridWord).
+qrfs::GridWord grid_word(const qrfs_context* ctx, bool captured) {
+    static std::atomic<unsigned long long> next{0}, id{1};
+    char* base = (char*)scratch_ptr(ctx->device);
+    if (!base || (!captured && ctx->grid_slot < 0)) return {};
+    const unsigned long long i =
+        captured ? kGridSlots + next.fetch_add(1) % kGridRing : (unsigned long long)ctx->grid_slot;
+    return {(unsigned long long*)(base + kScratchBytes) + i, id.fetch_add(1)};
 }
 
 #define CHECK_PTR(p)                                                                 \
@@ -383,7 +406,7 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     // those are worth its launch, 8 us when the points turn out to be none: a
     // grid saves up to 5/6 of the time in binary64, half in FP32
     const double pad = qrfs::grid_max_pad(precision == QRFS_PREC_FP64, a.R_block);
-    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && ctx->grids &&
+    if (basis == qrfs::BASIS_PHASE && pad > 0.0 &&
         sp.us > (precision == QRFS_PREC_FP64 ? 25.0 : 60.0) && a.P >= 171 &&
         a.P <= ((int64_t)1 << 24)) {
         qrfs::SepArgs b{};
@@ -403,7 +426,8 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
         b.out = a.out;
         a.grid = grid_word(ctx, is_capturing(st));
         const hipError_t e =
-            qrfs::launch_grid_sum(precision == QRFS_PREC_FP64, b, pad, a.grid, st);
+            a.grid.word ? qrfs::launch_grid_sum(precision == QRFS_PREC_FP64, b, pad, a.grid, st)
+                        : hipSuccess;
         if (e != hipSuccess) return hip_fail(e, "grid sum launch");
     }
     qrfs_status s = run_sum(precision, basis, qrfs::EPI_STORE, a, n_sets, st);
@@ -781,8 +805,7 @@ qrfs_status qrfs_context_create(qrfs_context** out, int32_t device, size_t works
     if (!c) return fail(QRFS_ERR_OUT_OF_MEMORY, "host allocation of the context");
     c->device = device;
     c->ws_cap = workspace_cap_bytes;
-    if (char* base = (char*)scratch_ptr(device))
-        c->grids = (unsigned long long*)(base + kScratchBytes);
+    c->grid_slot = take_grid_slot(device);
     *out = c;
     return ok();
 }
@@ -818,6 +841,7 @@ qrfs_status qrfs_context_destroy(qrfs_context* ctx) {
             free_scratch(ctx);
         }
     }
+    give_grid_slot(ctx->device, ctx->grid_slot);
     delete ctx;
     return st ? st : ok();
 }

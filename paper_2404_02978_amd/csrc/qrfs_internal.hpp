@@ -39,9 +39,11 @@ enum Epilogue : int {
 
 // Whether a call's points form a grid, as k_grid_sum found: a word of device
 // memory that only grows (atomic maximum), 2 id where they do and 2 id + 1 where
-// they do not, with an id of its own for each call.  Should another call take
-// the word meanwhile, the answer reads as no, and the general kernel does the
-// work as well.
+// they do not, with an id of its own for each call.  The word of a call in several
+// frequency ranges is its own until its last kernel: the general kernel and the
+// one that adds its ranges must read the same answer.  In a call of one range the
+// word may be shared: should another call take it meanwhile, even between two
+// blocks, the answer reads as no, and the general kernel does the work as well.
 constexpr int GRID_MAX_V = 4096;  // longest row
 struct GridWord {
     unsigned long long* word;  // NULL: not asked

@@ -127,3 +127,54 @@ def test_capped_scratch_gives_way_to_the_workspace(q, precision):
             out = c.synthesize_phase(K, fx, fy, w, px, py, R, R_block, rng=q.Rng(1, 0, 0),
                                      precision=precision)
             assert np.max(np.abs(host(out) - ref)) <= TOL[precision] * math.sqrt(np.mean(ref * ref))
+
+
+def test_grid_answers_of_two_contexts(q):
+    """512 calls in ranges on a grid's points, from each of two contexts on
+    streams of their own that start together: every answer is its call's own, so
+    every field is the same."""
+    K, R, n, calls = 4096, 8, 32, 512
+    with q.Context(0) as a, q.Context(0) as b:
+        fx, fy, w, _, _ = problem(a, q, K, R, 1, 1)
+        g = np.linspace(0.0, 1.0, n)
+        px, py = dev(np.tile(g, n)), dev(np.repeat(g, n))
+        outs = [torch.full((calls, R, n * n), float("nan"), dtype=torch.float64, device="cuda")
+                for _ in range(2)]
+
+        def call(c, out):
+            c.synthesize_phase(K, fx, fy, w, px, py, R, 1, rng=q.Rng(2, 0, 0), precision=0, out=out)
+
+        call(a, outs[0][0])
+        call(b, outs[1][0])  # both hold their scratch now
+        want = host(outs[0][0])
+        start = torch.cuda.Event()
+        torch.cuda._sleep(50_000_000)
+        start.record()
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        for s in streams:
+            s.wait_event(start)
+        print("512 calls on each of two streams", flush=True)
+        for c, s, o in zip((a, b), streams, outs):
+            with torch.cuda.stream(s):
+                for i in range(calls):
+                    call(c, o[i])
+        torch.cuda.synchronize()
+        for o in outs:
+            assert torch.equal(o, torch.as_tensor(want).cuda().expand_as(o))
+        ref = oracle.synthesize(host(fx), host(fy), host(w), host(px), host(py), R, 1, K=K, seed=2)
+        assert np.max(np.abs(want - ref)) <= TOL[0] * math.sqrt(np.mean(ref * ref))
+
+
+def test_more_contexts_than_words_for_grids(q):
+    """Contexts beyond the 512 words take the general kernel."""
+    K, R, n = 1024, 8, 32
+    held = [q.Context(0) for _ in range(514)]
+    fx, fy, w, _, _ = problem(held[0], q, K, R, 1, 1)
+    g = np.linspace(0.0, 1.0, n)
+    px, py = dev(np.tile(g, n)), dev(np.repeat(g, n))
+    ref = oracle.synthesize(host(fx), host(fy), host(w), host(px), host(py), R, 1, K=K, seed=2)
+    for c in (held[0], held[-1]):
+        out = c.synthesize_phase(K, fx, fy, w, px, py, R, 1, rng=q.Rng(2, 0, 0), precision=0)
+        assert np.max(np.abs(host(out) - ref)) <= TOL[0] * math.sqrt(np.mean(ref * ref))
+    for c in held:
+        c.close()
