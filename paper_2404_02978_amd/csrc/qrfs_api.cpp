@@ -396,7 +396,7 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     char* part = nullptr;
     if (sp.ksplit > 1) {
         part = is_capturing(st) ? nullptr : scratch_block(ctx, sp.bytes);
-        if (!part) sp = {1, a.K, 0, 0.0};
+        if (!part) sp = qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, 0);
     }
     a.ksplit = sp.ksplit;
     a.kspan = sp.kspan;
