@@ -626,11 +626,15 @@ qrfs_status wide_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs 
         if (s) return s;
         base = (char*)ctx->ws;
         part = p.ksplit > 1 ? scratch_block(ctx, p.part_bytes) : nullptr;
+        if (p.ksplit > 1 && !part) {  // no room for partial sums: one range
+            s = wide_plan(ctx, precision, a.K, a.P, a.R, a.R_block, 1, p);
+            if (s) return s;
+        }
     } else {
         base = scratch_block(ctx, p.bytes() + p.part_bytes);
-        part = base + p.bytes();
+        part = base ? base + p.bytes() : nullptr;
     }
-    if (!base || (p.ksplit > 1 && !part))
+    if (!base)
         return fail(QRFS_ERR_OUT_OF_MEMORY, "scratch of %zu bytes", p.bytes() + p.part_bytes);
     double* ascale = (double*)(base + p.tile_bytes + 256);
     if (precision == QRFS_PREC_FP16X3) {

@@ -208,3 +208,22 @@ def test_captured_grids_keep_their_route(q, precision):
         general = np.empty_like(host(outs[1]))
         general[:, order] = host(outs[1])
         assert not np.array_equal(general, host(outs[0]))
+
+
+def test_full_problem_without_room_for_ranges(q):
+    """A screen that fills the device, whose 513 tiles would run better in two
+    ranges, in a context with room for its tiles but not for 136 MB of partial
+    sums besides: one range."""
+    K, R, P = 4096, 130, 131100
+    with q.Context(0, workspace_cap=160 << 20) as c:
+        fx, fy, w, px, py = problem(c, q, K, R, R, P)
+        s = q.logpolar_sampler(1e-3, 1e2)
+        n = 1100000  # a workspace of 35.2 MB
+        gx, gy, _ = c.sample_frequencies(s, n, 4)
+        c.point_set_measures(gx, gy, n, 4, -100.0, -100.0, 200.0, 200.0, 0.1)
+        print(f"full K{K} R{R} P{P}", flush=True)
+        out = c.synthesize_phase(K, fx, fy, w, px, py, R, R, rng=q.Rng(1, 0, 0), precision=1)
+        sel = np.r_[0:8, P - 8:P]
+        ref = oracle.synthesize(host(fx), host(fy), host(w), host(px)[sel], host(py)[sel], R, R,
+                                K=K, seed=1)
+        assert np.max(np.abs(host(out)[:, sel] - ref)) <= TOL[1] * math.sqrt(np.mean(ref * ref))
