@@ -401,14 +401,19 @@ qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs
     a.ksplit = sp.ksplit;
     a.kspan = sp.kspan;
     a.phi_part = part;
-    // narrow sets: fields on a regular grid go through its product structure,
-    // if the points are one (the general kernel sees the same answer), where
-    // those are worth its launch, 8 us when the points turn out to be none: a
-    // grid saves up to 5/6 of the time in binary64, half in FP32
-    const double pad = qrfs::grid_max_pad(precision == QRFS_PREC_FP64, a.R_block);
-    if (basis == qrfs::BASIS_PHASE && pad > 0.0 &&
-        sp.us > (precision == QRFS_PREC_FP64 ? 25.0 : 60.0) && a.P >= 171 &&
-        a.P <= ((int64_t)1 << 24)) {
+    // narrow sets: fields on a regular grid go through its product structure, if
+    // the points are one (the general kernel sees the same answer).  A grid of at
+    // least 171 points (the fewest whose padded tiles can pass) saves up to 5/6 of
+    // the time in binary64, half in FP32; a no costs 4 us: asked where that is
+    // under 5 % of the call (in binary64 the estimate falls short by a quarter), or
+    // where ranges have saved twice as much
+    const bool fp64 = precision == QRFS_PREC_FP64;
+    const double pad = qrfs::grid_max_pad(fp64, a.R_block);
+    if (basis == qrfs::BASIS_PHASE && pad > 0.0 && a.P >= 171 && a.P <= ((int64_t)1 << 24) &&
+        (sp.us > (fp64 ? 60.0 : 80.0) ||
+         (sp.ksplit > 1 && sp.us > (fp64 ? 25.0 : 60.0) &&
+          sp.us + 8.0 <
+              qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, 0).us))) {
         qrfs::SepArgs b{};
         b.K = a.K;
         b.fx = a.fx;

@@ -1,0 +1,62 @@
+"""What the question whether points form a grid may cost a call whose points are
+none: disks, whose first rows divide the number of points or not, take about as
+long in row order as shuffled, where the first two points already say no.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2404_02978_amd as q
+    q.load_library()
+    return q
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def best_of(call, n=20, rounds=5):
+    """Shortest time of a call among n in a row, ms."""
+    times = []
+    for _ in range(rounds):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) / n)
+    return min(times)
+
+
+# the unmended check did the grid's work first: 1.4 to 2.5 times the time; runs
+# differ by 3 %
+@pytest.mark.parametrize("precision,K,R,R_block,n", [(0, 512, 400, 1, 32), (1, 512, 400, 1, 32),
+                                                     (0, 512, 400, 2, 32), (0, 256, 512, 1, 32),
+                                                     (1, 1024, 300, 1, 48)])
+def test_disks_cost_no_grid_work(q, precision, K, R, R_block, n):
+    with q.Context(0) as c:
+        s = q.logpolar_sampler(1e-3, 1e2, index=5)
+        fx, fy, area = c.sample_frequencies(s, math.ceil(R / R_block), K)
+        w = c.weights(q.psd(0.1, 25.0), fx, fy, area)
+        px, py = workloads.disk_mask_points(n, 1.0)
+        order = np.random.default_rng(0).permutation(px.size)
+        out = torch.empty((R, px.size), dtype=torch.float32 if precision else torch.float64,
+                          device="cuda")
+        t = []
+        for o in (np.arange(px.size), order):
+            x, y = dev(px[o]), dev(py[o])
+            t.append(best_of(lambda: c.synthesize_phase(
+                K, fx, fy, w, x, y, R, R_block, rng=q.Rng(3, 7, 0), precision=precision, out=out)))
+        print(f"p{precision} K{K} R{R} P{px.size}: {1e3 * t[0]:.1f} us, shuffled {1e3 * t[1]:.1f}",
+              flush=True)
+        assert t[0] < 1.15 * t[1]
