@@ -30,9 +30,11 @@ __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) 
     if (grid_done(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
-    const int64_t ct = (int64_t)blockIdx.x % col_tiles;
-    const int64_t ks = (int64_t)blockIdx.x / col_tiles % a.ksplit;  // frequency range
-    const int64_t sl = (int64_t)blockIdx.x / col_tiles / a.ksplit;
+    // (32-bit divisions: a launch's blocks fit)
+    const uint32_t nct = (uint32_t)col_tiles, nks = (uint32_t)a.ksplit;
+    const int64_t ct = blockIdx.x % nct;
+    const int64_t ks = blockIdx.x / nct % nks;  // frequency range
+    const int64_t sl = blockIdx.x / nct / nks;
     const int64_t kr = ks * a.kspan;
     const int64_t ke = kr + a.kspan < a.K ? kr + a.kspan : a.K;
     const int64_t set = a.set0 + sl;
@@ -61,9 +63,12 @@ __global__ __launch_bounds__(256) void k_sum_f64n(SumArgs a, int64_t col_tiles) 
         if (tid < F64N_KC) {
             const int64_t k = k0 + tid;
             const bool ok = k < ke;
-            sfx[tid] = ok ? fx[k] : 0.0;
-            sfy[tid] = ok ? fy[k] : 0.0;
-            sw[tid] = ok ? w[k] : 0.0;
+            // (loaded at once, not one after the other's test)
+            const int64_t kl = ok ? k : ke - 1;
+            const double f0 = fx[kl], f1 = fy[kl], wk = w[kl];
+            sfx[tid] = ok ? f0 : 0.0;
+            sfy[tid] = ok ? f1 : 0.0;
+            sw[tid] = ok ? wk : 0.0;
         }
         // RB rows x 32 Philox blocks (4 coefficients each)
         for (int i = tid; i < RB * (F64N_KC / 2); i += nt) {
@@ -205,9 +210,10 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
     if (grid_done(a.grid)) return;  // k_grid_sum did the work
     const int tid = threadIdx.x;
     const int nt = blockDim.x;
-    const int64_t ct = (int64_t)blockIdx.x % col_tiles;
-    const int64_t ks = (int64_t)blockIdx.x / col_tiles % a.ksplit;  // frequency range
-    const int64_t sl = (int64_t)blockIdx.x / col_tiles / a.ksplit;
+    const uint32_t nct = (uint32_t)col_tiles, nks = (uint32_t)a.ksplit;
+    const int64_t ct = blockIdx.x % nct;
+    const int64_t ks = blockIdx.x / nct % nks;  // frequency range
+    const int64_t sl = blockIdx.x / nct / nks;
     const int64_t kr = ks * a.kspan;
     const int64_t ke = kr + a.kspan < a.K ? kr + a.kspan : a.K;
     const int64_t set = a.set0 + sl;
@@ -232,9 +238,12 @@ __global__ __launch_bounds__(256) void k_sum_f32n(SumArgs a, int64_t col_tiles) 
         if (tid < KCN) {
             const int64_t k = k0 + tid;
             const bool ok = k < ke;
-            sfx[tid] = ok ? fx[k] : 0.0;
-            sfy[tid] = ok ? fy[k] : 0.0;
-            sw[tid] = ok ? w[k] : 0.0;
+            // (loaded at once, not one after the other's test)
+            const int64_t kl = ok ? k : ke - 1;
+            const double f0 = fx[kl], f1 = fy[kl], wk = w[kl];
+            sfx[tid] = ok ? f0 : 0.0;
+            sfy[tid] = ok ? f1 : 0.0;
+            sw[tid] = ok ? wk : 0.0;
         }
         for (int i = tid; i < RB * (KCN / 2); i += nt) {
             const int rr = i / (KCN / 2);
