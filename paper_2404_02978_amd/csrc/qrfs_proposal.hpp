@@ -34,7 +34,7 @@ StepSizes prop_step_sizes(int64_t n_ctx, int64_t m, int64_t G);
 hipError_t prop_launch_step(float* prm, const StepSizes& z, int64_t n_ctx, int64_t m,
                             const int32_t* ctxlist, const double* ctx4, const double* ell,
                             const double* theta, const double* h, int G, double lmin, double Lw,
-                            double* dscratch, float* fscratch, float* gpart, float* grad,
+                            double* dscratch, float* fscratch, double* gpart, float* grad,
                             double* loss, float* m1, float* m2, float lr, int64_t t,
                             hipStream_t st);
 hipError_t prop_launch_table(const float* o, int64_t nB, int n_cells, const double* bth,

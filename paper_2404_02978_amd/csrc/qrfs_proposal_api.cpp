@@ -84,7 +84,7 @@ struct StepScratch {
     qrfs::StepSizes z;
     double* dscr;
     float* fscr;
-    float* gpart;
+    double* gpart;
     int32_t* ctxlist;
 };
 
@@ -97,7 +97,7 @@ qrfs_status step_scratch(qrfs_proposal* p, int64_t n_ctx, int64_t m, int G, int6
     const size_t fs = o;
     o += a256(sizeof(float) * s.z.floats);
     const size_t gp = o;
-    o += a256(sizeof(float) * (size_t)s.z.blocks * qrfs::NPARAM);
+    o += a256(sizeof(double) * (size_t)s.z.blocks * qrfs::NPARAM);
     const size_t cl = o;
     o += a256(sizeof(int32_t) * list_len);
     qrfs_status st = workspace(p, o);
@@ -105,7 +105,7 @@ qrfs_status step_scratch(qrfs_proposal* p, int64_t n_ctx, int64_t m, int G, int6
     char* b = (char*)p->ws;
     s.dscr = (double*)(b + ds);
     s.fscr = (float*)(b + fs);
-    s.gpart = (float*)(b + gp);
+    s.gpart = (double*)(b + gp);
     s.ctxlist = (int32_t*)(b + cl);
     return QRFS_OK;
 }
