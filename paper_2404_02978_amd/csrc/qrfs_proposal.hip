@@ -56,24 +56,6 @@ __device__ __forceinline__ float ell_feature(double ell, double lmin, double Lw)
     return (float)(2.0 * (ell - lmin) / Lw - 1.0);
 }
 
-// tanh in binary32: below 5/8 an odd polynomial (least squares fit of
-// (tanh(x)/x - 1)/x^2 in x^2, relative error 2e-10 before rounding), above
-// 1 - 2 / (exp(2 |x|) + 1) with the hardware exponential and reciprocal;
-// within 2 units in the last place, at about 20 vector instructions.
-__device__ __forceinline__ float tanh_f32(float x) {
-    const float a = fabsf(x), z = x * x;
-    float p = 2.14280e-3f;
-    p = fmaf(p, z, -8.17709e-3f);
-    p = fmaf(p, z, 2.17005e-2f);
-    p = fmaf(p, z, -5.39467e-2f);
-    p = fmaf(p, z, 0.13333205f);
-    p = fmaf(p, z, -0.33333331f);
-    const float small = fmaf(x * z, p, x);
-    const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * a);
-    const float big = copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f), x);
-    return a < 0.625f ? small : big;
-}
-
 // Inputs of a row: the 5 features, 1 (for the bias of layer 1), 0, 0.
 constexpr int XW = 8;
 
@@ -147,7 +129,7 @@ __device__ __forceinline__ void forward_tile(NetSmem<NR>& s, const float (*x)[XW
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                s.h1[(16 * m + 4 * lh + i) * ST + u] = tanh_f32(acc[m][i]);
+                s.h1[(16 * m + 4 * lh + i) * ST + u] = tanhf(acc[m][i]);
     }
     __syncthreads();
     f32x4 acc[MT] = {};
@@ -168,7 +150,7 @@ __device__ __forceinline__ void forward_tile(NetSmem<NR>& s, const float (*x)[XW
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            s.h2[(16 * m + 4 * lh + i) * ST + u] = tanh_f32(acc[m][i] + b2);
+            s.h2[(16 * m + 4 * lh + i) * ST + u] = tanhf(acc[m][i] + b2);
     __syncthreads();
     // outputs: 8 threads per row, 16 units each, added in a fixed tree
     const int r = t >> 3, part = t & 7;
@@ -378,7 +360,7 @@ struct TileSum {
 // two waves compute the loss and fetch the next tile's rows beside the other
 // waves' matrix work.  33792 rows: 56 us (68 with loops over the rows in LDS for
 // the small layers); with the exact sums over the tiles, which go out in binary64,
-// a training step of them takes 93 us, 85 before.
+// a training step of them takes 88 us, 85 before.
 __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm, RowSpec rs,
                                                    uint32_t chunk, double* __restrict__ gpart,
                                                    double* __restrict__ lpart) {
@@ -412,7 +394,7 @@ __global__ __launch_bounds__(THREADS) void k_train(const float* __restrict__ prm
             const int r = t >> 3;
             const bool sample = !(in.C[r] > 1.5);
             const float wg = (float)in.w[r], C = sample ? (float)in.C[r] : 0.0f;
-            const float ta = tanh_f32(o[1]);
+            const float ta = tanhf(o[1]);
             const float alpha = 0.9f * ta;
             const float g1 = sample ? wg * C / (1.0f + alpha * C) * 0.9f * (1.0f - ta * ta) : 0.0f;
             dout[r][0] = wg;

@@ -101,3 +101,27 @@ def test_gradient_of_many_rows(q, ctx, n_ctx, m, G, seed):
     print(f"  gradient {e:.2e}", flush=True)
     assert loss == pytest.approx(rl, rel=1e-8)
     assert e <= 3e-7
+
+
+def test_tanh_of_the_hidden_units(q, ctx):
+    """With no weights in the second layer the outputs are tanh of two of its
+    biases, bit for bit.  Errors in [5/8, 1), where the exponential's and the
+    quotient's show most, in units of the last place: the library's tanhf has 0.417
+    RMS and at most 1.41 there; 8192 values give the RMS to 1 %."""
+    x = np.linspace(0.625, 1.0, 8192, endpoint=False).astype(np.float32)
+    prm = np.zeros(workloads.mlp_init(0).size, dtype=np.float32)
+    W1, b1, W2, b2, W3, b3 = split(t := torch.as_tensor(prm).cuda())
+    W3[0, 5] = W3[1, 77] = 1.0
+    p = q.Proposal(ctx, workloads.FMIN, workloads.FMAX, prm)
+    ell, c4 = dev([LMIN]), dev(workloads.proposal_contexts(1, seed=1))
+    xs, out = torch.as_tensor(x).cuda(), []
+    for i in range(0, x.size, 2):
+        b2[5], b2[77] = xs[i], xs[i + 1]
+        p.set_params(t)
+        out.append(p.forward(ell, c4))
+    got = torch.cat(out).flatten().double().cpu().numpy()
+    p.close()
+    ref = np.tanh(x.astype(np.float64))
+    e = np.abs(got - ref) / np.spacing(ref.astype(np.float32)).astype(np.float64)
+    print(f"rms {math.sqrt(np.mean(e * e)):.3f} max {e.max():.3f}", flush=True)
+    assert math.sqrt(np.mean(e * e)) <= 0.435 and e.max() <= 1.42
