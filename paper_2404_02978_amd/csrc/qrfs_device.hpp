@@ -286,19 +286,30 @@ __device__ __forceinline__ void sincos2pi_reduced(double r, double& s, double& c
 // ------------------------------------------------- binary64 generator ----
 // sqrt(-2 ln u) for a uniform u = (2m + 1) 2^-24: u = 2^e f with f in
 // [1/sqrt 2, sqrt 2), ln f = 2 atanh(s), s = (f - 1) / (f + 1), |s| <= 0.172,
-// by the series s (1 + z/3 + z^2/5 + ...), z = s^2, through z^9 (first
-// omitted term below 3e-17).  f - 1 is exact, the quotient and the root are
-// hardware estimates with a Newton step and one correction by their
-// residual.  Largest relative error over all 2^23 such u: 2.7e-16 (the
-// general-purpose log and sqrt: 1.7e-16), at about 40 vector instructions.
-constexpr double kAtanh[10] = {1.0 / 19, 1.0 / 17, 1.0 / 15, 1.0 / 13, 1.0 / 11,
-                               1.0 / 9,  1.0 / 7,  1.0 / 5,  1.0 / 3,  1.0};
+// by the series s + s^3 (1/3 + z/5 + ...), z = s^2, through z^9 (first omitted
+// term below 3e-17).  f - 1 and e times the high part of 2 ln 2 (45 bits) are
+// exact; what the quotient, the leading sum and a = -2 ln u round away is carried
+// to the root's last correction.  Largest relative error over all 2^23 such u
+// 1.11e-16, 4.7e-17 RMS (the general-purpose log and sqrt: 1.68e-16 and 5.3e-17),
+// at about 48 vector instructions.
+constexpr double kTwoLn2Hi = 1.3862943611198943, kTwoLn2Lo = -3.728377347448607e-15;
+constexpr double kAtanh[9] = {1.0 / 19, 1.0 / 17, 1.0 / 15, 1.0 / 13, 1.0 / 11,
+                              1.0 / 9,  1.0 / 7,  1.0 / 5,  1.0 / 3};
+
+// sqrt(a + l), |l| at most half a unit in the last place of a.
+__device__ __forceinline__ double sqrt_sum(double a, double l) {
+    double r = __builtin_amdgcn_rsq(a);
+    r = fma(r, fma(-0.5 * a, r * r, 0.5), r);
+    const double g = a * r;
+    return fma(fma(-g, g, a) + l, 0.5 * r, g);
+}
+
 __device__ __forceinline__ double gauss_radius_f64(double u) {
     double f = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
-    int e = __builtin_amdgcn_frexp_exp(u);
+    const int ue = __builtin_amdgcn_frexp_exp(u);
     const bool low = f < 0.70710678118654757;
     f = low ? f + f : f;
-    e = low ? e - 1 : e;
+    const double e = (double)(low ? ue - 1 : ue);
     const double d = f - 1.0, q = f + 1.0;
     double y = __builtin_amdgcn_rcp(q);
     y = fma(fma(-q, y, 1.0), y, y);
@@ -307,23 +318,48 @@ __device__ __forceinline__ double gauss_radius_f64(double u) {
     const double z = s * s;
     double p = kAtanh[0];
 #pragma unroll
-    for (int n = 1; n < 10; ++n) p = fma_s(p, z, kAtanh[n]);
-    const double a = fma(-4.0 * s, p, (double)e * -1.3862943611198906);  // -2 ln u > 0
-    double r = __builtin_amdgcn_rsq(a);
-    r = fma(r, fma(-0.5 * a, r * r, 0.5), r);
-    const double g = a * r;
-    return fma(fma(-g, g, a), 0.5 * r, g);
+    for (int n = 1; n < 9; ++n) p = fma_s(p, z, kAtanh[n]);
+    const double t = fma(s * z, p, fma(-s, q, d) * y);  // atanh(s) - s
+    const double m = e * -kTwoLn2Hi;
+    const double h = fma(-4.0, s, m);
+    const double l = fma(-4.0, s, m - h) + fma(-4.0, t, e * -kTwoLn2Lo);
+    const double a = h + l;
+    return sqrt_sum(a, (h - a) + l);
+}
+
+// sin and cos of 2 pi r for the generator, as sincos2pi_reduced but with 2 pi z
+// and 1 - 2 pi^2 z^2 to the last bit (the low parts of both coefficients, and what
+// the difference rounds away): within 7e-17 where sincos2pi_reduced is
+// within 1.9e-16 (the general-purpose sincospi: 8.3e-17), 5 instructions more.
+__device__ __forceinline__ void sincos2pi_gauss(double r, double& s, double& c) {
+    const double q = rint(4.0 * r);
+    const double z = fma(-0.25, q, r);
+    const double w = z * z;  // exact: z is a multiple of 2^-24
+    double ps = kSin2pi[0];
+#pragma unroll
+    for (int n = 1; n < 7; ++n) ps = fma_s(ps, w, kSin2pi[n]);
+    ps = fma(z, kSin2pi[7], fma_s(ps, w, 2.4492935982947064e-16) * z);
+    double pc = kCos2pi[0];
+#pragma unroll
+    for (int n = 1; n < 7; ++n) pc = fma_s(pc, w, kCos2pi[n]);
+    const double h = fma(w, kCos2pi[7], 1.0);
+    const double l = fma(w, kCos2pi[7], 1.0 - h);
+    pc = h + fma(w, fma_s(pc, w, -1.2530591017479423e-15), l);
+    const double cq = 1.0 - fabs(q);
+    const double sq = q * (1.0 - fabs(cq));
+    s = fma(ps, cq, pc * sq);
+    c = fma(pc, cq, -(ps * sq));
 }
 
 // The FP64 path's Box-Muller pair and coefficients: the contract's values
 // with the radius above and the project's revolution sine and cosine
-// (u2 - rint(u2) is exact).  A pair takes about 85 vector instructions; with
+// (u2 - rint(u2) is exact).  A pair takes about 100 vector instructions; with
 // the general-purpose log, sqrt and sincospi the generator was ~150 per
 // coefficient.
 __device__ __forceinline__ void box_muller_f64(double u1, double u2, double& g0, double& g1) {
     const double rho = gauss_radius_f64(u1);
     double s, c;
-    sincos2pi_reduced(u2 - rint(u2), s, c);
+    sincos2pi_gauss(u2 - rint(u2), s, c);
     g0 = rho * c;
     g1 = rho * s;
 }
@@ -341,7 +377,7 @@ __device__ __forceinline__ void coef4_f64(uint64_t seed, uint64_t real, uint32_t
             box_muller_f64(word_uniform_f64(x.x), word_uniform_f64(x.y), rn, unused);
             double s, c;
             const double u = word_uniform_f64(x.z);
-            sincos2pi_reduced(u - rint(u), s, c);
+            sincos2pi_gauss(u - rint(u), s, c);
             g[2 * h] = 1.4142135623730951 * rn * c;
             g[2 * h + 1] = -1.4142135623730951 * rn * s;
         }
