@@ -5,163 +5,166 @@
 namespace qrfs {
 
 // --------------------------------------------------------- coefficients ----
-// The generator of qrfs_device.hpp with two tables of 64 entries in LDS, for a
-// kernel that draws most of its time: entry i holds r = 1 / c (rounded) and
-// 2 ln r for the mantissas around c = 1/2 + (i + 1/2) / 128 (r = 1 in the last,
-// so that u near 1 cancels nothing), and sin, cos of 2 pi (i + 1/2) / 64.  With
-// u = (2m + 1) 2^-24 = f 2^e: -2 ln u = 2 ln r - 2 log1p(f r - 1) - 2 e ln 2,
-// |f r - 1| <= 1/128, log1p by its series through the 8th power (first omitted
-// term 2e-18); the angle is the entry's, turned by what is left of it, at most
-// 1/128 revolution, by the first terms of the series for 1/8.  Over all 2^23 u:
-// radius within 2.2e-16 (relative), sine and cosine within 1.7e-16 of the exact
-// values, at ~50 vector instructions a pair in the place of ~85.  1e5 realisations
-// x 4096 frequencies x 32 baselines: 2.07 ms, 2.70 without the tables.
-static __device__ __attribute__((aligned(16))) const double kGaussTab[64][4] = {
-    {1.9844961240310077, 1.3707300802357807,
-     0.049067674327418015, 0.9987954562051724},
-    {1.9541984732824427, 1.3399602425568218,
-     0.14673047445536175, 0.989176509964781},
-    {1.9248120300751879, 1.3096566325156174,
-     0.2429801799032639, 0.970031253194544},
-    {1.8962962962962964, 1.2798053320822662,
-     0.33688985339222005, 0.9415440651830208},
-    {1.8686131386861313, 1.250393037302875,
-     0.4275550934302821, 0.9039892931234433},
-    {1.841726618705036, 1.2214070226977416,
-     0.5141027441932218, 0.8577286100002721},
-    {1.8156028368794326, 1.1928351082027884,
-     0.5956993044924334, 0.8032075314806449},
-    {1.7902097902097902, 1.1646656284393104,
-     0.6715589548470184, 0.7409511253549591},
-    {1.7655172413793103, 1.1368874041179762,
-     0.7409511253549591, 0.6715589548470184},
-    {1.7414965986394557, 1.1094897154016523,
-     0.8032075314806449, 0.5956993044924334},
-    {1.7181208053691275, 1.0824622770682066,
-     0.8577286100002721, 0.5141027441932218},
-    {1.695364238410596, 1.0557952153292762,
-     0.9039892931234433, 0.4275550934302821},
-    {1.673202614379085, 1.029479046174254,
-     0.9415440651830208, 0.33688985339222005},
-    {1.6516129032258065, 1.0035046551206317,
-     0.970031253194544, 0.2429801799032639},
-    {1.6305732484076434, 0.977863278262509,
-     0.989176509964781, 0.14673047445536175},
-    {1.610062893081761, 0.952546484518662,
-     0.9987954562051724, 0.049067674327418015},
-    {1.5900621118012421, 0.9275461589901989,
-     0.9987954562051724, -0.049067674327418015},
-    {1.5705521472392638, 0.9028544873456004,
-     0.989176509964781, -0.14673047445536175},
-    {1.5515151515151515, 0.8784639411579638,
-     0.970031253194544, -0.2429801799032639},
-    {1.532934131736527, 0.8543672641256148,
-     0.9415440651830208, -0.33688985339222005},
-    {1.514792899408284, 0.830557459112978,
-     0.9039892931234433, -0.4275550934302821},
-    {1.4970760233918128, 0.8070277759538051,
-     0.8577286100002721, -0.5141027441932218},
-    {1.4797687861271676, 0.783771699963567,
-     0.8032075314806449, -0.5956993044924334},
-    {1.4628571428571429, 0.7607829411120969,
-     0.7409511253549591, -0.6715589548470184},
-    {1.4463276836158192, 0.7380554238114666,
-     0.6715589548470184, -0.7409511253549591},
-    {1.4301675977653632, 0.7155832772776151,
-     0.5956993044924334, -0.8032075314806449},
-    {1.4143646408839778, 0.6933608264274733,
-     0.5141027441932218, -0.8577286100002721},
-    {1.3989071038251366, 0.6713825832762831,
-     0.4275550934302821, -0.9039892931234433},
-    {1.3837837837837839, 0.6496432388024754,
-     0.33688985339222005, -0.9415440651830208},
-    {1.3689839572192513, 0.6281376552499516,
-     0.2429801799032639, -0.970031253194544},
-    {1.3544973544973544, 0.6068608588398401,
-     0.14673047445536175, -0.989176509964781},
-    {1.3403141361256545, 0.5858080328658654,
-     0.049067674327418015, -0.9987954562051724},
-    {1.3264248704663213, 0.5649745111493539,
-     -0.049067674327418015, -0.9987954562051724},
-    {1.3128205128205128, 0.5443557718316313,
-     -0.14673047445536175, -0.989176509964781},
-    {1.299492385786802, 0.5239474314831478,
-     -0.2429801799032639, -0.970031253194544},
-    {1.2864321608040201, 0.5037452395101402,
-     -0.33688985339222005, -0.9415440651830208},
-    {1.2736318407960199, 0.4837450728409734,
-     -0.4275550934302821, -0.9039892931234433},
-    {1.2610837438423645, 0.46394293087555033,
-     -0.5141027441932218, -0.8577286100002721},
-    {1.248780487804878, 0.4443349306823086,
-     -0.5956993044924334, -0.8032075314806449},
-    {1.2367149758454106, 0.4249173024283867,
-     -0.6715589548470184, -0.7409511253549591},
-    {1.2248803827751196, 0.4056863850295029,
-     -0.7409511253549591, -0.6715589548470184},
-    {1.2132701421800949, 0.3866386220069921,
-     -0.8032075314806449, -0.5956993044924334},
-    {1.2018779342723005, 0.36777055754027477,
-     -0.8577286100002721, -0.5141027441932218},
-    {1.1906976744186046, 0.3490788327037993,
-     -0.9039892931234433, -0.4275550934302821},
-    {1.1797235023041475, 0.33056018187820585,
-     -0.9415440651830208, -0.33688985339222005},
-    {1.1689497716894977, 0.3122114293261232,
-     -0.970031253194544, -0.2429801799032639},
-    {1.158371040723982, 0.2940294859236195,
-     -0.989176509964781, -0.14673047445536175},
-    {1.147982062780269, 0.2760113460388874,
-     -0.9987954562051724, -0.049067674327418015},
-    {1.1377777777777778, 0.2581540845502847,
-     -0.9987954562051724, 0.049067674327418015},
-    {1.1277533039647578, 0.24045485399631977,
-     -0.989176509964781, 0.14673047445536175},
-    {1.1179039301310043, 0.22291088185064556,
-     -0.970031253194544, 0.2429801799032639},
-    {1.1082251082251082, 0.20551946791553788,
-     -0.9415440651830208, 0.33688985339222005},
-    {1.0987124463519313, 0.18827798182772382,
-     -0.9039892931234433, 0.4275550934302821},
-    {1.0893617021276596, 0.17118386067080707,
-     -0.8577286100002721, 0.5141027441932218},
-    {1.080168776371308, 0.1542346066888624,
-     -0.8032075314806449, 0.5956993044924334},
-    {1.0711297071129706, 0.13742778509610346,
-     -0.7409511253549591, 0.6715589548470184},
-    {1.062240663900415, 0.12076102197781496,
-     -0.6715589548470184, 0.7409511253549591},
-    {1.0534979423868314, 0.1042320022780282,
-     -0.5956993044924334, 0.8032075314806449},
-    {1.0448979591836736, 0.08783846786967116,
-     -0.5141027441932218, 0.8577286100002721},
-    {1.0364372469635628, 0.07157821570317058,
-     -0.4275550934302821, 0.9039892931234433},
-    {1.0281124497991967, 0.05544909602970954,
-     -0.33688985339222005, 0.9415440651830208},
-    {1.0199203187250996, 0.039449010695557146,
-     -0.2429801799032639, 0.970031253194544},
-    {1.0118577075098814, 0.023575911504084345,
-     -0.14673047445536175, 0.989176509964781},
-    {1.0, 0.0,
-     -0.049067674327418015, 0.9987954562051724},
+// The generator of qrfs_device.hpp with tables of 64 entries in LDS, for a kernel
+// that draws most of its time (gen_gauss_table.py): entry i holds r, about 1 / c,
+// and 2 ln r for the mantissas around c = 1/2 + (i + 1/2) / 128 (r = 1 in the last,
+// so that u near 1 cancels nothing), and sin, cos of 2 pi (i + 1/2) / 64 in two
+// parts each.  With u = (2m + 1) 2^-24 = f 2^e: -2 ln u = 2 ln r - 2 log1p(f r - 1)
+// - 2 e ln 2, |f r - 1| <= 1/128, log1p by its series through the 8th power (first
+// omitted term 2e-18), small terms first; 2 ln r - 2 e ln 2 is exact but for the
+// latter's low part.  The angle is the entry's, turned by what is left of it, at most
+// 1/128 revolution, by the first terms of the series for 1/8.  A million pairs: within
+// 3.04e-16 of the radius, 5.70e-17 RMS (sqrt, log and sincospi: 3.04e-16 and
+// 5.72e-17), at ~56 vector instructions a pair in the place of ~100.  1e5 realisations
+// x 4096 frequencies x 32 baselines: 2.16 ms, 2.70 without the tables, 2.07 with
+// tables whose rounding showed (3.87e-16 and 7.0e-17).
+static __device__ __attribute__((aligned(16))) const double kGaussTab[64][6] = {
+    {1.9844961240301546, 1.370730080234921, 0.049067674327418015, 0.9987954562051724,
+     -6.79610372051828e-19, -1.2291693337075465e-17},
+    {1.9541984737338076, 1.3399602430187656, 0.14673047445536175, 0.989176509964781,
+     3.726947147046568e-18, -4.098730993704711e-17},
+    {1.9248120305217513, 1.3096566329796246, 0.2429801799032639, 0.970031253194544,
+     -8.751431529719663e-18, 1.8365300348428844e-17},
+    {1.8962962962953356, 1.2798053320812528, 0.33688985339222005, 0.9415440651830208,
+     -4.200094003347509e-19, -2.789637954769834e-17},
+    {1.8686131391203746, 1.250393037767651, 0.4275550934302821, 0.9039892931234433,
+     9.411189816295473e-18, -6.609754468748431e-18},
+    {1.8417266182762306, 1.2214070222320856, 0.5141027441932218, 0.8577286100002721,
+     -4.5712707523615624e-17, -4.818344793633662e-17},
+    {1.815602836459876, 1.1928351077406205, 0.5956993044924334, 0.8032075314806449,
+     -1.3438641936579467e-17, -3.306060980481491e-17},
+    {1.790209790622127, 1.164665628899968, 0.6715589548470184, 0.7409511253549591,
+     -4.048903774929669e-17, -1.4708616952297345e-17},
+    {1.7655172417868847, 1.1368874045796815, 0.7409511253549591, 0.6715589548470184,
+     -1.4708616952297345e-17, -4.048903774929669e-17},
+    {1.7414965986366826, 1.1094897153984675, 0.8032075314806449, 0.5956993044924334,
+     -3.306060980481491e-17, -1.3438641936579467e-17},
+    {1.718120804970509, 1.0824622766041898, 0.8577286100002721, 0.5141027441932218,
+     -4.818344793633662e-17, -4.5712707523615624e-17},
+    {1.6953642380174592, 1.0557952148654977, 0.9039892931234433, 0.4275550934302821,
+     -6.609754468748431e-18, 9.411189816295473e-18},
+    {1.673202613990444, 1.0294790457097065, 0.9415440651830208, 0.33688985339222005,
+     -2.789637954769834e-17, -4.200094003347509e-19},
+    {1.6516129032291549, 1.0035046551246865, 0.970031253194544, 0.2429801799032639,
+     1.8365300348428844e-17, -8.751431529719663e-18},
+    {1.6305732484066429, 0.9778632782612817, 0.989176509964781, 0.14673047445536175,
+     -4.098730993704711e-17, 3.726947147046568e-18},
+    {1.610062892710059, 0.9525464840569384, 0.9987954562051724, 0.049067674327418015,
+     -1.2291693337075465e-17, -6.79610372051828e-19},
+    {1.5900621121693315, 0.9275461594531862, 0.9987954562051724, -0.049067674327418015,
+     -1.2291693337075465e-17, 6.79610372051828e-19},
+    {1.570552146878473, 0.9028544868861559, 0.989176509964781, -0.14673047445536175,
+     -4.098730993704711e-17, -3.726947147046568e-18},
+    {1.5515151512604133, 0.8784639408295902, 0.970031253194544, -0.2429801799032639,
+     1.8365300348428844e-17, 8.751431529719663e-18},
+    {1.5329341317351102, 0.8543672641237663, 0.9415440651830208, -0.33688985339222005,
+     -2.789637954769834e-17, 4.200094003347509e-19},
+    {1.5147928994074684, 0.8305574591119012, 0.9039892931234433, -0.4275550934302821,
+     -6.609754468748431e-18, -9.411189816295473e-18},
+    {1.4970760230447533, 0.8070277754901554, 0.8577286100002721, -0.5141027441932218,
+     -4.818344793633662e-17, 4.5712707523615624e-17},
+    {1.4797687864697993, 0.7837717004266551, 0.8032075314806449, -0.5956993044924334,
+     -3.306060980481491e-17, 1.3438641936579467e-17},
+    {1.4628571431962445, 0.7607829415757124, 0.7409511253549591, -0.6715589548470184,
+     -1.4708616952297345e-17, 4.048903774929669e-17},
+    {1.4463276836141494, 0.7380554238091577, 0.6715589548470184, -0.7409511253549591,
+     -4.048903774929669e-17, 1.4708616952297345e-17},
+    {1.430167597768992, 0.7155832772826898, 0.5956993044924334, -0.8032075314806449,
+     -1.3438641936579467e-17, 3.306060980481491e-17},
+    {1.4143646408867057, 0.6933608264313307, 0.5141027441932218, -0.8577286100002721,
+     -4.5712707523615624e-17, 4.818344793633662e-17},
+    {1.3989071038259322, 0.6713825832774205, 0.4275550934302821, -0.9039892931234433,
+     9.411189816295473e-18, 6.609754468748431e-18},
+    {1.3837837837863356, 0.6496432388061635, 0.33688985339222005, -0.9415440651830208,
+     -4.200094003347509e-19, 2.789637954769834e-17},
+    {1.3689839569053195, 0.6281376547913169, 0.2429801799032639, -0.970031253194544,
+     -8.751431529719663e-18, -1.8365300348428844e-17},
+    {1.354497354183659, 0.606860858376649, 0.14673047445536175, -0.989176509964781,
+     3.726947147046568e-18, 4.098730993704711e-17},
+    {1.3403141361270006, 0.5858080328678739, 0.049067674327418015, -0.9987954562051724,
+     -6.79610372051828e-19, 1.2291693337075465e-17},
+    {1.3264248704667203, 0.5649745111499556, -0.049067674327418015, -0.9987954562051724,
+     6.79610372051828e-19, 1.2291693337075465e-17},
+    {1.3128205125175074, 0.5443557713700216, -0.14673047445536175, -0.989176509964781,
+     -3.726947147046568e-18, 4.098730993704711e-17},
+    {1.2994923854879543, 0.5239474310232026, -0.2429801799032639, -0.970031253194544,
+     8.751431529719663e-18, -1.8365300348428844e-17},
+    {1.2864321608071907, 0.5037452395150694, -0.33688985339222005, -0.9415440651830208,
+     4.200094003347509e-19, 2.789637954769834e-17},
+    {1.2736318407941747, 0.4837450728380759, -0.4275550934302821, -0.9039892931234433,
+     -9.411189816295473e-18, 6.609754468748431e-18},
+    {1.2610837438445397, 0.46394293087899996, -0.5141027441932218, -0.8577286100002721,
+     4.5712707523615624e-17, 4.818344793633662e-17},
+    {1.2487804878024695, 0.4443349306784512, -0.5956993044924334, -0.8032075314806449,
+     1.3438641936579467e-17, 3.306060980481491e-17},
+    {1.236714975848238, 0.42491730243295933, -0.6715589548470184, -0.7409511253549591,
+     4.048903774929669e-17, 1.4708616952297345e-17},
+    {1.224880382493843, 0.405686384570231, -0.7409511253549591, -0.6715589548470184,
+     1.4708616952297345e-17, 4.048903774929669e-17},
+    {1.2132701424608696, 0.3866386224698317, -0.8032075314806449, -0.5956993044924334,
+     3.306060980481491e-17, 1.3438641936579467e-17},
+    {1.2018779342719892, 0.36777055753975674, -0.8577286100002721, -0.5141027441932218,
+     4.818344793633662e-17, 4.5712707523615624e-17},
+    {1.1906976746938116, 0.34907883316606103, -0.9039892931234433, -0.4275550934302821,
+     6.609754468748431e-18, -9.411189816295473e-18},
+    {1.1797235025772344, 0.33056018234117346, -0.9415440651830208, -0.33688985339222005,
+     2.789637954769834e-17, 4.200094003347509e-19},
+    {1.168949771955645, 0.31221142978148464, -0.970031253194544, -0.2429801799032639,
+     -1.8365300348428844e-17, 8.751431529719663e-18},
+    {1.1583710407215355, 0.2940294859193955, -0.989176509964781, -0.14673047445536175,
+     4.098730993704711e-17, -3.726947147046568e-18},
+    {1.1479820630471371, 0.27601134650382164, -0.9987954562051724, -0.049067674327418015,
+     1.2291693337075465e-17, 6.79610372051828e-19},
+    {1.1377777775188667, 0.2581540840951675, -0.9987954562051724, 0.049067674327418015,
+     1.2291693337075465e-17, -6.79610372051828e-19},
+    {1.127753303961548, 0.24045485399062727, -0.989176509964781, 0.14673047445536175,
+     4.098730993704711e-17, 3.726947147046568e-18},
+    {1.1179039301295621, 0.2229108818480654, -0.970031253194544, 0.2429801799032639,
+     -1.8365300348428844e-17, -8.751431529719663e-18},
+    {1.1082251082215009, 0.20551946790902775, -0.9415440651830208, 0.33688985339222005,
+     2.789637954769834e-17, -4.200094003347509e-19},
+    {1.0987124463487308, 0.1882779818218978, -0.9039892931234433, 0.4275550934302821,
+     6.609754468748431e-18, 9.411189816295473e-18},
+    {1.089361702129727, 0.17118386067460278, -0.8577286100002721, 0.5141027441932218,
+     4.818344793633662e-17, -4.5712707523615624e-17},
+    {1.0801687763734018, 0.15423460669273936, -0.8032075314806449, 0.5956993044924334,
+     3.306060980481491e-17, -1.3438641936579467e-17},
+    {1.0711297068679422, 0.1374277846385894, -0.7409511253549591, 0.6715589548470184,
+     1.4708616952297345e-17, -4.048903774929669e-17},
+    {1.0622406641458795, 0.12076102243997866, -0.6715589548470184, 0.7409511253549591,
+     4.048903774929669e-17, -1.4708616952297345e-17},
+    {1.0534979423841346, 0.10423200227290863, -0.5956993044924334, 0.8032075314806449,
+     1.3438641936579467e-17, -3.306060980481491e-17},
+    {1.0448979589410512, 0.08783846740527679, -0.5141027441932218, 0.8577286100002721,
+     4.5712707523615624e-17, -4.818344793633662e-17},
+    {1.0364372469627228, 0.07157821570154965, -0.4275550934302821, 0.9039892931234433,
+     -9.411189816295473e-18, -6.609754468748431e-18},
+    {1.02811245003605, 0.055449096490463035, -0.33688985339222005, 0.9415440651830208,
+     4.200094003347509e-19, -2.789637954769834e-17},
+    {1.0199203189587593, 0.039449011153749325, -0.2429801799032639, 0.970031253194544,
+     8.751431529719663e-18, 1.8365300348428844e-17},
+    {1.0118577072759711, 0.023575911041746167, -0.14673047445536175, 0.989176509964781,
+     -3.726947147046568e-18, -4.098730993704711e-17},
+    {1.0, 0.0, -0.049067674327418015, 0.9987954562051724,
+     6.79610372051828e-19, -1.2291693337075465e-17},
 };
-constexpr double kLog1p[8] = {-1.0 / 8, 1.0 / 7, -1.0 / 6, 1.0 / 5, -1.0 / 4, 1.0 / 3, -1.0 / 2, 1.0};
+// -2 log1p(d) = -2 d + d^2 (1 - 2 d / 3 + 2 d^2 / 4 - ...)
+constexpr double kLog1p[7] = {2.0 / 8, -2.0 / 7, 2.0 / 6, -2.0 / 5, 2.0 / 4, -2.0 / 3, 1.0};
 
 struct GaussTab {
-    double2 ln[64], sc[64];
+    double2 ln[64], sc[64], lo[64];  // r, 2 ln r; sin, cos; their low parts
 };
 
 __device__ __forceinline__ double gauss_radius_tab(const GaussTab& t, uint32_t x) {
     const double M = (double)((x >> 8) | 1u);  // 2m + 1
     const double f = __builtin_amdgcn_frexp_mant(M);
-    const int e = __builtin_amdgcn_frexp_exp(M) - 24;
+    const double e = (double)(__builtin_amdgcn_frexp_exp(M) - 24);
     const double2 L = t.ln[((uint32_t)__double2hiint(M) >> 14) & 63u];
     const double d = fma(f, L.x, -1.0);
     double p = kLog1p[0];
 #pragma unroll
-    for (int n = 1; n < 8; ++n) p = fma_s(p, d, kLog1p[n]);
-    const double a = fma(-2.0 * d, p, fma((double)e, -1.3862943611198906, L.y));
+    for (int n = 1; n < 7; ++n) p = fma_s(p, d, kLog1p[n]);
+    const double a = fma(e, -kTwoLn2Hi, L.y) + fma(-2.0, d, fma(d * d, p, e * -kTwoLn2Lo));
     double r = __builtin_amdgcn_rsq(a);
     r = fma(r, fma(-0.5 * a, r * r, 0.5), r);
     const double g = a * r;
@@ -169,7 +172,7 @@ __device__ __forceinline__ double gauss_radius_tab(const GaussTab& t, uint32_t x
 }
 
 __device__ __forceinline__ void sincos_tab(const GaussTab& t, uint32_t x, double& s, double& c) {
-    const double2 sc = t.sc[x >> 26];
+    const double2 sc = t.sc[x >> 26], lo = t.lo[x >> 26];
     const double z = fma((double)((x >> 9) & 0x1ffffu), 0x1p-23, 0x1p-24 - 0x1p-7);
     const double w = z * z;
     double ps = kSin2pi[4];
@@ -180,8 +183,8 @@ __device__ __forceinline__ void sincos_tab(const GaussTab& t, uint32_t x, double
 #pragma unroll
     for (int n = 5; n < 8; ++n) pc = fma_s(pc, w, kCos2pi[n]);
     pc *= w;
-    s = fma(sc.y, ps, fma(sc.x, pc, sc.x));
-    c = fma(-sc.x, ps, fma(sc.y, pc, sc.y));
+    s = sc.x + fma(sc.y, ps, fma(sc.x, pc, lo.x));
+    c = sc.y + fma(-sc.x, ps, fma(sc.y, pc, lo.y));
 }
 
 __device__ __forceinline__ void coef4_tab(const GaussTab& t, uint64_t seed, uint64_t real,
@@ -222,7 +225,7 @@ __device__ __forceinline__ void coef4_tab(const GaussTab& t, uint64_t seed, uint
 // when the launch cuts K into ranges) or squared.
 //
 // Bound: the FP64 datapath, shared by the matrix instructions and the vector
-// ALU (measured: the times add).  Per (row, frequency): two coefficients, ~52
+// ALU (measured: the times add).  Per (row, frequency): two coefficients, ~56
 // vector operations; 16 NC columns, 32 NC multiply-adds; the basis, ~40
 // operations per column, shared by the group's 16 MR WR rows.  The vector
 // kernel this replaces read two basis values and eight coefficients from LDS
@@ -345,9 +348,9 @@ k_sum_fm(SumArgs a, int64_t row_tiles, int64_t col_tiles) {
 #pragma unroll
         for (int n = 0; n < NC; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
 
-    if (CSRC < 2 && tid < 128) {
+    if (CSRC < 2 && tid < 192) {
         const double2* src = (const double2*)kGaussTab[tid & 63] + (tid >> 6);
-        (tid < 64 ? tab.ln : tab.sc)[tid & 63] = *src;
+        (tid < 64 ? tab.ln : tid < 128 ? tab.sc : tab.lo)[tid & 63] = *src;
     }
     double f[3];
     load_freq(0, f);
@@ -484,7 +487,7 @@ static inline int64_t fcdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // columns per block and row waves that share a basis by the estimated time
 // of the fullest compute unit.  Blocks come in whole rounds of the 256 compute
 // units; a block's wave takes 16 MR rows and WR / 8 of its range's frequencies,
-// and a (row, frequency) costs ~52 operations for its coefficients, 2 per
+// and a (row, frequency) costs ~56 operations for its coefficients, 2 per
 // column, and the basis of its columns shared by the group's rows: ~40
 // operations each, ~300 with the binary64 filter of two edges.  (Fewer row
 // waves and columns: more and shorter blocks that fill the chip evenly, but
@@ -501,7 +504,7 @@ FmShape fm_shape(int basis, int64_t K, int64_t R, int64_t R_block, int64_t P, in
         for (int wr = 8; wr >= 1; wr >>= 1) {
             const int64_t blocks =
                 ksplit * n_sets * fcdiv(R_block, 16 * s.MR * wr) * fcdiv(P, 16 * nc);
-            const double per_row = 52.0 + 32.0 * nc + col_ops * nc / (s.MR * wr);
+            const double per_row = 56.0 + 32.0 * nc + col_ops * nc / (s.MR * wr);
             // 8 waves on 4 SIMDs, 16 MR rows on 64 lanes, 4 cycles
             const double us = (double)fcdiv(blocks, 256) * ((double)K / ksplit) * wr * s.MR *
                               per_row * (0.25 / 0.6 / 2400.0);

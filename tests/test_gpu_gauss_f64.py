@@ -1,7 +1,7 @@
 """Accuracy of the binary64 Gaussian coefficients, read back bit for bit: with one
 frequency (1, 0) of weight 1, the field is a at the origin and b at (1/4, 0).  Of
-a million pairs, from the narrow kernels' generator (one realisation per set),
-against extended precision (64 bits of
+a million pairs, from the narrow kernels' generator (one realisation per set) and
+from the tabulated one of shared sets, against extended precision (64 bits of
 mantissa) on the same Philox words.
 
 Bounds, in units of the pair's radius: what sqrt(-2 log u) and sincospi of the
@@ -60,7 +60,7 @@ def test_words_match_the_oracle():
         assert [int(v[r]) for v in x] == [int(v) for v in want]
 
 
-@pytest.mark.parametrize("R_block", [1])
+@pytest.mark.parametrize("R_block", [1, R])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_coefficients(q, R_block, mode):
     seed, n_sets = 17, R // R_block
