@@ -380,7 +380,26 @@ bool is_capturing(hipStream_t st) {
     return cap != hipStreamCaptureStatusNone;
 }
 
-// Most workspace that the partial sums of a stored contraction take.
+// Partial sums of the frozen-flow estimator in blocks of `rows` realisations.
+size_t temporal_part_bytes(int64_t R, int64_t M, int rows) {
+    return align256((size_t)cdiv(R, rows) * M * 2 * sizeof(double));
+}
+
+// The estimator's workspace, with `fixed` bytes besides, and its blocks' rows: the
+// longer blocks halve the partial sums where the workspace is capped, cannot grow
+// (under capture) or finds no memory.
+qrfs_status temporal_workspace(qrfs_context* ctx, int64_t R, int64_t M, size_t fixed,
+                               hipStream_t st, int* rows) {
+    *rows = qrfs::TEMPORAL_ROWS;
+    const size_t bytes = fixed + temporal_part_bytes(R, M, *rows);
+    qrfs_status s = QRFS_ERR_OUT_OF_MEMORY;
+    if (!(bytes > ctx->ws_size && is_capturing(st))) s = ensure_workspace(ctx, bytes);
+    if (s != QRFS_ERR_OUT_OF_MEMORY) return s;
+    *rows = qrfs::TEMPORAL_ROWS_CAPPED;
+    return ensure_workspace(ctx, fixed + temporal_part_bytes(R, M, *rows));
+}
+
+// Most scratch that the partial sums of a stored contraction take.
 constexpr size_t kSplitCap = (size_t)256 << 20;
 
 // Stored sums in the fused kernels.  Where their tiles leave compute units
@@ -1146,15 +1165,10 @@ qrfs_status qrfs_temporal_sf(qrfs_context* ctx, int64_t R, int64_t M, int32_t pr
     if (!ctx) return fail(QRFS_ERR_INVALID_ARG, "context is NULL");
     DeviceGuard g(ctx->device);
     if (!g.okay) return fail(QRFS_ERR_DEVICE, "cannot select device %d", ctx->device);
-    int rows = qrfs::TEMPORAL_ROWS;
-    // the longer blocks halve the workspace where it is capped, or cannot grow
-    const size_t bytes = align256((size_t)cdiv(R, rows) * M * 2 * sizeof(double));
-    if ((ctx->ws_cap && bytes > ctx->ws_cap) ||
-        (bytes > ctx->ws_size && is_capturing((hipStream_t)stream)))
-        rows = qrfs::TEMPORAL_ROWS_CAPPED;
-    const int64_t nb = cdiv(R, rows);
-    qrfs_status st = ensure_workspace(ctx, align256((size_t)nb * M * 2 * sizeof(double)));
+    int rows;
+    qrfs_status st = temporal_workspace(ctx, R, M, 0, (hipStream_t)stream, &rows);
     if (st) return st;
+    const int64_t nb = cdiv(R, rows);
     double* part = (double*)ctx->ws;
     hipStream_t stream_ = (hipStream_t)stream;
     hipError_t e = qrfs::launch_temporal_rows(precision == QRFS_PREC_FP64, false, pistons, R, M,
@@ -1218,14 +1232,11 @@ qrfs_status qrfs_temporal_piston_structure(qrfs_context* ctx, const qrfs_psd* ps
     // such a series keeps the differential pistons only
     const size_t pist_bytes = align256((size_t)spb * R_block * (series ? M : P) * esize);
     const size_t fixed_bytes = 2 * pt_bytes + 4 * arr + pist_bytes;
-    int rows_block = qrfs::TEMPORAL_ROWS;
-    size_t part_bytes = align256((size_t)cdiv(R, rows_block) * M * 2 * sizeof(double));
-    if (ctx->ws_cap && part_bytes + fixed_bytes > ctx->ws_cap) {
-        rows_block = qrfs::TEMPORAL_ROWS_CAPPED;
-        part_bytes = align256((size_t)cdiv(R, rows_block) * M * 2 * sizeof(double));
-    }
+    int rows_block;
+    if ((st = temporal_workspace(ctx, R, M, fixed_bytes, (hipStream_t)stream, &rows_block)))
+        return st;
     const int64_t nb = cdiv(R, rows_block);
-    if ((st = ensure_workspace(ctx, part_bytes + fixed_bytes))) return st;
+    const size_t part_bytes = temporal_part_bytes(R, M, rows_block);
     char* base = (char*)ctx->ws;
     double* part = (double*)base;
     double* px = (double*)(base + part_bytes);

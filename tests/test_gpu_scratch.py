@@ -227,3 +227,34 @@ def test_full_problem_without_room_for_ranges(q):
         ref = oracle.synthesize(host(fx), host(fy), host(w), host(px)[sel], host(py)[sel], R, R,
                                 K=K, seed=1)
         assert np.max(np.abs(host(out)[:, sel] - ref)) <= TOL[1] * math.sqrt(np.mean(ref * ref))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_captured_time_series_in_the_smaller_workspace(q, precision):
+    """A workspace with room for the estimator's longer blocks only, which cannot
+    grow under capture."""
+    K, M, R, R_block = 64, 1024, 2000, 50
+    with q.Context(0) as c:
+        args = (q.psd(0.1, 25.0), q.Aperture(8.0, 1.1), (0.0, 0.0), (56.5, 0.0), (10.2, 0.0), 1e-3, M)
+        tail = (K, R, R_block)
+        kw = dict(rng=q.Rng(3, 0, 0), precision=precision)
+        # 4.1 MB of partial sums (8.2 in shorter blocks) and 16.4 MB of pistons, of
+        # two telescopes in FP32, of their differences in FP64; frequencies
+        n = 670000  # 21.4 MB
+        gx, gy, _ = c.sample_frequencies(q.logpolar_sampler(1e-3, 1e2), n, 4)
+        c.point_set_measures(gx, gy, n, 4, -100.0, -100.0, 200.0, 200.0, 0.1)
+        torch.cuda.synchronize()
+        print(f"series p{precision}", flush=True)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            sf, se = c.temporal_piston_structure(*args, q.cartesian_sampler(8, 0.25 / 22.0), *tail,
+                                                 **kw)
+        for _ in range(2):
+            sf.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            with q.Context(0) as other:
+                ref, ref_se = other.temporal_piston_structure(
+                    *args, q.cartesian_sampler(8, 0.25 / 22.0), *tail, **kw)
+            assert np.allclose(host(sf), host(ref), rtol=1e-12, atol=0)
+            assert np.allclose(host(se), host(ref_se), rtol=1e-9, atol=0)
