@@ -401,17 +401,20 @@ qrfs_status temporal_workspace(qrfs_context* ctx, int64_t R, int64_t M, size_t f
 
 // Most scratch that the partial sums of a stored contraction take.
 constexpr size_t kSplitCap = (size_t)256 << 20;
+size_t split_room(const qrfs_context* ctx) {
+    return scratch_room(ctx) < kSplitCap ? scratch_room(ctx) : kSplitCap;
+}
 
 // Stored sums in the fused kernels.  Where their tiles leave compute units
 // idle, K is cut into ranges whose partial sums go through the scratch; not
 // beyond the context's cap, and not while the stream is being captured (a
 // graph must not hold memory that a later call may replace): then one range,
 // which needs none.
-qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a, int64_t n_sets,
-                      hipStream_t st) {
-    const size_t room = scratch_room(ctx) < kSplitCap ? scratch_room(ctx) : kSplitCap;
-    qrfs::StoreSplit sp =
-        qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, room);
+// sp: the split for split_room, or ksplit = 0.
+qrfs_status fused_sum(qrfs_context* ctx, int precision, int basis, qrfs::SumArgs a,
+                      qrfs::StoreSplit sp, int64_t n_sets, hipStream_t st) {
+    if (sp.ksplit == 0)
+        sp = qrfs::store_split(precision, basis, a.K, a.R, a.R_block, a.P, split_room(ctx));
     char* part = nullptr;
     if (sp.ksplit > 1) {
         part = is_capturing(st) ? nullptr : scratch_block(ctx, sp.bytes);
@@ -586,8 +589,10 @@ int64_t wide_least_freqs(int precision, int basis, bool tilt) {
 // this one 66, at ten apertures x 1e4 realisations 115 and 433.  Captured calls
 // keep to problems that fill the chip whatever the path: a call that needs no
 // workspace must not take one under capture.
+// `sp` receives the fused kernels' ranges and time where they were estimated.
 bool use_wide(const qrfs_context* ctx, int precision, int basis, bool tilt, int64_t K, int64_t P,
-              int64_t R, int64_t R_block, bool caller_coef, hipStream_t st, int* ksplit) {
+              int64_t R, int64_t R_block, bool caller_coef, hipStream_t st, int* ksplit,
+              qrfs::StoreSplit* sp) {
     *ksplit = 1;
     if (precision == QRFS_PREC_FP64 || ctx->wide_path == 1) return false;
     // FP16X3 scales the coefficient tiles by the largest value the generators
@@ -599,7 +604,8 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, bool tilt, int6
     if (ctx->wide_path == 2) return true;  // as asked, in one range whatever the cap
     if (is_capturing(st)) return full;
     if (!full && (R_block <= 8 || K < wide_least_freqs(precision, basis, tilt))) return false;
-    const double fused = qrfs::store_split(precision, basis, K, R, R_block, P, kSplitCap).us;
+    *sp = qrfs::store_split(precision, basis, K, R, R_block, P, split_room(ctx));
+    const double fused = sp->us;
     double best = 1e300;
     const double coef = 2.3e-6 * (double)(cdiv(R, R_block) * cdiv(R_block, 256) * 256) * (double)K;
     const double one_us = 2.0 / 4e6 * (double)R * (double)P * sizeof(float);  // written and read
@@ -765,8 +771,9 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
         a.gy = 2.0 * M_PI * grad_u[1];
     }
     int ksplit = 1;
+    qrfs::StoreSplit sp{};
     bool wide = use_wide(ctx, precision, basis, grad_u != nullptr, K, P, R, R_block,
-                         coef != nullptr, (hipStream_t)stream, &ksplit);
+                         coef != nullptr, (hipStream_t)stream, &ksplit, &sp);
     if (wide) {
         s = wide_sum(ctx, precision, basis, a, cdiv(R, R_block), ksplit, (hipStream_t)stream);
         // no memory for its tiles (nothing is enqueued yet): the fused kernel
@@ -774,7 +781,7 @@ qrfs_status sum_entry(qrfs_context* ctx, int basis, int64_t K, const double* fx,
         wide = !(s == QRFS_ERR_OUT_OF_MEMORY && ctx->wide_path == 0 && !wide_fills(P, R, R_block));
     }
     if (!wide)
-        s = fused_sum(ctx, precision, basis, a, cdiv(R, R_block), (hipStream_t)stream);
+        s = fused_sum(ctx, precision, basis, a, sp, cdiv(R, R_block), (hipStream_t)stream);
     if (s) return s;
     return ok();
 }

@@ -318,12 +318,12 @@ qrfs_status qrfs_proposal_train(qrfs_proposal* p, int64_t n_ctx, int64_t m, cons
     if (e == hipSuccess) e = hipStreamSynchronize(strm);
     if (e != hipSuccess) return hfail(e, "upload of the context order");
     for (int64_t k = 0; k < steps; ++k) {
-        p->t += 1;
         e = qrfs::prop_launch_step(p->prm, s.z, ctx_per_step, m, s.ctxlist + k * ctx_per_step, ctx4,
                                    ell, theta, h, G, p->lmin, p->Lw, s.dscr, s.fscr, s.gpart,
                                    p->grad, loss_log ? loss_log + k : nullptr, p->m1, p->m2,
-                                   (float)lr, p->t, strm);
+                                   (float)lr, p->t + 1, strm);
         if (e != hipSuccess) return hfail(e, "training step");
+        p->t += 1;
     }
     return api_ok();
 }
