@@ -358,6 +358,10 @@ QRFS_API qrfs_status qrfs_choose_cartesian(const qrfs_psd* psd, const qrfs_apert
  * required), or double[R][2K] (c[2k] = a, c[2k+1] = b) supplied by the
  * caller (rng ignored).  phase: double[R][P] for QRFS_PREC_FP64, float[R][P]
  * otherwise (row-major).
+ * How the sum over K is cut, and so the result's last bits, may depend on R,
+ * R_block, P, the context's cap and tuning, the memory at hand, and on whether
+ * the call is captured in a graph or runs at once; so too for qrfs_piston,
+ * qrfs_tilt and qrfs_diff_piston.
  * Errors: K, P, R <= 0; R_block outside [1, R]; NULL arrays; unknown
  * precision; rng NULL with coef NULL; unknown coefficient mode. */
 QRFS_API qrfs_status qrfs_synthesize_phase(qrfs_context* ctx, int64_t K, const double* fx,

@@ -586,7 +586,8 @@ int64_t wide_least_freqs(int precision, int basis, bool tilt) {
 // is drawn once (2.3 ps per padded row and frequency).  Fused: see store_split
 // (coefficients redrawn per column tile).  At 100 realisations (50 per set) of
 // 2500 points x 4096 frequencies in FP16x3 the fused kernel takes 139 us and
-// this one 66, at ten apertures x 1e4 realisations 115 and 433.  Captured calls
+// this one 66, at ten apertures x 1e4 realisations 115 and 433.  A further range
+// has to gain 5 %, this kernel 10 %: the estimates are no better.  Captured calls
 // keep to problems that fill the chip whatever the path: a call that needs no
 // workspace must not take one under capture.
 // `sp` receives the fused kernels' ranges and time where they were estimated.
@@ -616,7 +617,7 @@ bool use_wide(const qrfs_context* ctx, int precision, int basis, bool tilt, int6
     const double mean = (most * (double)(R_block / 256) +
                          (rest ? qrfs::wide_tile_ns(precision, basis, rest) : 0.0)) /
                         (double)cdiv(R_block, 256);
-    for (int k = 1; k <= 32 && (k == 1 || (int64_t)k * 64 <= K); ++k) {
+    for (int k = 1; k <= 32 && (k == 1 || (int64_t)k * 64 <= K); ++k) {  // as in store_split
         if (k > 1 && (size_t)k * R * P * sizeof(float) > kSplitCap) break;
         const int64_t rounds = cdiv(tiles * k, 256);
         const double ns = rounds > 1 ? std::fmax(most, mean * (double)rounds) : most;

@@ -18,9 +18,10 @@ namespace qrfs {
 // every realisation: R_block = 1): one point per thread, RB rows per block.
 // Per chunk of 64 frequencies the block stages fx, fy, w and the RB rows'
 // coefficients in LDS (drawn once per block); each thread evaluates its
-// point's basis once per frequency and adds it into its RB rows, in the
-// same order for any tiling.  A 16-row matrix tile
-// would spend most of its contraction on rows the set does not have.
+// point's basis once per frequency and adds it into its RB rows, in order
+// within the block's frequency range (how many ranges there are depends on R and
+// P, see store_split).  A 16-row matrix tile would spend most of its contraction
+// on rows the set does not have.
 constexpr int F64N_KC = 64;
 
 template <int BASIS, int RB>
@@ -1280,7 +1281,9 @@ hipError_t launch_split_sum(bool fp64, const void* part, int ksplit, int64_t n, 
 
 // A stored contraction is cut into frequency ranges when its tiles alone leave
 // compute units idle: its partial sums cost a second launch (8 us with the
-// host's part) and their traffic, against a range's share of the time.
+// host's part) and their traffic, against a range's share of the time.  A further
+// range has to gain 5 %: the estimates are no better.  Ranges have whole 64
+// frequencies, the longest chunk of any kernel.
 StoreSplit store_split(int precision, int basis, int64_t K, int64_t R, int64_t R_block, int64_t P,
                        size_t max_bytes) {
     StoreSplit s{1, K, 0, 0.0};

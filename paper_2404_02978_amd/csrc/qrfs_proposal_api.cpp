@@ -12,9 +12,8 @@
 #include "qrfs_internal.hpp"
 #include "qrfs_proposal.hpp"
 
-// rows of one loss/gradient or training step (plus at most 4M grid rows):
-// the network kernels take 64 rows per 256-thread block, so this keeps a
-// launch well within 2^32 work-items
+// rows of one loss/gradient or training step; with at most 4M grid rows they
+// stay well within the kernels' 32-bit row numbers
 static constexpr int64_t kMaxStepRows = (int64_t)1 << 29;
 
 namespace qrfs {
@@ -211,8 +210,6 @@ qrfs_status qrfs_proposal_set_params(qrfs_proposal* p, const float* src, void* s
 qrfs_status qrfs_proposal_forward(qrfs_proposal* p, int64_t n, const double* ell,
                                   const double* ctx4, float* out, void* stream) {
     if (!p) return api_fail(QRFS_ERR_INVALID_ARG, "proposal is NULL");
-    // 64 points per 256-thread block: at most 2^30 - 2^16 points keep the
-    // launch within 2^32 work-items
     if (n <= 0 || n > ((int64_t)1 << 30) - ((int64_t)1 << 16))
         return api_fail(QRFS_ERR_INVALID_ARG, "n must be in 1..2^30 - 2^16");
     if (!ell || !ctx4 || !out || !al8(ell) || !al8(ctx4) || !al4(out))
@@ -254,7 +251,6 @@ qrfs_status qrfs_proposal_loss_grad(qrfs_proposal* p, int64_t n_ctx, int64_t m,
     if (!p) return api_fail(QRFS_ERR_INVALID_ARG, "proposal is NULL");
     if (n_ctx <= 0 || n_ctx > 1024 || m <= 0 || G < 1 || G > 4096)
         return api_fail(QRFS_ERR_INVALID_ARG, "need 1 <= n_ctx <= 1024, m >= 1, 1 <= G <= 4096");
-    // rows of one step, 64 per 256-thread block, within 2^32 work-items
     if (n_ctx * m > kMaxStepRows)
         return api_fail(QRFS_ERR_INVALID_ARG, "n_ctx * m must be <= 2^29");
     if (!ctx4 || !ell || !theta || !h || !grad || !al8(ctx4) || !al8(ell) || !al8(theta) ||
