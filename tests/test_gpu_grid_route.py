@@ -147,3 +147,21 @@ def test_points_change_between_replays(q, ctx):
         got = host(out)
         assert np.max(np.abs(got[:, sel] - ref)) <= TOL[0] * math.sqrt(np.mean(ref * ref))
         assert np.all(np.isfinite(got))
+
+
+def test_blocks_of_several_items(q, ctx):
+    """Two tiles per realisation and half as many blocks: no block leaves its second
+    tile because the first block has not answered yet (600 calls, whose fields all
+    are the first one's)."""
+    K, R = 333, 300
+    px, py = grid(33, 31, "x")
+    fx, fy, w = frequencies(q, ctx, K, R, 1)
+    dx, dy = dev(px), dev(py)
+    out = torch.empty((R, px.size), dtype=torch.float64, device="cuda")
+    first, bad = None, torch.zeros((), dtype=torch.int64, device="cuda")
+    for _ in range(600):
+        out.fill_(float("nan"))
+        ctx.synthesize_phase(K, fx, fy, w, dx, dy, R, 1, rng=q.Rng(6, 21, 0), precision=0, out=out)
+        first = out.clone() if first is None else first
+        bad += (out != first).sum()
+    assert int(bad) == 0 and bool(torch.isfinite(first).all())
