@@ -64,8 +64,10 @@ __device__ __forceinline__ void turn(const double2& t, double& sn, double& cs) {
 // One output tile of realisation r (all threads of the block call it): the
 // lane's rows (rx, ry) and columns (cx, cy), frequencies fx, fy, w of the set.
 // emit(m, n, i, sum) receives element (16 m + lane / 16 + 4 i, 16 n + lane % 16).
+// Returns whether the lane met a weighted coefficient that is not finite: the
+// product of the two factors is then NaN where the sum of Eq. 3 is infinite.
 template <bool DIFF, int MU, int NV, int WV, typename Emit>
-__device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r,
+__device__ __forceinline__ bool sep_tile(double* sm, const SepArgs& a, int64_t r,
                                          const double (&rx)[MU], const double (&ry)[MU],
                                          const double (&cx)[NV], const double (&cy)[NV],
                                          const Emit& emit) {
@@ -81,6 +83,7 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
 #pragma unroll
         for (int n = 0; n < NV; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
 
+    bool finite = true;
     const int64_t kw = ((a.K + 8 * WV - 1) / (8 * WV)) * 8;
     const int64_t kb = wave * kw;
     const int64_t ke = kb + kw < a.K ? kb + kw : a.K;
@@ -105,6 +108,7 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
                 const double f0 = ok ? fx[k + h] : 0.0, f1 = ok ? fy[k + h] : 0.0;
                 const double wk = ok ? w[k + h] : 0.0;
                 double ca = wk * g[2 * h], cb = wk * g[2 * h + 1];
+                if constexpr (!DIFF) finite &= isfinite(ca) && isfinite(cb);
                 if constexpr (DIFF) {
                     double sh, ch;
                     sincos2pi_reduced(0.5 * frac_centered(f0 * a.dx + f1 * a.dy), sh, ch);
@@ -200,6 +204,7 @@ __device__ __forceinline__ void sep_tile(double* sm, const SepArgs& a, int64_t r
 #pragma unroll
                 for (int i = 0; i < 4; ++i) emit(m, n, i, acc[m][n][i]);
     }
+    return !finite;
 }
 
 template <int WV>
@@ -328,10 +333,13 @@ __device__ __forceinline__ void grid_tile(double* sm, const SepArgs& a, int64_t 
         cy[m] = xfast ? 0.0 : a.py[p];
     }
     T* out = (T*)a.out + r * a.P;
-    sep_tile<false, MU, NV, WV>(sm, a, r, rx, ry, cx, cy, [&](int m, int q, int i, double s) {
-        const int u = u0 + 16 * m + lh + 4 * i, v = v0 + 16 * q + li;
-        if (u < U && v < V) out[(int64_t)u * V + v] = (T)s;
-    });
+    const bool inf =
+        sep_tile<false, MU, NV, WV>(sm, a, r, rx, ry, cx, cy, [&](int m, int q, int i, double s) {
+            const int u = u0 + 16 * m + lh + 4 * i, v = v0 + 16 * q + li;
+            if (u < U && v < V) out[(int64_t)u * V + v] = (T)s;
+        });
+    // infinities go through the general kernel, as if the points were no grid
+    if (__any(inf) && lane == 0) atomicMax(g.word, 2 * g.id + 1);
 }
 
 // Sums on a grid: blocks take (realisation, tile) in turn, tiles at the edges in

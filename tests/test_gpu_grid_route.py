@@ -165,3 +165,31 @@ def test_blocks_of_several_items(q, ctx):
         first = out.clone() if first is None else first
         bad += (out != first).sum()
     assert int(bad) == 0 and bool(torch.isfinite(first).all())
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("kind", ["weight", "last weight", "coefficient", "nan"])
+def test_values_that_are_not_finite(q, ctx, kind, precision):
+    """Infinite and NaN weights and coefficients: the fields of the general kernel,
+    infinite where the sum is."""
+    K, R = (1100, 40) if precision == 0 else (8192, 40)
+    px, py = grid(32, 32, "x")
+    fx, fy, w = frequencies(q, ctx, K, R, 1)
+    coef = np.random.default_rng(2).normal(size=(R, 2 * K))
+    if kind == "weight":
+        w[K // 3] = float("inf")
+    elif kind == "last weight":
+        w[R * K - 1] = -float("inf")
+    elif kind == "coefficient":
+        coef[1, K], coef[7, 2 * K - 1] = np.inf, -np.inf
+    else:
+        coef[R - 1, 64] = np.nan
+    order = np.random.default_rng(0).permutation(px.size)
+    print(f"{kind} p{precision}", flush=True)
+    out = host(ctx.synthesize_phase(K, fx, fy, w, dev(px), dev(py), R, 1, coef=dev(coef),
+                                    precision=precision))
+    other = np.empty_like(out)
+    other[:, order] = host(ctx.synthesize_phase(K, fx, fy, w, dev(px[order]), dev(py[order]), R, 1,
+                                                coef=dev(coef), precision=precision))
+    assert not np.isfinite(other).all()
+    assert np.array_equal(out, other, equal_nan=True)
