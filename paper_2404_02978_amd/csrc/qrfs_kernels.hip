@@ -1178,15 +1178,20 @@ static int64_t sf_resident_slots(int precision, int64_t R_block, int64_t P) {
         const int64_t v = slot->load(std::memory_order_relaxed);
         if (v) return v;
     }
+    bool told = true;  // a guess in the place of a failed query is not kept
     if (!have_dev ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        ncu < 1)
+        ncu < 1) {
         ncu = 256;
+        told = false;
+    }
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 64 * s.WV, 0) != hipSuccess ||
-        nb < 1)
+        nb < 1) {
         nb = 1;
+        told = false;
+    }
     (void)hipGetLastError();
-    if (slot) slot->store((int64_t)ncu * nb, std::memory_order_relaxed);
+    if (slot && told) slot->store((int64_t)ncu * nb, std::memory_order_relaxed);
     return (int64_t)ncu * nb;
 }
 
