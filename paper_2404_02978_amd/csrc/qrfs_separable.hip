@@ -361,11 +361,6 @@ __global__ __launch_bounds__(64 * WV) __attribute__((
     const int ut = (U + 16 * MU - 1) / (16 * MU), vt = (V + 16 * NV - 1) / (16 * NV);
     const int64_t tiles = (int64_t)ut * vt, n = a.R * tiles;
     for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
-        // another block may have found a point off the grid since (a smaller word
-        // only says that the first block has not noted its yes yet)
-        if (it >= gridDim.x &&
-            __hip_atomic_load(g.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 2 * g.id)
-            return;
         const int64_t r = it / tiles;
         const int tile = (int)(it % tiles);
         const int u0 = (tile / vt) * 16 * MU, v0 = (tile % vt) * 16 * NV;
