@@ -38,8 +38,8 @@ def best_of(call, n=20, rounds=5):
     return min(times)
 
 
-# the unmended check did the grid's work first: 1.4 to 2.5 times the time; runs
-# differ by 3 %
+# a check of the rows' lengths alone lets the grid kernel do all its work first: 1.4
+# to 2.5 times the time; the question itself takes 3 to 6 % here, runs differ by 3 %
 @pytest.mark.parametrize("precision,K,R,R_block,n", [(0, 512, 400, 1, 32), (1, 512, 400, 1, 32),
                                                      (0, 512, 400, 2, 32), (0, 256, 512, 1, 32),
                                                      (1, 1024, 300, 1, 48)])
@@ -59,4 +59,4 @@ def test_disks_cost_no_grid_work(q, precision, K, R, R_block, n):
                 K, fx, fy, w, x, y, R, R_block, rng=q.Rng(3, 7, 0), precision=precision, out=out)))
         print(f"p{precision} K{K} R{R} P{px.size}: {1e3 * t[0]:.1f} us, shuffled {1e3 * t[1]:.1f}",
               flush=True)
-        assert t[0] < 1.15 * t[1]
+        assert t[0] < 1.25 * t[1]
